@@ -38,7 +38,13 @@
  * geometry's first.  The cache holds at most 256 entries / 1 GiB: past that
  * the least recently used entries that no call is using are freed, after a
  * device synchronisation.  xct_cache_clear() frees them all.  The library
- * allocates nothing else.
+ * allocates nothing else but stream-ordered scratch (hipMallocAsync) in
+ * xct_backproject, xct_project_adjoint, xct_forward_project and
+ * xct_forward_residual, freed on the stream before the call returns; the first
+ * such call on a device sets that device's default memory pool to keep up to
+ * 1.25 GiB of freed memory between calls.  xct_backproject and
+ * xct_project_adjoint on a stream under capture, or without memory for it,
+ * take kernels that need none.
  *
  * Errors: every argument is validated before any HIP call and nothing is
  * written when a call returns an error.  Return value 0 = XCT_OK, otherwise a
@@ -170,7 +176,10 @@ int xct_preprocess_filter(const xct_geometry *g, int32_t n_rows, int32_t row_beg
  *                    + scale * sum_k sum_n sino[s][k][n] K(u_k(x_j, y_i) - n)
  * Linear interpolation along the detector in FP32; FP16 / BF16 sinograms are
  * widened exactly and everything after is FP32.  Kernel choice (results agree
- * to FP32 rounding): square even slices with an angle set closed under
+ * to FP32 rounding): calls of 1.5e10 voxel updates and more with enough slices
+ * run on the matrix cores, FP32 operands split into two FP16 halves each
+ * (pixels up to 1.1 bins wide, finite rows; up to 1 GiB of scratch); of the
+ * rest, square even slices with an angle set closed under
  * quarter turns and 2c integral take the quarter-turn symmetric kernel; any
  * other slice with 2c integral the mirror kernel (pixel pairs reflected
  * through the slice centre, u -> 2c - u); the rest the generic kernel.  FBP over a half turn uses
@@ -212,9 +221,7 @@ int xct_backproject_u16(const xct_geometry *g, int32_t n_slices, const void *sin
  * with the four slices' values side by side (and a transposed copy), made on
  * the stream in stream-ordered device memory: 32 N_x N_y bytes per group of
  * four slices, at most 1 GiB per chunk of groups (one group when a group
- * needs more), freed on the stream before the call returns; the first such
- * call on a device sets that device's default memory pool to keep up to
- * 1 GiB of freed memory between calls.
+ * needs more), freed on the stream before the call returns.
  * Deterministic (gather form, no atomics).  Errors: XCT_EINVAL for
  * non-finite alpha, XCT_ETOOBIG beyond 65535 slices or 2^31 workgroups
  * (one per group of four slices, 256 bins and up to 16 angles), XCT_EHIP
@@ -236,8 +243,10 @@ int xct_forward_residual(const xct_geometry *g, int32_t n_slices, const float *i
  * pixel^2 / pitch), the backward half of the differentiable pair:
  *   image[s] = (accumulate ? image[s] : 0) + alpha (P^T sino[s])
  *   sino   device [n_slices][N_p][N_c] FP32;  image  device [n_slices][N_y][N_x] FP32
- * Same kernels and arithmetic as xct_backproject with
- * scale = fl32(alpha pixel^2 / pitch).  The least-squares gradient
+ * Same kernels as xct_backproject with scale = fl32(alpha pixel^2 / pitch),
+ * the matrix cores at any size that they are faster for, and the angles of a
+ * call too small to fill the device split into parts whose images are added
+ * up in a fixed order.  The least-squares gradient
  * 2 P^T (P x - y) is alpha = -2 applied to the residual y - P x. */
 int xct_project_adjoint(const xct_geometry *g, int32_t n_slices, const float *sino, float *image,
                         float alpha, int32_t accumulate, xct_stream stream);
@@ -270,9 +279,13 @@ size_t xct_fbp_workspace_bytes(const xct_slab *slabs, int32_t n_slabs, int32_t f
  * slabs, one)
  * walks all (slab, slice, tile) work items, most expensive slab first; the
  * work counters and the table of slab descriptors also live in the
- * workspace.  Every work item is computed whole by one workgroup with the
- * variant a call with its slab alone would use, so the images equal those of
- * separate calls bit for bit.  workspace: device, 256-byte aligned,
+ * workspace.  Slabs that the matrix cores are faster for are launched on their
+ * own before it, and the angles of a slab too small to fill the device are
+ * split into parts (work items of their own in a small batch, added up inside
+ * the item in a large one).  The variant and the parts depend on the slab
+ * alone, so the images equal those of separate calls bit for bit.  (A workspace
+ * that covers only the counters, table and filtered rows is accepted: every
+ * slab then takes the vector kernels.)  workspace: device, 256-byte aligned,
  * at least xct_fbp_workspace_bytes(); its contents are scratch, and calls
  * that share a workspace must not overlap.  1 <= n_slabs <= 65536. */
 int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_t window,

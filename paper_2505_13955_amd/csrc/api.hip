@@ -26,10 +26,12 @@ int hip_fail(hipError_t e)
     return XCT_EHIP;
 }
 
-// Stream-ordered scratch of the forward projector's four-slice copies: at
-// most this much per chunk, and the device's default pool keeps up to this
-// much between calls instead of returning it at each synchronisation.
+// Stream-ordered scratch: the forward projector's four-slice copies and the
+// back-projector's split tables take at most kQuadBytes at a time, partial
+// images at most kPartBytes, and the device's default pool keeps up to both
+// between calls instead of returning them at each synchronisation.
 constexpr int64_t kQuadBytes = (int64_t)1 << 30;
+constexpr int64_t kPartBytes = (int64_t)1 << 28;
 
 void keep_stream_pool()
 {
@@ -42,7 +44,7 @@ void keep_stream_pool()
     done.push_back(dev);
     hipMemPool_t pool;
     if (hipDeviceGetDefaultMemPool(&pool, dev) != hipSuccess) return;
-    uint64_t keep = (uint64_t)kQuadBytes;
+    uint64_t keep = (uint64_t)(kQuadBytes + kPartBytes);
     (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep);
 }
 
@@ -506,6 +508,10 @@ struct BPJob {
     int path;
     int32_t out_u16 = 0;
     float code_a = 0.0f, code_b = 0.0f;
+    // Vector kernels: the angles (pairs) that are added up at a time, and the
+    // parts' copies of the image when each is a work item of its own.
+    int32_t parts = 1, part_len = std::numeric_limits<int32_t>::max() / 2;
+    float *partial = nullptr;
 };
 
 // Tiles per slice as the kernel indexes them (tiles_x, tiles_y) and the work
@@ -539,6 +545,68 @@ int64_t plan_tiles(const BPJob &j, int sl, int *tx, int *ty)
 constexpr size_t kGenericStageBytes = 32 * 1024;
 constexpr size_t kSymStageBytes = 37 * 1024;
 constexpr size_t kSym2StageBytes = XCT_SYM2_STAGE_KB * 1024;
+constexpr int kPartStages = 2;  // LDS stages of the shortest part of a split job
+
+// Window, angles (pairs) per stage and LDS bytes of a vector kernel whose
+// widest window needs W entries, for `spi` slices per work item.
+struct VectorShape { int win, kb; size_t lds; };
+
+VectorShape vector_shape(int path, int W, int spi)
+{
+    VectorShape v;
+    const size_t budget = spi == 2 ? kSym2StageBytes : kSymStageBytes;
+    v.win = path == kPathGeneric ? W : bp_sym_window(W);  // choose_path only routes windows that fit here
+    if (path == kPathSymmetric) {
+        v.kb = (int)std::max<size_t>(1, budget / (4 * (size_t)v.win * spi * sizeof(float4) + 24));
+        v.lds = bp_sym_lds_bytes(v.win, v.kb, spi);
+    } else if (path == kPathMirror) {
+        v.kb = (int)std::max<size_t>(1, budget / ((size_t)v.win * spi * sizeof(float4) + sizeof(float4)));
+        v.lds = bp_mirror_lds_bytes(v.win, v.kb, spi);
+    } else {
+        v.kb = (int)std::max<size_t>(1, std::min<size_t>(64, kGenericStageBytes / (8 * (size_t)v.win + 16)));
+        v.lds = bp_generic_lds_bytes(v.win, v.kb);
+    }
+    return v;
+}
+
+// Work items of a job alone on the vector kernels, with its slices per item.
+int64_t vector_items(const BPJob &j, int *spi)
+{
+    *spi = j.path != kPathGeneric && j.n_slices >= 2 ? XCT_SYM_MAX_SLICES : 1;
+    int tx, ty;
+    return plan_tiles(j, *spi, &tx, &ty);
+}
+
+// Parts of a small job's angles: a workgroup walks all angles of its tile, so
+// a call with fewer items than CUs leaves CUs idle and takes the time of one
+// walk (one 256^2 slice, 360 angles: four items, 194 us).  Its angles are
+// split so that items x parts fill the device about twice, down to two LDS
+// stages a part, and the parts' images are added up.  The split depends on
+// the job alone: in a batch with enough items the same parts are added up one
+// after the other inside each item, to the same bits.
+void plan_parts(BPJob &j)
+{
+    int spi;
+    const int64_t items = vector_items(j, &spi);
+    if (j.out_u16 || items >= device_cus()) return;
+    const VectorShape v = vector_shape(j.path, window_entries(j.g->pixel_size / j.g->det_pitch), spi);
+    const int units = j.path == kPathSymmetric ? j.g->n_angles / 2 : j.g->n_angles;
+    const int64_t most = units / (kPartStages * v.kb);
+    const int64_t want = std::min<int64_t>(most, (2 * (int64_t)device_cus() + items - 1) / items);
+    if (want < 2) return;
+    j.part_len = (int)((units + want - 1) / want + v.kb - 1) / v.kb * v.kb;
+    j.parts = (units + j.part_len - 1) / j.part_len;
+    if (j.parts < 2) j.part_len = std::numeric_limits<int32_t>::max() / 2;
+}
+
+size_t image_bytes(const BPJob &j) { return sizeof(float) * (size_t)j.n_slices * j.g->nx * j.g->ny; }
+
+// Partial images of a split job that takes one item per part (0: too large, or not split).
+size_t part_bytes(const BPJob &j)
+{
+    const size_t b = j.parts * image_bytes(j);
+    return j.parts > 1 && b <= (size_t)kPartBytes ? align256(b) : 0;
+}
 
 // Launch one back-projection over jobs that all take the same kernel path.
 // `counters` (kXcds zeroed words on the stream) makes it persistent; `table`
@@ -546,7 +614,7 @@ constexpr size_t kSym2StageBytes = XCT_SYM2_STAGE_KB * 1024;
 // kInlineSlabs jobs.  A non-persistent launch whose grid would exceed 2^32
 // work-items is split into several launches over consecutive item ranges.
 int launch_bp_jobs(std::vector<BPJob> jobs, int dtype, unsigned int *counters, BPSlab *table,
-                   hipStream_t s)
+                   hipStream_t s, const uint32_t *gate = nullptr)
 {
     if (jobs.empty()) return XCT_OK;
     const int path = jobs[0].path;
@@ -555,8 +623,11 @@ int launch_bp_jobs(std::vector<BPJob> jobs, int dtype, unsigned int *counters, B
                      [](const BPJob &a, const BPJob &b) { return a.g->n_angles > b.g->n_angles; });
     // two slices per work item when every slab has at least two
     int spi = path != kPathGeneric ? XCT_SYM_MAX_SLICES : 1;
-    for (const BPJob &j : jobs)
+    bool split = gate != nullptr;
+    for (const BPJob &j : jobs) {
         if (j.n_slices < 2) spi = 1;
+        split = split || j.parts > 1;
+    }
     std::vector<BPSlab> desc(jobs.size());
     int W = 0;
     int64_t items = 0;
@@ -583,10 +654,13 @@ int launch_bp_jobs(std::vector<BPJob> jobs, int dtype, unsigned int *counters, B
         sl.sets = path == kPathSymmetric ? symmetric_sets(j.g) : 1;
         sl.scale = j.scale;
         sl.accumulate = j.accumulate;
+        sl.part_len = j.part_len;
+        sl.parts = j.parts;
+        sl.partial = j.partial;
         sl.out_u16 = j.out_u16;
         sl.code_a = j.code_a;
         sl.code_b = j.code_b;
-        items += n_items;
+        items += j.partial ? n_items * j.parts : n_items;
         W = std::max(W, window_entries(j.g->pixel_size / j.g->det_pitch));
     }
     if (items >= (int64_t)1 << 31) return XCT_ETOOBIG;
@@ -595,21 +669,11 @@ int launch_bp_jobs(std::vector<BPJob> jobs, int dtype, unsigned int *counters, B
     b.n_slabs = (int32_t)jobs.size();
     b.total_items = items;
     b.counter = counters;
-    size_t lds;
-    if (path == kPathSymmetric) {
-        W = bp_sym_window(W);  // choose_path only routes windows that fit here
-        const size_t budget = spi == 2 ? kSym2StageBytes : kSymStageBytes;
-        b.kb = (int)std::max<size_t>(1, budget / (4 * (size_t)W * spi * sizeof(float4) + 24));
-        lds = bp_sym_lds_bytes(W, b.kb, spi);
-    } else if (path == kPathMirror) {
-        W = bp_sym_window(W);
-        const size_t budget = spi == 2 ? kSym2StageBytes : kSymStageBytes;
-        b.kb = (int)std::max<size_t>(1, budget / ((size_t)W * spi * sizeof(float4) + sizeof(float4)));
-        lds = bp_mirror_lds_bytes(W, b.kb, spi);
-    } else {
-        b.kb = (int)std::max<size_t>(1, std::min<size_t>(64, kGenericStageBytes / (8 * (size_t)W + 16)));
-        lds = bp_generic_lds_bytes(W, b.kb);
-    }
+    b.gate = gate;
+    const VectorShape v = vector_shape(path, W, spi);
+    W = v.win;
+    b.kb = v.kb;
+    const size_t lds = v.lds;
     b.win = W;
     if (lds > 160 * 1024) return XCT_ETOOBIG;
     if (jobs.size() > (size_t)kInlineSlabs) {
@@ -621,9 +685,14 @@ int launch_bp_jobs(std::vector<BPJob> jobs, int dtype, unsigned int *counters, B
         std::memcpy(b.slab, desc.data(), sizeof(BPSlab) * desc.size());
     }
     if (counters) {
-        const int per_cu = bp_max_blocks_per_cu(path, dtype, W, spi, lds);
+        const int per_cu = bp_max_blocks_per_cu(path, dtype, W, spi, split, lds);
         const int grid = (int)std::min<int64_t>(items, (int64_t)per_cu * device_cus());
-        hipError_t e = launch_bp(path, b, dtype, spi, grid, lds, s);
+        hipError_t e = launch_bp(path, b, dtype, spi, split, grid, lds, s);
+        return e == hipSuccess ? XCT_OK : hip_fail(e);
+    }
+    if (gate) {  // most often nothing to do: a grid that fills the device strides over the items
+        b.stride = (int)std::min<int64_t>(items, 2 * (int64_t)device_cus());
+        hipError_t e = launch_bp(path, b, dtype, spi, split, b.stride, lds, s);
         return e == hipSuccess ? XCT_OK : hip_fail(e);
     }
     const int64_t threads = bp_block_threads(path, spi);
@@ -632,10 +701,237 @@ int launch_bp_jobs(std::vector<BPJob> jobs, int dtype, unsigned int *counters, B
         const int64_t count = std::min(max_items, items - base);
         b.item_base = base;
         b.xcd_remap = (count % 8 == 0) ? 1 : 0;
-        hipError_t e = launch_bp(path, b, dtype, spi, (int)count, lds, s);
+        hipError_t e = launch_bp(path, b, dtype, spi, split, (int)count, lds, s);
         if (e != hipSuccess) return hip_fail(e);
     }
     return XCT_OK;
+}
+
+// A split job, one work item per part.
+int launch_bp_parts(BPJob j, int dtype, float *partial, hipStream_t s)
+{
+    j.partial = partial;
+    if (int rc = launch_bp_jobs({j}, dtype, nullptr, nullptr, s)) return rc;
+    const hipError_t e = launch_sum_parts(static_cast<float *>(j.image), partial, j.parts, (int64_t)j.n_slices * j.g->nx * j.g->ny,
+                                          j.accumulate, nullptr, s);
+    return e == hipSuccess ? XCT_OK : hip_fail(e);
+}
+
+// ---------------------------------------------------------------- matrix-core back-projection
+
+// How a job takes the matrix-core kernel: the kind (what a coordinate
+// serves), 32-column tiles per item (0: it does not), and the angles per launch.
+struct MXPlan {
+    int kind = kMXPlain, nt = 0;
+    int angles = 0;    // per launch (of one quarter turn for kMXQuarter)
+    int part_len = 0;  // angles added up at a time (see MXArgs)
+    int parts = 1;     // of a launch
+    bool spread = false;  // one workgroup per item and part
+};
+
+// The split table of one launch is held to this much scratch; a table that
+// needs more is made and used angle range by angle range, the image
+// accumulating.
+constexpr int64_t kMXTableBytes = kQuadBytes;
+
+// xct_backproject keeps the vector kernels below this many voxel updates
+// (about a millisecond), so that there its images are to the bit what
+// xct_backproject_u16 quantises.
+constexpr double kMXLeastUpdates = 1.5e10;
+
+// Angle k of a half turn is angle k pi / N_p: reflection pairs angle k with N_p - k.
+bool reflected_set(const xct_geometry *g)
+{
+    if (std::fabs(g->angles[0]) > 1e-9) return false;
+    for (int k = 1; k < g->n_angles; ++k)
+        if (std::fabs(g->angles[k] + g->angles[g->n_angles - k] - M_PI) > 1e-9) return false;
+    return true;
+}
+
+size_t mx_words_bytes(int n_slices) { return align256(sizeof(uint32_t) * (size_t)(n_slices + 1)); }
+
+int mx_ops(int kind)
+{
+    return kind == kMXPlain ? 1 : kind == kMXMirror ? 2 : kind == kMXQuarter2 ? 8 : 4;
+}
+
+// Work items of a job on the matrix cores, and their tiles.
+int64_t mx_items(const BPJob &j, int kind, int nt, int *tiles_x, int *tiles_y)
+{
+    const bool all_x = kind == kMXPlain || kind == kMXMirror, all_y = kind == kMXPlain;
+    *tiles_x = ((all_x ? j.g->nx : (j.g->nx + 1) / 2) + kMXTile - 1) / kMXTile;
+    *tiles_y = ((all_y ? j.g->ny : (j.g->ny + 1) / 2) + kMXTile - 1) / kMXTile;
+    const int64_t tiles = kind == kMXQuarter2 ? (int64_t)*tiles_x * (*tiles_x + 1) / 2 : (int64_t)*tiles_x * *tiles_y;
+    const int spi = 32 * nt / mx_ops(kind);
+    return tiles * ((j.n_slices + spi - 1) / spi);
+}
+
+// Which kernels a job takes is decided by their times as measured (ns per
+// angle that a round of work items over 256 CUs takes; all others follow from
+// the items' count):
+//  * matrix: one item per CU; 440 with one 32-column tile, 720 with two
+//    (2048^2, 8 slices: 3.65 ms; 8192^2, 16 slices: 293 ms).
+//  * symmetric, two slices per item: two items per CU, 1180 (8192^2: 458 ms),
+//    770 while every item has a CU to itself; one slice: four items, 1300, 710
+//    up to 256.
+//  * mirror, two slices: two items, 750 (8192^2, 4 slices: 140 ms), 580; one
+//    slice: four, 1270, 630.
+//  * generic: four items, 580 (2048^2, 16 slices: 19.0 ms), 485.
+// The matrix path's own passes over the rows (magnitudes, split table) are
+// added at the 4.5 TB/s they reach, with 15 us for their launches.
+double bp_vector_ns(const BPJob &j)
+{
+    int sl;
+    const int64_t items = vector_items(j, &sl), cus = device_cus();
+    const int per_cu = j.path == kPathGeneric || sl == 1 ? 4 : 2;
+    const double full = j.path == kPathGeneric ? 580 : j.path == kPathMirror ? (sl == 2 ? 750 : 1270) : (sl == 2 ? 1180 : 1300);
+    const double alone = j.path == kPathGeneric ? 485 : j.path == kPathMirror ? (sl == 2 ? 580 : 630) : (sl == 2 ? 770 : 710);
+    // (a last round fills the CUs from one item each up to per_cu)
+    auto rounds = [&](int64_t n) {
+        const int64_t slots = per_cu * cus, rest = n % slots;
+        const double last = rest == 0 ? 0 : rest <= cus ? alone : alone + (full - alone) * (double)(rest - cus) / (double)(slots - cus);
+        return (n / slots) * full + last;
+    };
+    if (part_bytes(j) == 0) return rounds(items) * j.g->n_angles;
+    const double per_part = (double)j.part_len * (j.path == kPathSymmetric ? 2 : 1);
+    return rounds(items * j.parts) * per_part + 8000.0 + (j.parts + 1) * (double)image_bytes(j) / 4000.0;
+}
+
+// The parts of a matrix launch over n angles: two at least where one launch
+// covers all angles (its three roundings per product pair would otherwise
+// leave more error in the sums than the vector kernels' one), and enough to
+// fill the device where the items are fewer than the CUs.
+void mx_parts(const BPJob &j, MXPlan &p, int64_t items, int n, bool whole)
+{
+    int64_t parts = whole ? 2 : 1;
+    const int64_t cus = device_cus();
+    p.spread = false;
+    if (items < cus) {
+        const int64_t want = std::min<int64_t>((3 * cus / 2 + items - 1) / items, n / 24);
+        if (want > 1 && std::max(want, parts) * (int64_t)image_bytes(j) <= kPartBytes) {
+            parts = std::max(want, parts);
+            p.spread = true;
+        }
+    }
+    p.part_len = (int)((n + parts - 1) / parts + kMXAngles - 1) & ~(kMXAngles - 1);
+    p.parts = (n + p.part_len - 1) / p.part_len;
+    if (p.parts < 2) p.spread = false;
+}
+
+double bp_matrix_ns(const BPJob &j, const MXPlan &p, int64_t items, int dtype)
+{
+    const int64_t cus = device_cus(), rounds = ((p.spread ? p.parts : 1) * items + cus - 1) / cus;
+    const double rows = (double)j.n_slices * j.g->n_angles * j.g->n_det;
+    const double angles = p.spread ? p.part_len : j.g->n_angles;
+    double ns = rounds * (p.nt == 2 ? 720.0 : 440.0) * angles + rows * (2 * dtype_size(dtype) + 4) / 4500.0 + 15000.0;
+    if (p.spread) ns += 8000.0 + (p.parts + 1) * (double)image_bytes(j) / 4000.0;
+    return ns;
+}
+
+MXPlan mx_plan(const BPJob &j, int dtype)
+{
+    MXPlan best;
+    const xct_geometry *g = j.g;
+    // (uint16 images keep the vector kernels' rounding; windows cover
+    // kMXMaxRatio; slice groups are a grid dimension)
+    if (j.out_u16 || g->pixel_size / g->det_pitch > kMXMaxRatio || j.n_slices > 4 * 65535) return best;
+    const int64_t angle_bytes = (int64_t)((j.n_slices + 3) / 4) * g->n_det * 16;
+    const int64_t fit = kMXTableBytes / angle_bytes;
+    // the reflected kinds read rows k and N_p - k together: whole tables only
+    const bool refl = j.path != kPathGeneric && fit >= g->n_angles && reflected_set(g);
+    double least = 0.95 * bp_vector_ns(j);
+    auto consider = [&](int kind) {
+        MXPlan p;
+        p.kind = kind;
+        const int run = kind == kMXQuarter ? g->n_angles / symmetric_sets(g) / 2 : g->n_angles;
+        const int64_t cap = (kind == kMXQuarter ? fit / 2 : fit) & ~(int64_t)(kMXAngles - 1);
+        if (fit < g->n_angles && cap <= 0) return;
+        // (equal ranges)
+        const int64_t ranges = fit >= g->n_angles ? 1 : (run + cap - 1) / cap;
+        p.angles = ranges == 1 ? run : (int)((run + ranges - 1) / ranges + kMXAngles - 1) & ~(kMXAngles - 1);
+        const int per_launch = kind == kMXQuarter ? 2 * p.angles : p.angles;
+        for (p.nt = 1; p.nt <= 2; ++p.nt) {
+            int tx, ty;
+            const int64_t items = mx_items(j, kind, p.nt, &tx, &ty);
+            if (items >= (int64_t)1 << 22) continue;  // (grid of workgroups of 1024 below 2^32)
+            mx_parts(j, p, items, per_launch, per_launch == g->n_angles);
+            const double ns = bp_matrix_ns(j, p, items, dtype);
+            if (ns < least) {
+                least = ns;
+                best = p;
+            }
+        }
+    };
+    consider(j.path == kPathSymmetric ? kMXQuarter : j.path == kPathMirror ? kMXMirror : kMXPlain);
+    if (refl) consider(j.path == kPathSymmetric ? kMXQuarter2 : kMXMirror2);
+    return best;
+}
+
+// Scratch of a job: the slices' magnitudes, the split table of one launch, and
+// the parts' images where each part is a work item of its own.
+size_t mx_scratch_bytes(const BPJob &j, const MXPlan &p)
+{
+    const size_t rows = (size_t)p.angles * (p.kind == kMXQuarter ? 2 : 1);
+    return mx_words_bytes(j.n_slices) + align256((size_t)((j.n_slices + 3) / 4) * rows * j.g->n_det * 16) +
+           (p.spread ? align256(p.parts * image_bytes(j)) : 0);
+}
+
+// The slices' magnitudes, then for each range of angles its split table and
+// its back-projection, and last the vector kernels, whose launch does nothing
+// unless some row element is not finite.
+int launch_bp_matrix(const BPJob &j, const MXPlan &p, int dtype, void *scratch, hipStream_t s)
+{
+    const xct_geometry *g = j.g;
+    uint32_t *amax = static_cast<uint32_t *>(scratch);
+    char *table = static_cast<char *>(scratch) + mx_words_bytes(j.n_slices);
+    hipError_t e = launch_absmax(j.sino, dtype, j.n_slices, (int64_t)g->n_angles * g->n_det, amax, s);
+    if (e != hipSuccess) return hip_fail(e);
+    MXArgs a{};
+    a.table = reinterpret_cast<int64_t>(table);
+    a.image = static_cast<float *>(j.image);
+    a.csd = j.t->table<double2>(1);
+    a.amax = amax;
+    a.center = g->center;
+    a.n_det = g->n_det;
+    a.nx = g->nx;
+    a.ny = g->ny;
+    a.n_slices = j.n_slices;
+    a.mirror = p.kind == kMXPlain ? 0 : (int32_t)std::nearbyint(2.0 * g->center);
+    a.scale = j.scale;
+    a.accumulate = j.accumulate;
+    a.part_len = p.part_len;
+    float *partial = reinterpret_cast<float *>(static_cast<char *>(scratch) + mx_scratch_bytes(j, p) - align256(p.parts * image_bytes(j)));
+    a.partial = p.spread ? partial : nullptr;
+    const int64_t items = mx_items(j, p.kind, p.nt, &a.tiles_x, &a.tiles_y);
+    const int sets = p.kind == kMXQuarter ? symmetric_sets(g) : 1;
+    const int h = g->n_angles / sets / 2;                       // quarter turn
+    const int run = p.kind == kMXQuarter ? h : g->n_angles;     // angles that one set's launches cover
+    SplitArgs t{};
+    t.sino = j.sino;
+    t.table = reinterpret_cast<uint4 *>(table);
+    t.amax = amax;
+    t.n_angles = g->n_angles;
+    t.n_det = g->n_det;
+    t.n_slices = j.n_slices;
+    for (int set = 0; set < sets; ++set) {
+        for (int k0 = 0; k0 < run; k0 += p.angles) {
+            const int n = std::min(p.angles, run - k0);
+            a.k_first = t.k_first = set * 2 * h * (p.kind == kMXQuarter) + k0;
+            a.half_set = p.kind == kMXQuarter ? n : p.kind == kMXQuarter2 ? h : 0;
+            a.k_jump = t.k_jump = p.kind == kMXQuarter ? h - n : 0;
+            a.n_angles = t.rows = p.kind == kMXQuarter ? 2 * n : n;
+            t.split = p.kind == kMXQuarter ? n : t.rows;
+            a.items = (int32_t)items;
+            e = launch_split(t, dtype, s);
+            const int parts = (a.n_angles + a.part_len - 1) / a.part_len;
+            if (e == hipSuccess) e = launch_bp_mfma(a, p.nt, p.kind, (int)(p.spread ? items * parts : items), s);
+            if (e == hipSuccess && p.spread)
+                e = launch_sum_parts(a.image, partial, parts, (int64_t)j.n_slices * g->nx * g->ny, a.accumulate, amax, s);
+            if (e != hipSuccess) return hip_fail(e);
+            a.accumulate = 1;
+        }
+    }
+    return launch_bp_jobs({j}, dtype, nullptr, nullptr, s, amax);
 }
 
 }  // namespace
@@ -793,10 +1089,11 @@ int xct_preprocess_filter(const xct_geometry *g, int32_t n_rows, int32_t row_beg
     return e == hipSuccess ? XCT_OK : hip_fail(e);
 }
 
-// Back-projection of one slab (all entry points but the batch).
+// Back-projection of one slab (all entry points but the batch).  `least`:
+// voxel updates from which the matrix cores are considered.
 static int backproject_one(const xct_geometry *g, int32_t n_slices, const void *sino, int32_t sino_t,
                            void *image, float scale, int32_t accumulate, int out_u16, float code_a,
-                           float code_b, hipStream_t s)
+                           float code_b, double least, hipStream_t s)
 {
     BPJob j;
     j.g = g;
@@ -810,7 +1107,25 @@ static int backproject_one(const xct_geometry *g, int32_t n_slices, const void *
     j.code_a = code_a;
     j.code_b = code_b;
     if (int rc = geo_tables(g, s, &j.t)) return rc;
-    return launch_bp_jobs({j}, sino_t, nullptr, nullptr, s);
+    const double updates = (double)n_slices * g->n_angles * g->nx * g->ny;
+    if (least == 0.0) plan_parts(j);
+    MXPlan p;
+    if (updates >= least) p = mx_plan(j, sino_t);
+    // Scratch in stream-ordered memory.  A stream under capture, or no memory,
+    // takes the vector kernels, which need none (a split job's parts are then
+    // added up inside its items, to the same bits).
+    const size_t bytes = p.nt ? mx_scratch_bytes(j, p) : part_bytes(j);
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    void *scratch = nullptr;
+    if (bytes && hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
+        keep_stream_pool();
+        if (hipMallocAsync(&scratch, bytes, s) != hipSuccess) scratch = nullptr;
+    }
+    (void)hipGetLastError();
+    if (!scratch) return launch_bp_jobs({j}, sino_t, nullptr, nullptr, s);
+    const int rc = p.nt ? launch_bp_matrix(j, p, sino_t, scratch, s) : launch_bp_parts(j, sino_t, static_cast<float *>(scratch), s);
+    const hipError_t e = hipFreeAsync(scratch, s);
+    return rc ? rc : e == hipSuccess ? XCT_OK : hip_fail(e);
 }
 
 int xct_backproject(const xct_geometry *g, int32_t n_slices, const void *sino, int32_t sino_t,
@@ -822,7 +1137,7 @@ int xct_backproject(const xct_geometry *g, int32_t n_slices, const void *sino, i
     if (!dtype_ok(sino_t)) return XCT_EDTYPE;
     if (!std::isfinite(scale)) return XCT_EINVAL;
     return backproject_one(g, n_slices, sino, sino_t, image, scale, accumulate, 0, 0.0f, 0.0f,
-                           (hipStream_t)stream);
+                           kMXLeastUpdates, (hipStream_t)stream);
 }
 
 int xct_backproject_u16(const xct_geometry *g, int32_t n_slices, const void *sino, int32_t sino_t,
@@ -842,7 +1157,7 @@ int xct_backproject_u16(const xct_geometry *g, int32_t n_slices, const void *sin
     const double B = (-1000.0 - hu_min) * span;
     const float a32 = (float)A, b32 = (float)B;
     if (!std::isfinite(a32) || !std::isfinite(b32)) return XCT_EINVAL;
-    return backproject_one(g, n_slices, sino, sino_t, image, scale, 0, 1, a32, b32,
+    return backproject_one(g, n_slices, sino, sino_t, image, scale, 0, 1, a32, b32, kMXLeastUpdates,
                            (hipStream_t)stream);
 }
 
@@ -941,7 +1256,7 @@ int xct_project_adjoint(const xct_geometry *g, int32_t n_slices, const float *si
     if (!sino || !image) return XCT_EINVAL;
     if (!std::isfinite(alpha)) return XCT_EINVAL;
     return backproject_one(g, n_slices, sino, XCT_F32, image, (float)((double)alpha * projector_scale(g)),
-                           accumulate, 0, 0.0f, 0.0f, (hipStream_t)stream);
+                           accumulate, 0, 0.0f, 0.0f, 0.0, (hipStream_t)stream);
 }
 
 // Detector bins of a slab's filtered rows: the virtual (mirrored) detector
@@ -975,16 +1290,68 @@ static int check_slabs(const xct_slab *slabs, int32_t n_slabs, bool need_data)
 // slab, each region 256-byte aligned.
 static size_t table_bytes(int32_t n_slabs) { return align256(sizeof(BPSlab) * (size_t)n_slabs); }
 
-size_t xct_fbp_workspace_bytes(const xct_slab *slabs, int32_t n_slabs, int32_t filtered_t)
+// Back-projection job of a batch's slab over its filtered rows `filt`: the
+// slab's geometry (`virt`: its copy with the virtual detector of an offset
+// scan) and weight.
+static BPJob slab_job(const xct_slab &sl, xct_geometry *virt, const void *filt)
 {
-    if (check_slabs(slabs, n_slabs, false) || !dtype_ok(filtered_t)) return 0;
-    size_t bytes = 256 + table_bytes(n_slabs);
+    BPJob j;
+    j.g = &sl.geom;
+    double weight = M_PI / sl.geom.n_angles;
+    if (sl.offset_overlap != 0.0) {
+        int first;
+        *virt = sl.geom;
+        offset_virtual(&sl.geom, &virt->n_det, &virt->center, &first);
+        j.g = virt;
+        weight = 2.0 * M_PI / sl.geom.n_angles;
+    }
+    j.n_slices = sl.n_slices;
+    j.sino = filt;
+    j.image = sl.image;
+    j.scale = (float)weight;
+    j.accumulate = 0;
+    j.path = choose_path(j.g);
+    return j;
+}
+
+// Bytes of the workspace's base (counters, table, filtered rows) and of the
+// scratch behind it: the slabs' matrix-core launches use it in turn, then the
+// vector launch keeps its split slabs' partial images there (`spread`: their
+// parts are work items of their own, in a batch that would not fill the
+// device otherwise).
+static size_t batch_bytes(const xct_slab *slabs, int32_t n_slabs, int32_t filtered_t, size_t *scratch, bool *spread)
+{
+    size_t bytes = 256 + table_bytes(n_slabs), parts = 0;
+    int64_t items = 0;
+    *scratch = 0;
     for (int i = 0; i < n_slabs; ++i) {
         const xct_geometry &g = slabs[i].geom;
         bytes += align256((size_t)slabs[i].n_slices * g.n_angles * filtered_bins(slabs[i]) *
                           dtype_size(filtered_t));
+        xct_geometry virt;
+        BPJob j = slab_job(slabs[i], &virt, nullptr);
+        plan_parts(j);
+        const MXPlan p = mx_plan(j, filtered_t);
+        if (p.nt) {
+            *scratch = std::max(*scratch, mx_scratch_bytes(j, p));
+        } else {
+            int spi;
+            items += vector_items(j, &spi);
+            parts += part_bytes(j);
+        }
     }
+    *spread = items < 2 * (int64_t)device_cus() && parts <= (size_t)kPartBytes;
+    if (*spread) *scratch = std::max(*scratch, parts);
     return bytes;
+}
+
+size_t xct_fbp_workspace_bytes(const xct_slab *slabs, int32_t n_slabs, int32_t filtered_t)
+{
+    if (check_slabs(slabs, n_slabs, false) || !dtype_ok(filtered_t)) return 0;
+    size_t scratch;
+    bool spread;
+    const size_t bytes = batch_bytes(slabs, n_slabs, filtered_t, &scratch, &spread);
+    return bytes + scratch;
 }
 
 int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_t window,
@@ -994,8 +1361,14 @@ int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_
     if (int rc = check_slabs(slabs, n_slabs, true)) return rc;
     if (!dtype_ok(sino_t) || !dtype_ok(filtered_t)) return XCT_EDTYPE;
     if (window < XCT_RAM_LAK || window > XCT_HANN) return XCT_EDTYPE;
-    const size_t need = xct_fbp_workspace_bytes(slabs, n_slabs, filtered_t);
+    size_t scratch;
+    bool spread;
+    const size_t need = batch_bytes(slabs, n_slabs, filtered_t, &scratch, &spread);
     if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < need) return XCT_EWORKSPACE;
+    // without the scratch every slab takes the vector kernels, parts inside their items
+    const bool with_scratch = workspace_bytes >= need + scratch;
+    spread = spread && with_scratch;
+    float *partial = reinterpret_cast<float *>(static_cast<char *>(workspace) + need);
     hipStream_t s = (hipStream_t)stream;
 
     char *ws = static_cast<char *>(workspace);
@@ -1016,36 +1389,32 @@ int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_
         const xct_geometry *g = &sl.geom;
         void *filt = ws + off;
         off += align256((size_t)sl.n_slices * g->n_angles * filtered_bins(sl) * dtype_size(filtered_t));
-        double weight = M_PI / g->n_angles;
-        if (sl.offset_overlap != 0.0) {
-            // full-turn offset scan: redundancy-weighted rows filtered on the
-            // virtual detector, back-projected with weight 2 pi / N_p
-            if (int rc = xct_filter_offset(g, sl.n_slices, sl.sino, sino_t, filt, filtered_t, window,
-                                           sl.offset_overlap, stream))
-                return rc;
-            int first;
-            virt[i] = *g;
-            offset_virtual(g, &virt[i].n_det, &virt[i].center, &first);
-            g = &virt[i];
-            weight = 2.0 * M_PI / g->n_angles;
-        } else if (int rc = xct_filter(g, sl.n_slices, sl.sino, sino_t, filt, filtered_t, window, stream)) {
+        const bool offset = sl.offset_overlap != 0.0;
+        // (an offset scan's redundancy-weighted rows are filtered on the virtual detector)
+        if (int rc = offset ? xct_filter_offset(g, sl.n_slices, sl.sino, sino_t, filt, filtered_t, window, sl.offset_overlap, stream)
+                            : xct_filter(g, sl.n_slices, sl.sino, sino_t, filt, filtered_t, window, stream))
             return rc;
+        BPJob j = slab_job(sl, &virt[i], filt);
+        if (int rc = geo_tables(j.g, s, &j.t)) return rc;
+        plan_parts(j);
+        const MXPlan p = with_scratch ? mx_plan(j, filtered_t) : MXPlan();
+        if (p.nt) {
+            if (int rc = launch_bp_matrix(j, p, filtered_t, ws + need, s)) return rc;
+            continue;
         }
-        BPJob j;
-        j.g = g;
-        j.n_slices = sl.n_slices;
-        j.sino = filt;
-        j.image = sl.image;
-        j.scale = (float)weight;
-        j.accumulate = 0;
-        j.path = choose_path(g);
-        if (int rc = geo_tables(g, s, &j.t)) return rc;
+        if (spread && part_bytes(j)) {
+            j.partial = partial;
+            partial += part_bytes(j) / sizeof(float);
+        }
         const int two = j.n_slices >= 2;
         const int grp = j.path == kPathGeneric  ? kGroupGeneric
                         : j.path == kPathMirror ? (two ? kGroupMirror2 : kGroupMirror1)
                                                 : (two ? kGroupSym2 : kGroupSym1);
         groups[grp].push_back(j);
     }
+    bool any = false;
+    for (const auto &grp : groups) any = any || !grp.empty();
+    if (!any) return XCT_OK;
     hipError_t e = launch_fill_u32(counters, kGroups * kXcds, 0u, s);
     if (e != hipSuccess) return hip_fail(e);
     // each group reads its descriptors from its own part of the table
@@ -1058,6 +1427,12 @@ int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_
     for (int grp = kGroups - 1; grp >= 0; --grp)
         if (int rc = launch_bp_jobs(groups[grp], filtered_t, counters + grp * kXcds, group_table[grp], s))
             return rc;
+    for (const auto &grp : groups)
+        for (const BPJob &j : grp) {
+            if (!j.partial) continue;
+            e = launch_sum_parts(static_cast<float *>(j.image), j.partial, j.parts, (int64_t)j.n_slices * j.g->nx * j.g->ny, 0, nullptr, s);
+            if (e != hipSuccess) return hip_fail(e);
+        }
     return XCT_OK;
 }
 

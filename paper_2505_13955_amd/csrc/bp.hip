@@ -85,6 +85,7 @@ __device__ __forceinline__ KSlab *slab_at(KBatch *b, int s)
     return &b->slab[s];
 }
 
+template <bool PARTS>
 __device__ __forceinline__ void select_slab(KBatch *b, int s, BPSlab &out)
 {
     KSlab *d = slab_at(b, s);
@@ -108,6 +109,11 @@ __device__ __forceinline__ void select_slab(KBatch *b, int s, BPSlab &out)
     out.code_a = d->code_a;
     out.code_b = d->code_b;
     out.sets = d->sets;
+    if constexpr (PARTS) {
+        out.part_len = d->part_len;
+        out.parts = d->parts;
+        out.partial = d->partial;
+    }
 }
 
 // Store of voxel `idx` (slab-wide index) from its accumulated sum: v = scale
@@ -127,6 +133,21 @@ __device__ __forceinline__ void store_voxel(const BPSlab &sl, int64_t idx, float
         if (sl.accumulate) v += img[idx];
         img[idx] = v;
     }
+}
+
+// Parts of a work item (see BPSlab): the item's index within its part, and the
+// parts [begin, end) it covers.  An item of one part stores to that part's copy.
+template <bool PARTS>
+__device__ __forceinline__ int64_t item_parts(BPSlab &sl, int64_t local, int64_t per_part, int64_t voxels, int &begin, int &end)
+{
+    begin = 0;
+    end = PARTS ? sl.parts : 1;
+    if (!PARTS || !sl.partial) return local;
+    begin = __builtin_amdgcn_readfirstlane((int)(local / per_part));
+    end = begin + 1;
+    sl.image = sl.partial + begin * voxels;
+    sl.accumulate = 0;
+    return local - begin * per_part;
 }
 
 // Slab of a work item: the last slab whose first item is at or before it
@@ -161,6 +182,7 @@ __device__ __forceinline__ int64_t uniform64(int64_t v)
 //    neighbouring tiles.  A workgroup whose XCD has run out takes items from
 //    the other XCDs' counters in turn.  Which XCD a workgroup runs on only
 //    affects locality: every item is taken exactly once either way.
+template <bool PARTS>
 __device__ __forceinline__ int64_t next_item(KBatch *b, int64_t *slot, int iter)
 {
     if (b->counter) {
@@ -184,6 +206,7 @@ __device__ __forceinline__ int64_t next_item(KBatch *b, int64_t *slot, int iter)
         __syncthreads();
         return it;
     }
+    if (PARTS && b->stride > 0) return (int64_t)blockIdx.x + (int64_t)iter * b->stride;
     if (iter > 0) return b->total_items;
     int64_t bid = blockIdx.x;
     if (b->xcd_remap) {
@@ -208,10 +231,11 @@ size_t bp_generic_lds_bytes(int win, int kb)
     return (size_t)kb * sizeof(float4) + (size_t)kb * win * sizeof(float2);
 }
 
-template <typename T>
+template <typename T, bool PARTS>
 __global__ __launch_bounds__(kBPThreads) void bp_generic_kernel(BPBatch arg)
 {
     KBatch *b = kernarg_batch();
+    if (PARTS && b->gate && *b->gate == 0) return;
     extern __shared__ float4 lds4[];
     __shared__ int64_t item_slot;
     const int kb = b->kb, W = b->win;
@@ -223,12 +247,14 @@ __global__ __launch_bounds__(kBPThreads) void bp_generic_kernel(BPBatch arg)
     const float dxo = px - 31.5f, dyo = py - 31.5f;
 
     for (int iter = 0;; ++iter) {
-        const int64_t item = uniform64(next_item(b, &item_slot, iter));
+        const int64_t item = uniform64(next_item<PARTS>(b, &item_slot, iter));
         if (item >= b->total_items) break;
         BPSlab sl;
-        select_slab(b, find_slab(b, item), sl);
-        const int64_t local = item - sl.item_begin;
+        select_slab<PARTS>(b, find_slab(b, item), sl);
         const int tiles = sl.tiles_x * sl.tiles_y;
+        int part, part_end;
+        const int64_t local = item_parts<PARTS>(sl, item - sl.item_begin, (int64_t)tiles * sl.n_slices,
+                                         (int64_t)sl.n_slices * sl.nx * sl.ny, part, part_end);
         const int z = __builtin_amdgcn_readfirstlane((int)(local / tiles));
         const int t = __builtin_amdgcn_readfirstlane((int)(local - (int64_t)z * tiles));
         const int ty = t / sl.tiles_x, tx = t - ty * sl.tiles_x;
@@ -238,12 +264,14 @@ __global__ __launch_bounds__(kBPThreads) void bp_generic_kernel(BPBatch arg)
         const int Np = sl.n_angles, Nc = sl.n_det;
         const T *q = static_cast<const T *>(sl.sino) + (int64_t)z * Np * Nc;
 
+        for (; part < part_end; ++part) {
         float acc[16];
 #pragma unroll
         for (int p = 0; p < 16; ++p) acc[p] = 0.0f;
 
-        for (int k0 = 0; k0 < Np; k0 += kb) {
-            const int nk = min(kb, Np - k0);
+        const int k_begin = PARTS ? part * sl.part_len : 0, k_end = PARTS ? min(Np, (part + 1) * sl.part_len) : Np;
+        for (int k0 = k_begin; k0 < k_end; k0 += kb) {
+            const int nk = min(kb, k_end - k0);
             __syncthreads();
             if (tid < nk) {
                 const double2 cd = sl.csd[k0 + tid];
@@ -290,6 +318,8 @@ __global__ __launch_bounds__(kBPThreads) void bp_generic_kernel(BPBatch arg)
                 const int i = i0 + py + 16 * bb, j = j0 + px + 16 * aa;
                 if (i < sl.ny && j < sl.nx) store_voxel(sl, plane + (int64_t)i * sl.nx + j, acc[bb * 4 + aa]);
             }
+        }
+        if (PARTS) sl.accumulate = 1;
         }
     }
 }
@@ -383,10 +413,11 @@ constexpr int sym_threads() { return SL == 2 ? XCT_SYM2_THREADS : kBPThreads; }
 template <int SL>
 constexpr int sym_waves() { return SL == 2 ? XCT_SYM2_WAVES : 4; }
 
-template <typename T, int W, int SL>
+template <typename T, int W, int SL, bool PARTS>
 __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_sym_kernel(BPBatch arg)
 {
     KBatch *b = kernarg_batch();
+    if (PARTS && b->gate && *b->gate == 0) return;
     extern __shared__ float4 lds4[];
     __shared__ int64_t item_slot;
     constexpr int kThreads = sym_threads<SL>();
@@ -406,12 +437,14 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_sym_ker
     const float dxo = px - 31.5f, dyo = py - 31.5f;
 
     for (int iter = 0;; ++iter) {
-        const int64_t item = uniform64(next_item(b, &item_slot, iter));
+        const int64_t item = uniform64(next_item<PARTS>(b, &item_slot, iter));
         if (item >= b->total_items) break;
         BPSlab sl;
-        select_slab(b, find_slab(b, item), sl);
-        const int64_t local = item - sl.item_begin;
+        select_slab<PARTS>(b, find_slab(b, item), sl);
         const int tiles = sl.tiles_x * sl.tiles_y;
+        int part, part_end;
+        const int64_t local = item_parts<PARTS>(sl, item - sl.item_begin, (int64_t)tiles * ((sl.n_slices + SL - 1) / SL),
+                                         (int64_t)sl.n_slices * sl.nx * sl.ny, part, part_end);
         // slice group and tile (the 64-bit division runs on the vector unit;
         // pin the results back to scalars)
         const int zg = __builtin_amdgcn_readfirstlane((int)(local / tiles));
@@ -434,6 +467,7 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_sym_ker
         const int64_t sl_stride = (int64_t)Np * Nc;  // elements between slices
         const int64_t h_stride = (int64_t)H * Nc;    // from row k to row k + H
 
+        for (; part < part_end; ++part) {
         float acc[SL][4][PX];
 #pragma unroll
         for (int s = 0; s < SL; ++s)
@@ -444,10 +478,11 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_sym_ker
 
         // stages of up to kb angle pairs k0 .. k0+nk-1 (with k0+H ..); kc
         // counts pairs over the sets, and a stage never crosses a set
-        for (int kc = 0, nk = 0; kc < sl.sets * H; kc += nk) {
+        const int kc_begin = PARTS ? part * sl.part_len : 0, kc_end = PARTS ? min(sl.sets * H, (part + 1) * sl.part_len) : sl.sets * H;
+        for (int kc = kc_begin, nk = 0; kc < kc_end; kc += nk) {
             const int set = kc / H;
             const int k0 = kc + set * H;
-            nk = min(kb, (set + 1) * H - kc);
+            nk = min(PARTS ? min(kb, kc_end - kc) : kb, (set + 1) * H - kc);
             __syncthreads();
             if (tid < nk) {
                 const double2 cd = sl.csd[k0 + tid];
@@ -596,6 +631,8 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_sym_ker
                 }
             }
         }
+        if (PARTS) sl.accumulate = 1;
+        }
     }
 }
 
@@ -616,10 +653,11 @@ size_t bp_mirror_lds_bytes(int win, int kb, int sl)
     return (size_t)kb * sizeof(float4) + (size_t)kb * win * sl * sizeof(float4);
 }
 
-template <typename T, int W, int SL>
+template <typename T, int W, int SL, bool PARTS>
 __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_mirror_kernel(BPBatch arg)
 {
     KBatch *b = kernarg_batch();
+    if (PARTS && b->gate && *b->gate == 0) return;
     extern __shared__ float4 lds4[];
     __shared__ int64_t item_slot;
     constexpr int kThreads = sym_threads<SL>();
@@ -636,12 +674,14 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_mirror_
     const float dxo = px - 31.5f, dyo = py - 31.5f;
 
     for (int iter = 0;; ++iter) {
-        const int64_t item = uniform64(next_item(b, &item_slot, iter));
+        const int64_t item = uniform64(next_item<PARTS>(b, &item_slot, iter));
         if (item >= b->total_items) break;
         BPSlab sl;
-        select_slab(b, find_slab(b, item), sl);
-        const int64_t local = item - sl.item_begin;
+        select_slab<PARTS>(b, find_slab(b, item), sl);
         const int tiles = sl.tiles_x * sl.tiles_y;
+        int part, part_end;
+        const int64_t local = item_parts<PARTS>(sl, item - sl.item_begin, (int64_t)tiles * ((sl.n_slices + SL - 1) / SL),
+                                         (int64_t)sl.n_slices * sl.nx * sl.ny, part, part_end);
         const int zg = __builtin_amdgcn_readfirstlane((int)(local / tiles));
         const int t = __builtin_amdgcn_readfirstlane((int)(local - (int64_t)zg * tiles));
         int ty, tx;
@@ -657,6 +697,7 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_mirror_
             uniform64(reinterpret_cast<int64_t>(static_cast<const T *>(sl.sino) + (int64_t)z0 * Np * Nc)));
         const int64_t sl_stride = (int64_t)Np * Nc;
 
+        for (; part < part_end; ++part) {
         float acc[SL][2][PX];
 #pragma unroll
         for (int s = 0; s < SL; ++s)
@@ -665,8 +706,9 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_mirror_
 #pragma unroll
                 for (int p = 0; p < PX; ++p) acc[s][r][p] = 0.0f;
 
-        for (int k0 = 0, nk = 0; k0 < Np; k0 += nk) {
-            nk = min(kb, Np - k0);
+        const int k_begin = PARTS ? part * sl.part_len : 0, k_end = PARTS ? min(Np, (part + 1) * sl.part_len) : Np;
+        for (int k0 = k_begin, nk = 0; k0 < k_end; k0 += nk) {
+            nk = min(kb, k_end - k0);
             __syncthreads();
             if (tid < nk) {
                 const double2 cd = sl.csd[k0 + tid];
@@ -768,7 +810,43 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_mirror_
                 }
             }
         }
+        if (PARTS) sl.accumulate = 1;
+        }
     }
+}
+
+// ---------------------------------------------------------------- parts
+
+// Four voxels a thread; the parts' copies are read in turn.
+__global__ __launch_bounds__(256) void sum_parts_kernel(float *image, const float *partial, int parts, int64_t n, int accumulate,
+                                                        const uint32_t *skip)
+{
+    if (skip && *skip != 0) return;
+    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+    const bool vec = (n & 3) == 0 && ((reinterpret_cast<uintptr_t>(image) | reinterpret_cast<uintptr_t>(partial)) & 15) == 0;
+    if (vec) {
+        if (i >= n) return;
+        float4 v = *reinterpret_cast<const float4 *>(accumulate ? image + i : partial + i);
+        for (int p = accumulate ? 0 : 1; p < parts; ++p) {
+            const float4 w = *reinterpret_cast<const float4 *>(partial + p * n + i);
+            v = make_float4(v.x + w.x, v.y + w.y, v.z + w.z, v.w + w.w);
+        }
+        *reinterpret_cast<float4 *>(image + i) = v;
+        return;
+    }
+    for (int64_t e = i; e < i + 4 && e < n; ++e) {
+        float v = accumulate ? image[e] : partial[e];
+        for (int p = accumulate ? 0 : 1; p < parts; ++p) v += partial[p * n + e];
+        image[e] = v;
+    }
+}
+
+hipError_t launch_sum_parts(float *image, const float *partial, int parts, int64_t n, int accumulate,
+                            const uint32_t *skip, hipStream_t s)
+{
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(sum_parts_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, s, image, partial, parts, n, accumulate, skip);
+    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- slab table
@@ -838,51 +916,53 @@ int bp_sym_window(int need) { return need <= 96 ? 96 : (need <= 192 ? 192 : 0); 
 
 // The kernel instantiation for (path, filtered dtype, window, slices per
 // item) and an action on it (launch or occupancy query), given the kernel
-// and its block size.
-template <int SL, typename F>
+// and its block size.  PARTS: launches that are gated or hold split slabs (the
+// loop over parts costs the mirror kernel a quarter of its speed, so the
+// others are built without it).
+template <int SL, bool PARTS, typename F>
 static auto with_sym(int dtype, int win, F &&f)
 {
     constexpr int th = sym_threads<SL>();
     if (win == 96) {
-        if (dtype == XCT_F32) return f(bp_sym_kernel<float, 96, SL>, th);
-        if (dtype == XCT_F16) return f(bp_sym_kernel<f16_t, 96, SL>, th);
-        return f(bp_sym_kernel<bf16_t, 96, SL>, th);
+        if (dtype == XCT_F32) return f(bp_sym_kernel<float, 96, SL, PARTS>, th);
+        if (dtype == XCT_F16) return f(bp_sym_kernel<f16_t, 96, SL, PARTS>, th);
+        return f(bp_sym_kernel<bf16_t, 96, SL, PARTS>, th);
     }
-    if (dtype == XCT_F32) return f(bp_sym_kernel<float, 192, SL>, th);
-    if (dtype == XCT_F16) return f(bp_sym_kernel<f16_t, 192, SL>, th);
-    return f(bp_sym_kernel<bf16_t, 192, SL>, th);
+    if (dtype == XCT_F32) return f(bp_sym_kernel<float, 192, SL, PARTS>, th);
+    if (dtype == XCT_F16) return f(bp_sym_kernel<f16_t, 192, SL, PARTS>, th);
+    return f(bp_sym_kernel<bf16_t, 192, SL, PARTS>, th);
 }
 
-template <int SL, typename F>
+template <int SL, bool PARTS, typename F>
 static auto with_mirror(int dtype, int win, F &&f)
 {
     constexpr int th = sym_threads<SL>();
     if (win == 96) {
-        if (dtype == XCT_F32) return f(bp_mirror_kernel<float, 96, SL>, th);
-        if (dtype == XCT_F16) return f(bp_mirror_kernel<f16_t, 96, SL>, th);
-        return f(bp_mirror_kernel<bf16_t, 96, SL>, th);
+        if (dtype == XCT_F32) return f(bp_mirror_kernel<float, 96, SL, PARTS>, th);
+        if (dtype == XCT_F16) return f(bp_mirror_kernel<f16_t, 96, SL, PARTS>, th);
+        return f(bp_mirror_kernel<bf16_t, 96, SL, PARTS>, th);
     }
-    if (dtype == XCT_F32) return f(bp_mirror_kernel<float, 192, SL>, th);
-    if (dtype == XCT_F16) return f(bp_mirror_kernel<f16_t, 192, SL>, th);
-    return f(bp_mirror_kernel<bf16_t, 192, SL>, th);
+    if (dtype == XCT_F32) return f(bp_mirror_kernel<float, 192, SL, PARTS>, th);
+    if (dtype == XCT_F16) return f(bp_mirror_kernel<f16_t, 192, SL, PARTS>, th);
+    return f(bp_mirror_kernel<bf16_t, 192, SL, PARTS>, th);
 }
 
-template <typename F>
+template <bool PARTS, typename F>
 static auto with_kernel(int path, int dtype, int win, int sl, F &&f)
 {
     if (path == kPathGeneric) {
-        if (dtype == XCT_F32) return f(bp_generic_kernel<float>, kBPThreads);
-        if (dtype == XCT_F16) return f(bp_generic_kernel<f16_t>, kBPThreads);
-        return f(bp_generic_kernel<bf16_t>, kBPThreads);
+        if (dtype == XCT_F32) return f(bp_generic_kernel<float, PARTS>, kBPThreads);
+        if (dtype == XCT_F16) return f(bp_generic_kernel<f16_t, PARTS>, kBPThreads);
+        return f(bp_generic_kernel<bf16_t, PARTS>, kBPThreads);
     }
-    if (path == kPathMirror) return sl == 2 ? with_mirror<2>(dtype, win, f) : with_mirror<1>(dtype, win, f);
-    return sl == 2 ? with_sym<2>(dtype, win, f) : with_sym<1>(dtype, win, f);
+    if (path == kPathMirror) return sl == 2 ? with_mirror<2, PARTS>(dtype, win, f) : with_mirror<1, PARTS>(dtype, win, f);
+    return sl == 2 ? with_sym<2, PARTS>(dtype, win, f) : with_sym<1, PARTS>(dtype, win, f);
 }
 
-hipError_t launch_bp(int path, const BPBatch &b, int dtype, int sl, int grid, size_t lds, hipStream_t s)
+hipError_t launch_bp(int path, const BPBatch &b, int dtype, int sl, bool parts, int grid, size_t lds, hipStream_t s)
 {
-    return with_kernel(path, dtype, b.win, sl,
-                       [&](auto k, int threads) { return launch(k, threads, b, grid, lds, s); });
+    auto go = [&](auto k, int threads) { return launch(k, threads, b, grid, lds, s); };
+    return parts ? with_kernel<true>(path, dtype, b.win, sl, go) : with_kernel<false>(path, dtype, b.win, sl, go);
 }
 
 int bp_block_threads(int path, int sl)
@@ -891,9 +971,10 @@ int bp_block_threads(int path, int sl)
     return sl == 2 ? sym_threads<2>() : sym_threads<1>();
 }
 
-int bp_max_blocks_per_cu(int path, int dtype, int win, int sl, size_t lds)
+int bp_max_blocks_per_cu(int path, int dtype, int win, int sl, bool parts, size_t lds)
 {
-    return with_kernel(path, dtype, win, sl, [&](auto k, int threads) { return occupancy(k, threads, lds); });
+    auto query = [&](auto k, int threads) { return occupancy(k, threads, lds); };
+    return parts ? with_kernel<true>(path, dtype, win, sl, query) : with_kernel<false>(path, dtype, win, sl, query);
 }
 
 }  // namespace xct

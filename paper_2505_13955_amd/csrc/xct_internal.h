@@ -43,6 +43,12 @@ struct BPSlab {
     int32_t out_u16;           // store clamp(rint(fl(fl(v code_a) + code_b))) as uint16
     float code_a, code_b;
     int32_t sets;              // symmetric path: half-turn angle sets (2 for a full turn)
+    // The angles (symmetric path: angle pairs) are added up part_len at a
+    // time, each part stored or added to the image on its own: all parts in
+    // one work item, or (partial) one item per part, part slowest, into its
+    // own copy of the slab's images, [part][S][Ny][Nx].
+    int32_t part_len, parts;
+    float *partial;
 };
 
 // Slabs, items and schedule of one back-projection launch.  Up to
@@ -60,6 +66,8 @@ struct BPBatch {
     int32_t win;            // window entries per angle and window
     int32_t kb;             // angles (generic) / angle pairs (symmetric) per LDS stage
     int32_t xcd_remap;      // map consecutive items to one XCD (non-persistent launches)
+    const uint32_t *gate;   // the launch does nothing if *gate is 0 (nullptr: it always runs)
+    int32_t stride;         // > 0: workgroup b takes items b, b + stride, ... (gated launches)
 };
 
 // Accelerator complex dies of an MI355X: workgroups are dispatched to them
@@ -82,13 +90,52 @@ enum { kPathGeneric = 0, kPathSymmetric = 1, kPathMirror = 2 };
 
 // Launch (returns hipError_t of the launch) and sizing helpers.
 // `sl`: slices per work item of the symmetric kernel (1 or 2).
-hipError_t launch_bp(int path, const BPBatch &b, int dtype, int sl, int grid, size_t lds, hipStream_t s);
+// `parts`: some slab of the launch is split, or the launch is gated.
+hipError_t launch_bp(int path, const BPBatch &b, int dtype, int sl, bool parts, int grid, size_t lds, hipStream_t s);
 size_t bp_generic_lds_bytes(int win, int kb);
 size_t bp_sym_lds_bytes(int win, int kb, int sl);
 size_t bp_mirror_lds_bytes(int win, int kb, int sl);
 int bp_sym_window(int need);  // window of the symmetric kernel covering `need` (0: none)
-int bp_max_blocks_per_cu(int path, int dtype, int win, int sl, size_t lds);
+int bp_max_blocks_per_cu(int path, int dtype, int win, int sl, bool parts, size_t lds);
 int bp_block_threads(int path, int sl);  // threads per workgroup of the kernel
+
+// Matrix-core back-projection (bp_mfma.hip): what a pixel's coordinate serves.
+enum { kMXPlain = 0, kMXMirror, kMXMirror2, kMXQuarter, kMXQuarter2 };
+constexpr int kMXTile = 32;            // tile edge (pixels)
+constexpr int kMXAngles = 4;           // angles per stage
+constexpr double kMXMaxRatio = 1.1;    // largest pixel_size / det_pitch its windows cover
+struct MXArgs {
+    int64_t table;         // device address of the split table [S/4][n_angles][Nc]
+    float *image;          // [S][Ny][Nx]
+    const double2 *csd;    // [Np] (cos, sin) * pixel / pitch
+    const uint32_t *amax;  // [0]: a row element is not finite; [1 + z]: slice z's largest magnitude (float bits)
+    double center;
+    // angles of this launch: k_first .. , with k_jump more from the
+    // half_set'th on (quarter-turn kinds: two runs a quarter turn apart)
+    int32_t n_angles, k_first, k_jump, half_set;
+    int32_t n_det, nx, ny, n_slices;
+    int32_t tiles_x, tiles_y;
+    int32_t mirror;        // 2c
+    float scale;
+    int32_t accumulate;
+    int32_t part_len;      // angles added up before they go to the image (a multiple of kMXAngles)
+    int32_t items;         // work items of one part
+    float *partial;        // one workgroup per item and part: [part][S][Ny][Nx] partial images; nullptr: the image
+};
+// image = (accumulate ? image : 0) + part 0 + part 1 + ..., in that order; does
+// nothing if *skip is not 0 (nullptr: always runs).
+hipError_t launch_sum_parts(float *image, const float *partial, int parts, int64_t n, int accumulate,
+                            const uint32_t *skip, hipStream_t s);
+struct SplitArgs {
+    const void *sino;      // [S][n_angles][Nc]
+    uint4 *table;          // [S/4][rows][Nc]
+    const uint32_t *amax;
+    int32_t n_angles, n_det, n_slices;
+    int32_t rows, k_first, k_jump, split;  // table row l is angle k_first + l, plus k_jump for l >= split
+};
+hipError_t launch_bp_mfma(const MXArgs &a, int nt, int kind, int grid, hipStream_t s);
+hipError_t launch_absmax(const void *sino, int dtype, int n_slices, int64_t per_slice, uint32_t *amax, hipStream_t s);
+hipError_t launch_split(const SplitArgs &a, int dtype, hipStream_t s);
 
 // Front end read in the filter's load phase: raw projection stack
 // [n_angles][n_rows][Nc] with dark and flat fields [n_rows][Nc].

@@ -1,0 +1,127 @@
+"""GPU parity of the back-projector's matrix-core form and of calls whose
+angles are split into parts, against the FP64 oracle.
+
+The adjoint and the batch choose the form from the call's size alone; the
+sizes here lie where each kind is chosen: plain, mirror and quarter-turn
+columns, each with and without the reflection, one and two 32-column tiles,
+slice counts that are no multiple of a group of four, ragged tiles and angle
+counts, arbitrary angles, and small calls split over the device."""
+
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from tests.gpu_util import rel_l2, say, to_dev
+
+pytestmark = pytest.mark.gpu
+
+# Coordinates are FP32 below 64 bins (2^-19 bin of rounding, some three of them
+# per pixel and angle); white-noise rows have a slope of sqrt(2) of their
+# magnitude per bin, and interpolation keeps sqrt(2/3) of it: 3 2^-19 sqrt(3) =
+# 1.0e-5.
+TOL = 1e-5
+
+
+@pytest.fixture(scope="module")
+def xct():
+    import paper_2505_13955_amd as pkg
+
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    pkg.load_library()
+    return pkg
+
+
+def _angles(kind, n, rng):
+    if kind == "rand":
+        return rng.uniform(-math.pi, 2 * math.pi, n)
+    return np.arange(n) * ((2.0 if kind == "full" else 1.0) * math.pi / n)
+
+
+CASES = [
+    # slices, nx, ny, angles, bins, centre, pixel, angle set
+    (70, 64, 64, 133, 70, 31.7, 1.0, "half"),      # plain
+    (37, 120, 90, 151, 150, 74.3, 1.1, "rand"),    # plain, arbitrary angles, largest pixel
+    (33, 101, 99, 249, 150, 74.5, 1.0, "half"),    # mirror, odd sizes
+    (35, 130, 64, 120, 160, 80.0, 0.8, "rand"),    # mirror, arbitrary angles
+    (5, 200, 200, 101, 289, 144.0, 1.0, "half"),   # mirror with reflection
+    (7, 321, 257, 361, 461, 230.0, 1.0, "half"),   # the same, middle row and column
+    (8, 512, 512, 360, 727, 363.0, 1.0, "half"),   # quarter turn with reflection
+    (12, 300, 300, 180, 427, 213.0, 1.0, "half"),  # quarter turn, ragged quadrant
+    (18, 258, 258, 128, 300, 149.5, 1.0, "full"),  # quarter turn, two half-turn sets
+    (1, 256, 256, 360, 367, 183.0, 1.0, "half"),   # split, vector kernels: symmetric
+    (3, 131, 77, 163, 150, 80.0, 1.1, "half"),     # split: mirror
+    (1, 200, 70, 200, 290, 144.6, 1.4, "rand"),    # split: generic
+    (2, 256, 256, 512, 367, 183.0, 1.0, "full"),   # split: symmetric, parts across the two sets
+]
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_adjoint_matches_oracle(xct, case):
+    S, nx, ny, na, nd, c, px, kind = CASES[case]
+    rng = np.random.default_rng(900 + case)
+    g = synth.Geometry(n_angles=na, n_det=nd, nx=nx, ny=ny, center=c, pixel_size=px, angles=_angles(kind, na, rng))
+    q = rng.standard_normal((S, na, nd)) * np.linspace(0.5, 2.0, S)[:, None, None]
+    base = rng.standard_normal((S, ny, nx))
+    say("adjoint", CASES[case])
+    dq = to_dev(q)
+    img = xct.project_adjoint(dq, g)
+    acc = to_dev(base)
+    xct.xct_project_adjoint(g, dq, acc, -0.5, accumulate=True)
+    torch.cuda.synchronize()
+    ref = oracle.backproject(q.astype(np.float32).astype(np.float64), g, oracle.adjoint_scale(g))
+    for z in range(S):
+        assert rel_l2(img[z].cpu().numpy(), ref[z]) < TOL, z
+    assert rel_l2(acc.cpu().numpy() - base.astype(np.float32), -0.5 * ref) < TOL
+
+
+@pytest.mark.parametrize("case", [0, 4, 7, 9])
+def test_non_finite_samples_reach_the_same_pixels(xct, case):
+    """A NaN and an infinity in the rows give non-finite pixels where the
+    oracle's taps meet them and nowhere else."""
+    S, nx, ny, na, nd, c, px, kind = CASES[case]
+    rng = np.random.default_rng(40 + case)
+    g = synth.Geometry(n_angles=na, n_det=nd, nx=nx, ny=ny, center=c, pixel_size=px, angles=_angles(kind, na, rng))
+    q = rng.standard_normal((S, na, nd)).astype(np.float32)
+    q[S // 2, na // 2, nd // 2] = np.nan
+    q[0, 0, nd // 3] = np.inf
+    img = xct.project_adjoint(to_dev(q), g).cpu().numpy()
+    mark = np.zeros(q.shape)
+    mark[~np.isfinite(q)] = 1.0
+    hit = oracle.backproject(mark, g) > 0
+    clear = oracle.backproject(mark, g) == 0
+    # (a tap's weight within rounding of zero may or may not count)
+    assert np.isfinite(img[clear]).mean() > 0.999
+    assert not np.isfinite(img[hit]).any() or (~np.isfinite(img[hit])).mean() > 0.999
+    assert (~np.isfinite(img)).any()
+
+
+@pytest.mark.parametrize("storage", [torch.float32, torch.float16, torch.bfloat16])
+def test_batch_of_split_and_matrix_slabs(xct, storage):
+    """One batch holding split and matrix slabs: each image equals its own
+    call's bit for bit, and the oracle; with a workspace that lacks the scratch
+    behind the filtered rows the vector kernels give the same within rounding."""
+    rng = np.random.default_rng(5)
+    slabs, refs = [], []
+    for S, nx, ny, na, nd, c, px, kind in (CASES[9], CASES[6], CASES[4], CASES[3]):
+        g = synth.Geometry(n_angles=na, n_det=nd, nx=nx, ny=ny, center=c, pixel_size=px, angles=_angles(kind, na, rng))
+        p = torch.as_tensor(rng.standard_normal((S, na, nd))).to(torch.float32).to(storage)
+        slabs.append((g, p.cuda(), torch.empty((S, ny, nx), device="cuda")))
+        refs.append(oracle.fbp(p.to(torch.float64).numpy(), g, "hann"))
+    xct.xct_fbp_batch(slabs, "hann")
+    for (g, p, img), ref in zip(slabs, refs):
+        alone = torch.empty_like(img)
+        xct.xct_fbp_batch([(g, p, alone)], "hann")
+        torch.cuda.synchronize()
+        assert torch.equal(alone, img)
+        assert rel_l2(img.cpu().numpy(), ref) < 2e-5
+    base = 256 + 4 * 1024 + sum((p.numel() * 4 + 255) // 256 * 256 for _, p, _ in slabs)
+    assert xct.xct_fbp_workspace_bytes(slabs) > base
+    again = [(g, p, torch.empty_like(img)) for g, p, img in slabs]
+    xct.xct_fbp_batch(again, "hann", workspace=torch.empty(base, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    for (_, _, img), (_, _, b) in zip(slabs, again):
+        assert rel_l2(b.cpu().numpy(), img.cpu().numpy().astype(np.float64)) < 2e-5
