@@ -1161,6 +1161,8 @@ int xct_backproject_u16(const xct_geometry *g, int32_t n_slices, const void *sin
                            (hipStream_t)stream);
 }
 
+constexpr int kFPPartSteps = 32;  // walk steps of a split forward projection's shortest part
+
 // P = (pixel^2 / pitch) A, the projector of the least-squares problem.
 static double projector_scale(const xct_geometry *g) { return g->pixel_size * g->pixel_size / g->det_pitch; }
 
@@ -1198,7 +1200,22 @@ static int forward_project(const xct_geometry *g, int32_t n_slices, const float 
     a.nx = g->nx;
     a.ny = g->ny;
     a.n_slices = n_slices;
-    if (sl == 1) {
+    // A call with fewer workgroups than the device holds (four per CU) takes
+    // the time of one workgroup's walk over the image (one 512^2 slice, 720
+    // angles: 180 workgroups, 450 us), so its walks are split until there are
+    // about two rounds of them, down to kFPPartSteps steps.
+    a.parts = 1;
+    const int64_t triples = (int64_t)a.n_blocks * a.bin_blocks * ((n_slices + sl - 1) / sl);
+    const int64_t slots = 4 * (int64_t)device_cus();
+    const size_t sino_bytes = sizeof(float) * (size_t)n_slices * g->n_angles * g->n_det;
+    if (triples < slots) {
+        const int64_t want = std::min<int64_t>((2 * slots + triples - 1) / triples, std::min(g->nx, g->ny) / kFPPartSteps);
+        if (want > 1 && want * sino_bytes <= (size_t)kPartBytes) a.parts = (int)want;
+    }
+    // (under capture a one-slice form stays whole, without scratch)
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (a.parts > 1 && (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)) a.parts = 1;
+    if (sl == 1 && a.parts == 1) {
         const hipError_t e = launch_forward(a, 1, s);
         return e == hipSuccess ? XCT_OK : hip_fail(e);
     }
@@ -1206,27 +1223,40 @@ static int forward_project(const xct_geometry *g, int32_t n_slices, const float 
     // its transpose, made chunk by chunk of slice groups in stream-ordered
     // memory (kQuadBytes, or one group when a group needs more).
     const int64_t plane = (int64_t)g->nx * g->ny;
-    const int64_t group_bytes = 2 * plane * (int64_t)sizeof(float4);
-    const int64_t groups = (n_slices + 3) / 4;
-    const int64_t per = std::max<int64_t>(1, std::min<int64_t>(groups, kQuadBytes / group_bytes));
+    const int64_t group_bytes = sl == 4 ? 2 * plane * (int64_t)sizeof(float4) : 0;
+    const int64_t groups = (n_slices + sl - 1) / sl;
+    const int64_t per = sl == 4 ? std::max<int64_t>(1, std::min<int64_t>(groups, kQuadBytes / group_bytes)) : groups;
+    if (per < groups) a.parts = 1;
     keep_stream_pool();
-    void *buf = nullptr;
-    hipError_t e = hipMallocAsync(&buf, (size_t)(per * group_bytes), s);
+    char *buf = nullptr;
+    const size_t part_bytes = a.parts > 1 ? align256(a.parts * sino_bytes) : 0;
+    hipError_t e = hipMallocAsync(reinterpret_cast<void **>(&buf), part_bytes + (size_t)(per * group_bytes), s);
+    if (e != hipSuccess && sl == 1) {  // no memory: the whole form needs none
+        (void)hipGetLastError();
+        a.parts = 1;
+        e = launch_forward(a, 1, s);
+        return e == hipSuccess ? XCT_OK : hip_fail(e);
+    }
     if (e != hipSuccess) return hip_fail(e);
-    float4 *quad = static_cast<float4 *>(buf), *quad_t = quad + per * plane;
-    for (int64_t g0 = 0; g0 < groups && e == hipSuccess; g0 += per) {
-        const int64_t z = 4 * g0;
-        const int ns = (int)std::min<int64_t>(n_slices - z, 4 * per);
-        e = launch_forward_quads(image + z * plane, ns, g->nx, g->ny, quad, quad_t, s);
-        if (e != hipSuccess) break;
-        FPArgs c = a;
-        c.image = image + z * plane;
-        c.sino = sino + z * (int64_t)g->n_angles * g->n_det;
-        if (base) c.base = base + z * (int64_t)g->n_angles * g->n_det;
-        c.n_slices = ns;
-        c.quad = quad;
-        c.quad_t = quad_t;
-        e = launch_forward(c, 4, s);
+    a.partial = reinterpret_cast<float *>(buf);
+    if (sl == 1) {
+        e = launch_forward(a, 1, s);
+    } else {
+        float4 *quad = reinterpret_cast<float4 *>(buf + part_bytes), *quad_t = quad + per * plane;
+        for (int64_t g0 = 0; g0 < groups && e == hipSuccess; g0 += per) {
+            const int64_t z = 4 * g0;
+            const int ns = (int)std::min<int64_t>(n_slices - z, 4 * per);
+            e = launch_forward_quads(image + z * plane, ns, g->nx, g->ny, quad, quad_t, s);
+            if (e != hipSuccess) break;
+            FPArgs c = a;
+            c.image = image + z * plane;
+            c.sino = sino + z * (int64_t)g->n_angles * g->n_det;
+            if (base) c.base = base + z * (int64_t)g->n_angles * g->n_det;
+            c.n_slices = ns;
+            c.quad = quad;
+            c.quad_t = quad_t;
+            e = launch_forward(c, 4, s);
+        }
     }
     const hipError_t f = hipFreeAsync(buf, s);
     if (e == hipSuccess) e = f;

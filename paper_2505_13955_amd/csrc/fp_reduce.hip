@@ -92,7 +92,11 @@ __global__ __launch_bounds__(kFPBins, 4) void fp_tile_kernel(FPArgs a)
     // block fastest, so the workgroups of one XCD stage overlapping pixels
     const int n_wg = (int)gridDim.x, xcd = (int)blockIdx.x & 7, jx = (int)blockIdx.x >> 3;
     const int qx = n_wg >> 3, rx = n_wg & 7;
-    const int wg = a.block_base + xcd * qx + min(xcd, rx) + jx;
+    int wg = a.block_base + xcd * qx + min(xcd, rx) + jx;
+    // A small call splits its walk: part p of a workgroup's triple takes the
+    // p'th run of whole stages and stores its sums to the part's own sinogram.
+    const int part = a.parts > 1 ? wg / a.triples : 0;
+    wg -= part * a.triples;
     const int blk = wg % a.n_blocks;
     const int tb = wg / a.n_blocks;
     const int bb = tb % a.bin_blocks;
@@ -110,6 +114,8 @@ __global__ __launch_bounds__(kFPBins, 4) void fp_tile_kernel(FPArgs a)
     const float4 *quad = SL == 4 ? (walk ? a.quad_t : a.quad) + (int64_t)(z0 >> 2) * plane : nullptr;
     const int quad_ld = walk ? a.ny : a.nx;
     const int rows = B.rows[SL == 4 ? 1 : 0], pitch = B.pitch[SL == 4 ? 1 : 0];
+    const int run = a.parts > 1 ? ((nw + a.parts - 1) / a.parts + rows - 1) / rows * rows : nw;
+    const int w_begin = part * run, w_end = min(nw, w_begin + run);
     const bool on = q < count;
     const FPAngle p = a.ang[k0 + (on ? q : 0)];
     const float invA = (float)p.invA;
@@ -151,9 +157,9 @@ __global__ __launch_bounds__(kFPBins, 4) void fp_tile_kernel(FPArgs a)
 
     // Stages in turn: the next stage's cross range is formed while the
     // current stage is added up, so a stage takes two barriers.
-    plan_range(0, 0);
+    plan_range(w_begin, 0);
     __syncthreads();
-    for (int s = 0, w0 = 0; w0 < nw; ++s, w0 += rows) {
+    for (int s = 0, w0 = w_begin; w0 < w_end; ++s, w0 += rows) {
         const int rc = min(rows, nw - w0);
         const int vlo = range[s & 1].x, width = range[s & 1].y;
         const bool stage_on = vlo + width > 0 && vlo < nv;  // the strips reach the image here
@@ -208,7 +214,7 @@ __global__ __launch_bounds__(kFPBins, 4) void fp_tile_kernel(FPArgs a)
         __syncthreads();  // the stage is in tile; every wavefront has read its range
         // wavefront 0 forms the next stage's range first, so that its
         // latency hides behind its own taps rather than delaying the barrier
-        if (w0 + rows < nw) plan_range(w0 + rows, (s + 1) & 1);
+        if (w0 + rows < w_end) plan_range(w0 + rows, (s + 1) & 1);
         if (stage_on) {
             // This thread's crossings: v*(nb + 4b, w0 + r) - vlo = rel0 + 4b/A + r dv,
             // anchored once per stage in FP64 (integer part bi0, FP32 fraction f00)
@@ -297,16 +303,30 @@ __global__ __launch_bounds__(kFPBins, 4) void fp_tile_kernel(FPArgs a)
         const int n = n0 + tid;
         if (n < a.n_det) {
             const int64_t row0 = ((int64_t)(z0 + sl) * a.n_angles + k0) * a.n_det + n;
-            float *out = a.sino + row0;
+            float *out = (a.parts > 1 ? a.partial + (int64_t)part * a.n_slices * a.n_angles * a.n_det : a.sino) + row0;
             const float *base = a.base ? a.base + row0 : nullptr;
             for (int qq = 0; qq < count; ++qq) {
                 const float v = out_lds[qq * kOutPitch + tid];
                 float *o = out + (int64_t)qq * a.n_det;
-                if (base) *o = fmaf(a.scale, v, base[(int64_t)qq * a.n_det]);
+                if (a.parts > 1) *o = v;
+                else if (base) *o = fmaf(a.scale, v, base[(int64_t)qq * a.n_det]);
                 else *o = a.accumulate ? fmaf(a.scale, v, *o) : a.scale * v;
             }
         }
     }
+}
+
+// Sinogram of a split call from its parts' sums, added in the order of the
+// parts, with the store of the whole form.
+__global__ __launch_bounds__(256) void fp_sum_kernel(FPArgs a, int64_t n)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    float v = a.partial[i];
+    for (int p = 1; p < a.parts; ++p) v += a.partial[p * n + i];
+    float *o = a.sino + i;
+    if (a.base) *o = fmaf(a.scale, v, a.base[i]);
+    else *o = a.accumulate ? fmaf(a.scale, v, *o) : a.scale * v;
 }
 
 // Four-slice copies of the image for fp_tile_kernel<4>: for slice group g
@@ -353,10 +373,11 @@ hipError_t launch_forward(const FPArgs &a, int sl, hipStream_t s)
 {
     // one workgroup per (slice group, bin block, angle block) triple, split
     // so that no launch exceeds 2^32 - 1 work-items
-    const int64_t total = (int64_t)a.n_blocks * a.bin_blocks * ((a.n_slices + sl - 1) / sl);
+    FPArgs c = a;
+    c.triples = (int32_t)((int64_t)a.n_blocks * a.bin_blocks * ((a.n_slices + sl - 1) / sl));
+    const int64_t total = (int64_t)c.triples * a.parts;
     const int64_t max_x = ((((int64_t)1 << 32) - 1) / kFPBins);
     (void)hipGetLastError();
-    FPArgs c = a;
     for (int64_t x0 = 0; x0 < total; x0 += max_x) {
         c.block_base = (int32_t)x0;
         dim3 grid((unsigned)(total - x0 < max_x ? total - x0 : max_x));
@@ -366,6 +387,11 @@ hipError_t launch_forward(const FPArgs &a, int sl, hipStream_t s)
             hipLaunchKernelGGL(fp_tile_kernel<1>, grid, dim3(kFPBins), 0, s, c);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
+    }
+    if (a.parts > 1) {
+        const int64_t n = (int64_t)a.n_slices * a.n_angles * a.n_det;
+        hipLaunchKernelGGL(fp_sum_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, c, n);
+        return hipGetLastError();
     }
     return hipSuccess;
 }

@@ -203,6 +203,10 @@ struct FPArgs {
     float scale;
     int32_t accumulate;
     int32_t n_angles, n_det, nx, ny, n_slices;
+    // parts > 1: the walk steps are split into that many runs, one workgroup
+    // each, whose sums go to partial [parts][S][Np][Nc] and are added up after
+    int32_t parts, triples;
+    float *partial;
 };
 // Host: angle table and blocks with their staging shapes (XCT_ETOOBIG when
 // some block has no one-slice shape; *four tells whether every block has a

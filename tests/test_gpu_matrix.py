@@ -125,3 +125,28 @@ def test_batch_of_split_and_matrix_slabs(xct, storage):
     torch.cuda.synchronize()
     for (_, _, img), (_, _, b) in zip(slabs, again):
         assert rel_l2(b.cpu().numpy(), img.cpu().numpy().astype(np.float64)) < 2e-5
+
+
+@pytest.mark.parametrize("case", [
+    # slices, nx, ny, angles, bins, centre, angle set
+    (1, 130, 97, 40, 190, 94.3, "half"),
+    (2, 256, 256, 90, 367, 183.0, "half"),
+    (3, 200, 64, 33, 301, 150.0, "rand"),    # four-slice form, walks of different lengths
+    (5, 97, 131, 60, 170, 84.5, "full"),
+])
+def test_split_forward_projection(xct, case):
+    """Calls too small to fill the device, whose walks over the image are split."""
+    S, nx, ny, na, nd, c, kind = case
+    rng = np.random.default_rng(70 + na)
+    g = synth.Geometry(n_angles=na, n_det=nd, nx=nx, ny=ny, center=c, angles=_angles(kind, na, rng))
+    x = rng.standard_normal((S, ny, nx))
+    y = rng.standard_normal((S, na, nd))
+    dx, dy = to_dev(x), to_dev(y)
+    say("split forward", case)
+    p = xct.forward_project(dx, g)
+    r = torch.empty_like(dy)
+    xct.xct_forward_residual(g, dx, dy, r)
+    torch.cuda.synchronize()
+    ref = oracle.forward(x.astype(np.float32).astype(np.float64), g)
+    assert rel_l2(p.cpu().numpy(), ref) < TOL
+    assert rel_l2(r.cpu().numpy(), y.astype(np.float32) - ref) < TOL
