@@ -514,6 +514,25 @@ struct BPJob {
     float *partial = nullptr;
 };
 
+#ifndef XCT_SYM_MAX_SLICES
+#define XCT_SYM_MAX_SLICES 2  // slices per work item of the symmetric kernel (1 or 2)
+#endif
+// Slices (pairs of slices) per work item of a job alone.
+int item_slices(const BPJob &j)
+{
+    if (j.path == kPathGeneric) return 1;
+    return std::min(j.path == kPathPairs ? (j.n_slices + 1) / 2 : j.n_slices, XCT_SYM_MAX_SLICES);
+}
+
+// Slices of any geometry go two at a time where the call may round otherwise
+// than xct_backproject_u16 does (which keeps the generic kernel's bits) and
+// the windows fit.
+void pair_slices(BPJob &j)
+{
+    if (j.path == kPathGeneric && !j.out_u16 && j.n_slices >= 2 && bp_sym_window(window_entries(j.g->pixel_size / j.g->det_pitch)))
+        j.path = kPathPairs;
+}
+
 // Tiles per slice as the kernel indexes them (tiles_x, tiles_y) and the work
 // items of the whole slab.
 int64_t plan_tiles(const BPJob &j, int sl, int *tx, int *ty)
@@ -522,6 +541,11 @@ int64_t plan_tiles(const BPJob &j, int sl, int *tx, int *ty)
         *tx = (j.g->nx + kTile - 1) / kTile;
         *ty = (j.g->ny + kTile - 1) / kTile;
         return (int64_t)*tx * *ty * j.n_slices;
+    }
+    if (j.path == kPathPairs) {
+        *tx = (j.g->nx + kTile - 1) / kTile;
+        *ty = (j.g->ny + kTile - 1) / kTile;
+        return (int64_t)*tx * *ty * ((j.n_slices + 2 * sl - 1) / (2 * sl));
     }
     if (j.path == kPathMirror) {  // the upper ceil(N_y/2) rows
         *tx = (j.g->nx + kTile - 1) / kTile;
@@ -538,9 +562,6 @@ int64_t plan_tiles(const BPJob &j, int sl, int *tx, int *ty)
 // workgroups per CU fit in 160 KiB).
 #ifndef XCT_SYM2_STAGE_KB
 #define XCT_SYM2_STAGE_KB 74
-#endif
-#ifndef XCT_SYM_MAX_SLICES
-#define XCT_SYM_MAX_SLICES 2  // slices per work item of the symmetric kernel (1 or 2)
 #endif
 constexpr size_t kGenericStageBytes = 32 * 1024;
 constexpr size_t kSymStageBytes = 37 * 1024;
@@ -559,7 +580,7 @@ VectorShape vector_shape(int path, int W, int spi)
     if (path == kPathSymmetric) {
         v.kb = (int)std::max<size_t>(1, budget / (4 * (size_t)v.win * spi * sizeof(float4) + 24));
         v.lds = bp_sym_lds_bytes(v.win, v.kb, spi);
-    } else if (path == kPathMirror) {
+    } else if (path == kPathMirror || path == kPathPairs) {
         v.kb = (int)std::max<size_t>(1, budget / ((size_t)v.win * spi * sizeof(float4) + sizeof(float4)));
         v.lds = bp_mirror_lds_bytes(v.win, v.kb, spi);
     } else {
@@ -572,34 +593,81 @@ VectorShape vector_shape(int path, int W, int spi)
 // Work items of a job alone on the vector kernels, with its slices per item.
 int64_t vector_items(const BPJob &j, int *spi)
 {
-    *spi = j.path != kPathGeneric && j.n_slices >= 2 ? XCT_SYM_MAX_SLICES : 1;
+    *spi = item_slices(j);
     int tx, ty;
     return plan_tiles(j, *spi, &tx, &ty);
 }
 
+// Times of the vector kernels as measured (ns per angle that a round of work
+// items takes, with every slot of the device taken and with one item per CU):
+//  * symmetric, two slices per item: two items per CU, 1180 (8192^2: 458 ms)
+//    and 770; one slice: four, 1300 and 710.
+//  * mirror (and slices in pairs), two slices (pairs): two items, 750 (8192^2,
+//    4 slices: 140 ms) and 580; one: four, 1270 and 630.
+//  * generic: four items, 580 (2048^2, 16 slices: 19.0 ms) and 485.
+struct VectorTimes { int per_cu; double full, alone; };
+
+VectorTimes vector_times(int path, int spi)
+{
+    if (path == kPathGeneric) return {4, 580, 485};
+    if (path == kPathSymmetric) return spi == 2 ? VectorTimes{2, 1180, 770} : VectorTimes{4, 1300, 710};
+    return spi == 2 ? VectorTimes{2, 750, 580} : VectorTimes{4, 1270, 630};
+}
+
+// Rounds of n items, in ns per angle (a last round fills the CUs from one
+// item each up to per_cu).
+double vector_rounds(const VectorTimes &t, int64_t n)
+{
+    const int64_t cus = device_cus(), slots = t.per_cu * cus, rest = n % slots;
+    const double last = rest == 0      ? 0
+                        : rest <= cus ? t.alone
+                                      : t.alone + (t.full - t.alone) * (double)(rest - cus) / (double)(slots - cus);
+    return (n / slots) * t.full + last;
+}
+
+size_t image_bytes(const BPJob &j) { return sizeof(float) * (size_t)j.n_slices * j.g->nx * j.g->ny; }
+
+// Adding up parts: a launch and its scratch, and the passes over the images at 4 TB/s.
+double sum_ns(const BPJob &j, int64_t parts) { return 14000.0 + (parts + 1) * (double)image_bytes(j) / 4000.0; }
+
+double bp_vector_ns(const BPJob &j)
+{
+    int spi;
+    const int64_t items = vector_items(j, &spi);
+    const VectorTimes t = vector_times(j.path, spi);
+    if (j.parts < 2) return vector_rounds(t, items) * j.g->n_angles;
+    const double per_part = (double)j.part_len * (j.path == kPathSymmetric ? 2 : 1);
+    return vector_rounds(t, items * j.parts) * per_part + sum_ns(j, j.parts);
+}
+
 // Parts of a small job's angles: a workgroup walks all angles of its tile, so
-// a call with fewer items than CUs leaves CUs idle and takes the time of one
-// walk (one 256^2 slice, 360 angles: four items, 194 us).  Its angles are
-// split so that items x parts fill the device about twice, down to two LDS
-// stages a part, and the parts' images are added up.  The split depends on
-// the job alone: in a batch with enough items the same parts are added up one
-// after the other inside each item, to the same bits.
+// a call with fewer items than the device has slots leaves some idle and takes
+// the time of one walk (one 256^2 slice, 360 angles: four items, 194 us).  Its
+// angles are split into the parts, of kPartStages LDS stages or more, whose
+// rounds and sum take least, and the parts' images are added up.  The split
+// depends on the job alone: in a batch with enough items the same parts are
+// added up one after the other inside each item, to the same bits.
 void plan_parts(BPJob &j)
 {
     int spi;
     const int64_t items = vector_items(j, &spi);
-    if (j.out_u16 || items >= device_cus()) return;
+    if (j.out_u16 || items >= vector_times(j.path, spi).per_cu * (int64_t)device_cus()) return;
     const VectorShape v = vector_shape(j.path, window_entries(j.g->pixel_size / j.g->det_pitch), spi);
     const int units = j.path == kPathSymmetric ? j.g->n_angles / 2 : j.g->n_angles;
-    const int64_t most = units / (kPartStages * v.kb);
-    const int64_t want = std::min<int64_t>(most, (2 * (int64_t)device_cus() + items - 1) / items);
-    if (want < 2) return;
-    j.part_len = (int)((units + want - 1) / want + v.kb - 1) / v.kb * v.kb;
-    j.parts = (units + j.part_len - 1) / j.part_len;
-    if (j.parts < 2) j.part_len = std::numeric_limits<int32_t>::max() / 2;
+    const int64_t most = std::min<int64_t>(units / (kPartStages * v.kb), kPartBytes / image_bytes(j));
+    BPJob t = j;
+    double least = 0.95 * bp_vector_ns(j);
+    for (int64_t want = 2; want <= most && want <= 64; ++want) {
+        t.part_len = (int)((units + want - 1) / want + v.kb - 1) / v.kb * v.kb;
+        t.parts = (units + t.part_len - 1) / t.part_len;
+        const double ns = t.parts < 2 ? least : bp_vector_ns(t);
+        if (ns < least) {
+            least = ns;
+            j.part_len = t.part_len;
+            j.parts = t.parts;
+        }
+    }
 }
-
-size_t image_bytes(const BPJob &j) { return sizeof(float) * (size_t)j.n_slices * j.g->nx * j.g->ny; }
 
 // Partial images of a split job that takes one item per part (0: too large, or not split).
 size_t part_bytes(const BPJob &j)
@@ -621,11 +689,11 @@ int launch_bp_jobs(std::vector<BPJob> jobs, int dtype, unsigned int *counters, B
     // largest cost per item first (items of one slab cost the same)
     std::stable_sort(jobs.begin(), jobs.end(),
                      [](const BPJob &a, const BPJob &b) { return a.g->n_angles > b.g->n_angles; });
-    // two slices per work item when every slab has at least two
-    int spi = path != kPathGeneric ? XCT_SYM_MAX_SLICES : 1;
+    // two slices (pairs) per work item when every slab has at least two
+    int spi = XCT_SYM_MAX_SLICES;
     bool split = gate != nullptr;
     for (const BPJob &j : jobs) {
-        if (j.n_slices < 2) spi = 1;
+        spi = std::min(spi, item_slices(j));
         split = split || j.parts > 1;
     }
     std::vector<BPSlab> desc(jobs.size());
@@ -650,7 +718,7 @@ int launch_bp_jobs(std::vector<BPJob> jobs, int dtype, unsigned int *counters, B
         sl.n_slices = j.n_slices;
         sl.tiles_x = tx;
         sl.tiles_y = ty;
-        sl.mirror = path != kPathGeneric ? (int32_t)std::nearbyint(2.0 * j.g->center) : 0;
+        sl.mirror = path == kPathSymmetric || path == kPathMirror ? (int32_t)std::nearbyint(2.0 * j.g->center) : 0;
         sl.sets = path == kPathSymmetric ? symmetric_sets(j.g) : 1;
         sl.scale = j.scale;
         sl.accumulate = j.accumulate;
@@ -766,37 +834,12 @@ int64_t mx_items(const BPJob &j, int kind, int nt, int *tiles_x, int *tiles_y)
     return tiles * ((j.n_slices + spi - 1) / spi);
 }
 
-// Which kernels a job takes is decided by their times as measured (ns per
-// angle that a round of work items over 256 CUs takes; all others follow from
-// the items' count):
-//  * matrix: one item per CU; 440 with one 32-column tile, 720 with two
+// Which kernels a job takes is decided by their times as measured: the vector
+// kernels' above; the matrix kernel's ns per angle that a round of one item per
+// CU takes are 440 with one 32-column tile, 720 with two
 //    (2048^2, 8 slices: 3.65 ms; 8192^2, 16 slices: 293 ms).
-//  * symmetric, two slices per item: two items per CU, 1180 (8192^2: 458 ms),
-//    770 while every item has a CU to itself; one slice: four items, 1300, 710
-//    up to 256.
-//  * mirror, two slices: two items, 750 (8192^2, 4 slices: 140 ms), 580; one
-//    slice: four, 1270, 630.
-//  * generic: four items, 580 (2048^2, 16 slices: 19.0 ms), 485.
 // The matrix path's own passes over the rows (magnitudes, split table) are
 // added at the 4.5 TB/s they reach, with 15 us for their launches.
-double bp_vector_ns(const BPJob &j)
-{
-    int sl;
-    const int64_t items = vector_items(j, &sl), cus = device_cus();
-    const int per_cu = j.path == kPathGeneric || sl == 1 ? 4 : 2;
-    const double full = j.path == kPathGeneric ? 580 : j.path == kPathMirror ? (sl == 2 ? 750 : 1270) : (sl == 2 ? 1180 : 1300);
-    const double alone = j.path == kPathGeneric ? 485 : j.path == kPathMirror ? (sl == 2 ? 580 : 630) : (sl == 2 ? 770 : 710);
-    // (a last round fills the CUs from one item each up to per_cu)
-    auto rounds = [&](int64_t n) {
-        const int64_t slots = per_cu * cus, rest = n % slots;
-        const double last = rest == 0 ? 0 : rest <= cus ? alone : alone + (full - alone) * (double)(rest - cus) / (double)(slots - cus);
-        return (n / slots) * full + last;
-    };
-    if (part_bytes(j) == 0) return rounds(items) * j.g->n_angles;
-    const double per_part = (double)j.part_len * (j.path == kPathSymmetric ? 2 : 1);
-    return rounds(items * j.parts) * per_part + 8000.0 + (j.parts + 1) * (double)image_bytes(j) / 4000.0;
-}
-
 // The parts of a matrix launch over n angles: two at least where one launch
 // covers all angles (its three roundings per product pair would otherwise
 // leave more error in the sums than the vector kernels' one), and enough to
@@ -824,7 +867,7 @@ double bp_matrix_ns(const BPJob &j, const MXPlan &p, int64_t items, int dtype)
     const double rows = (double)j.n_slices * j.g->n_angles * j.g->n_det;
     const double angles = p.spread ? p.part_len : j.g->n_angles;
     double ns = rounds * (p.nt == 2 ? 720.0 : 440.0) * angles + rows * (2 * dtype_size(dtype) + 4) / 4500.0 + 15000.0;
-    if (p.spread) ns += 8000.0 + (p.parts + 1) * (double)image_bytes(j) / 4000.0;
+    if (p.spread) ns += sum_ns(j, p.parts);
     return ns;
 }
 
@@ -838,7 +881,7 @@ MXPlan mx_plan(const BPJob &j, int dtype)
     const int64_t angle_bytes = (int64_t)((j.n_slices + 3) / 4) * g->n_det * 16;
     const int64_t fit = kMXTableBytes / angle_bytes;
     // the reflected kinds read rows k and N_p - k together: whole tables only
-    const bool refl = j.path != kPathGeneric && fit >= g->n_angles && reflected_set(g);
+    const bool refl = (j.path == kPathSymmetric || j.path == kPathMirror) && fit >= g->n_angles && reflected_set(g);
     double least = 0.95 * bp_vector_ns(j);
     auto consider = [&](int kind) {
         MXPlan p;
@@ -1108,6 +1151,7 @@ static int backproject_one(const xct_geometry *g, int32_t n_slices, const void *
     j.code_b = code_b;
     if (int rc = geo_tables(g, s, &j.t)) return rc;
     const double updates = (double)n_slices * g->n_angles * g->nx * g->ny;
+    if (updates >= least) pair_slices(j);
     if (least == 0.0) plan_parts(j);
     MXPlan p;
     if (updates >= least) p = mx_plan(j, sino_t);
@@ -1341,6 +1385,7 @@ static BPJob slab_job(const xct_slab &sl, xct_geometry *virt, const void *filt)
     j.scale = (float)weight;
     j.accumulate = 0;
     j.path = choose_path(j.g);
+    pair_slices(j);
     return j;
 }
 
@@ -1387,7 +1432,7 @@ size_t xct_fbp_workspace_bytes(const xct_slab *slabs, int32_t n_slabs, int32_t f
 int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_t window,
                   int32_t filtered_t, void *workspace, size_t workspace_bytes, xct_stream stream)
 {
-    static_assert(5 * kXcds * sizeof(unsigned int) <= 256, "work counters exceed their region");
+    static_assert(7 * kXcds * sizeof(unsigned int) <= 256, "work counters exceed their region");
     if (int rc = check_slabs(slabs, n_slabs, true)) return rc;
     if (!dtype_ok(sino_t) || !dtype_ok(filtered_t)) return XCT_EDTYPE;
     if (window < XCT_RAM_LAK || window > XCT_HANN) return XCT_EDTYPE;
@@ -1405,11 +1450,11 @@ int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_
     unsigned int *counters = reinterpret_cast<unsigned int *>(ws);
     BPSlab *table = reinterpret_cast<BPSlab *>(ws + 256);
     size_t off = 256 + table_bytes(n_slabs);
-    // Launch groups: the generic kernel; the mirror and the symmetric kernel,
-    // each with one slice per item (single-slice slabs) or two.  A slab takes
+    // Launch groups: the generic kernel; slices in pairs, the mirror and the
+    // symmetric kernel, each with one slice (pair) per item or two.  A slab takes
     // the kernel variant a call with that slab alone takes, so the images
     // equal separate calls bit for bit.
-    enum { kGroupGeneric = 0, kGroupMirror1, kGroupMirror2, kGroupSym1, kGroupSym2, kGroups };
+    enum { kGroupGeneric = 0, kGroupPairs1, kGroupPairs2, kGroupMirror1, kGroupMirror2, kGroupSym1, kGroupSym2, kGroups };
     std::vector<BPJob> groups[kGroups];
     // back-projection geometry of offset slabs (virtual detector); lives until
     // the launches below have read it
@@ -1436,8 +1481,9 @@ int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_
             j.partial = partial;
             partial += part_bytes(j) / sizeof(float);
         }
-        const int two = j.n_slices >= 2;
+        const int two = item_slices(j) == 2;
         const int grp = j.path == kPathGeneric  ? kGroupGeneric
+                        : j.path == kPathPairs  ? (two ? kGroupPairs2 : kGroupPairs1)
                         : j.path == kPathMirror ? (two ? kGroupMirror2 : kGroupMirror1)
                                                 : (two ? kGroupSym2 : kGroupSym1);
         groups[grp].push_back(j);

@@ -85,8 +85,8 @@ hipError_t write_slab_table(BPSlab *dst, const BPSlab *src, int n, hipStream_t s
 
 // Back-projection kernels: any geometry; quarter-turn + mirror symmetric
 // (square slices, angle sets closed under quarter turns, 2c integral); mirror
-// only (any slice and angle set, 2c integral).
-enum { kPathGeneric = 0, kPathSymmetric = 1, kPathMirror = 2 };
+// only (any slice and angle set, 2c integral); any geometry, slices in pairs.
+enum { kPathGeneric = 0, kPathSymmetric = 1, kPathMirror = 2, kPathPairs = 3 };
 
 // Launch (returns hipError_t of the launch) and sizing helpers.
 // `sl`: slices per work item of the symmetric kernel (1 or 2).

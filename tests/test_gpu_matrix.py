@@ -150,3 +150,29 @@ def test_split_forward_projection(xct, case):
     ref = oracle.forward(x.astype(np.float32).astype(np.float64), g)
     assert rel_l2(p.cpu().numpy(), ref) < TOL
     assert rel_l2(r.cpu().numpy(), y.astype(np.float32) - ref) < TOL
+
+
+# The vector kernels' gate (coordinates below 96 or 192 bins)
+TOL_VECTOR = 2e-5
+
+
+@pytest.mark.parametrize("case", [
+    # slices, nx, ny, angles, bins, centre, pixel, angle set
+    (2, 150, 100, 40, 220, 109.3, 1.0, "rand"),    # one pair
+    (3, 200, 130, 200, 330, 164.7, 1.2, "half"),   # two pairs, the second half empty, split
+    (5, 100, 300, 64, 430, 214.2, 1.5, "half"),    # three pairs, wide windows
+    (4, 96, 96, 48, 200, 99.4, 2.0, "rand"),       # the widest windows that fit
+    (3, 60, 44, 21, 260, 129.3, 3.0, "half"),      # too wide for pairs: generic
+])
+def test_slices_in_pairs(xct, case):
+    """Any geometry (axis off the half bins), two slices at a time."""
+    S, nx, ny, na, nd, c, px, kind = case
+    rng = np.random.default_rng(300 + na)
+    g = synth.Geometry(n_angles=na, n_det=nd, nx=nx, ny=ny, center=c, pixel_size=px, angles=_angles(kind, na, rng))
+    q = rng.standard_normal((S, na, nd)) * np.linspace(0.5, 2.0, S)[:, None, None]
+    say("pairs", case)
+    img = xct.project_adjoint(to_dev(q), g)
+    torch.cuda.synchronize()
+    ref = oracle.backproject(q.astype(np.float32).astype(np.float64), g, oracle.adjoint_scale(g))
+    for z in range(S):
+        assert rel_l2(img[z].cpu().numpy(), ref[z]) < TOL_VECTOR, z
