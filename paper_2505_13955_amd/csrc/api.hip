@@ -488,9 +488,10 @@ int symmetric_sets(const xct_geometry *g)
 // it applies; otherwise the mirror kernel when 2c is integral (detector bin
 // 2c - n exists for every bin n) and its windows fit; otherwise the generic
 // kernel.
-int choose_path(const xct_geometry *g)
+int choose_path(const xct_geometry *g, int *sets)
 {
-    if (symmetric_sets(g)) return kPathSymmetric;
+    *sets = symmetric_sets(g);
+    if (*sets) return kPathSymmetric;
     const double m = 2.0 * g->center;
     if (std::fabs(m - std::nearbyint(m)) <= 1e-9 && bp_sym_window(window_entries(g->pixel_size / g->det_pitch)))
         return kPathMirror;
@@ -506,6 +507,7 @@ struct BPJob {
     float scale;
     int32_t accumulate;
     int path;
+    int sets = 0;           // half-turn sets of the symmetric path
     int32_t out_u16 = 0;
     float code_a = 0.0f, code_b = 0.0f;
     // Vector kernels: the angles (pairs) that are added up at a time, and the
@@ -566,7 +568,7 @@ int64_t plan_tiles(const BPJob &j, int sl, int *tx, int *ty)
 constexpr size_t kGenericStageBytes = 32 * 1024;
 constexpr size_t kSymStageBytes = 37 * 1024;
 constexpr size_t kSym2StageBytes = XCT_SYM2_STAGE_KB * 1024;
-constexpr int kPartStages = 2;  // LDS stages of the shortest part of a split job
+constexpr int kPartStages = 1;  // LDS stages of the shortest part of a split job
 
 // Window, angles (pairs) per stage and LDS bytes of a vector kernel whose
 // widest window needs W entries, for `spi` slices per work item.
@@ -657,7 +659,7 @@ void plan_parts(BPJob &j)
     const int64_t most = std::min<int64_t>(units / (kPartStages * v.kb), kPartBytes / image_bytes(j));
     BPJob t = j;
     double least = 0.95 * bp_vector_ns(j);
-    for (int64_t want = 2; want <= most && want <= 64; ++want) {
+    for (int64_t want = 2; want <= most && want <= 64; want += 1 + want / 8) {
         t.part_len = (int)((units + want - 1) / want + v.kb - 1) / v.kb * v.kb;
         t.parts = (units + t.part_len - 1) / t.part_len;
         const double ns = t.parts < 2 ? least : bp_vector_ns(t);
@@ -719,7 +721,7 @@ int launch_bp_jobs(std::vector<BPJob> jobs, int dtype, unsigned int *counters, B
         sl.tiles_x = tx;
         sl.tiles_y = ty;
         sl.mirror = path == kPathSymmetric || path == kPathMirror ? (int32_t)std::nearbyint(2.0 * j.g->center) : 0;
-        sl.sets = path == kPathSymmetric ? symmetric_sets(j.g) : 1;
+        sl.sets = path == kPathSymmetric ? j.sets : 1;
         sl.scale = j.scale;
         sl.accumulate = j.accumulate;
         sl.part_len = j.part_len;
@@ -793,7 +795,8 @@ struct MXPlan {
     int kind = kMXPlain, nt = 0;
     int angles = 0;    // per launch (of one quarter turn for kMXQuarter)
     int part_len = 0;  // angles added up at a time (see MXArgs)
-    int parts = 1;     // of a launch
+    int per_launch = 0;   // angles of a launch
+    int parts = 1;        // of a launch
     bool spread = false;  // one workgroup per item and part
 };
 
@@ -840,35 +843,42 @@ int64_t mx_items(const BPJob &j, int kind, int nt, int *tiles_x, int *tiles_y)
 //    (2048^2, 8 slices: 3.65 ms; 8192^2, 16 slices: 293 ms).
 // The matrix path's own passes over the rows (magnitudes, split table) are
 // added at the 4.5 TB/s they reach, with 15 us for their launches.
-// The parts of a matrix launch over n angles: two at least where one launch
-// covers all angles (its three roundings per product pair would otherwise
-// leave more error in the sums than the vector kernels' one), and enough to
-// fill the device where the items are fewer than the CUs.
-void mx_parts(const BPJob &j, MXPlan &p, int64_t items, int n, bool whole)
-{
-    int64_t parts = whole ? 2 : 1;
-    const int64_t cus = device_cus();
-    p.spread = false;
-    if (items < cus) {
-        const int64_t want = std::min<int64_t>((3 * cus / 2 + items - 1) / items, n / 24);
-        if (want > 1 && std::max(want, parts) * (int64_t)image_bytes(j) <= kPartBytes) {
-            parts = std::max(want, parts);
-            p.spread = true;
-        }
-    }
-    p.part_len = (int)((n + parts - 1) / parts + kMXAngles - 1) & ~(kMXAngles - 1);
-    p.parts = (n + p.part_len - 1) / p.part_len;
-    if (p.parts < 2) p.spread = false;
-}
-
 double bp_matrix_ns(const BPJob &j, const MXPlan &p, int64_t items, int dtype)
 {
     const int64_t cus = device_cus(), rounds = ((p.spread ? p.parts : 1) * items + cus - 1) / cus;
     const double rows = (double)j.n_slices * j.g->n_angles * j.g->n_det;
-    const double angles = p.spread ? p.part_len : j.g->n_angles;
+    const double angles = p.spread ? (double)p.part_len / p.per_launch * j.g->n_angles : j.g->n_angles;
     double ns = rounds * (p.nt == 2 ? 720.0 : 440.0) * angles + rows * (2 * dtype_size(dtype) + 4) / 4500.0 + 15000.0;
     if (p.spread) ns += sum_ns(j, p.parts);
     return ns;
+}
+
+// The parts of a matrix launch: two at least where one launch covers all
+// angles (its three roundings per product pair would otherwise leave more
+// error in the sums than the vector kernels' one).  They are work items of
+// their own where that fills the last round of items better by more than
+// adding them up costs.
+void mx_parts(const BPJob &j, MXPlan &p, int64_t items, int dtype)
+{
+    const int n = p.per_launch, whole = n == j.g->n_angles ? 2 : 1;
+    const int64_t most = std::min<int64_t>(std::min<int64_t>(64, n / 16), kPartBytes / (int64_t)image_bytes(j));
+    auto split = [&](int64_t parts, bool spread) {
+        MXPlan q = p;
+        q.part_len = (int)((n + parts - 1) / parts + kMXAngles - 1) & ~(kMXAngles - 1);
+        q.parts = (n + q.part_len - 1) / q.part_len;
+        q.spread = spread && q.parts > 1;
+        return q;
+    };
+    p = split(whole, false);
+    double least = bp_matrix_ns(j, p, items, dtype);
+    for (int64_t parts = 2; parts <= most; parts += 1 + parts / 8) {
+        const MXPlan q = split(parts, true);
+        const double ns = bp_matrix_ns(j, q, items, dtype);
+        if (ns < least) {
+            least = ns;
+            p = q;
+        }
+    }
 }
 
 MXPlan mx_plan(const BPJob &j, int dtype)
@@ -878,6 +888,8 @@ MXPlan mx_plan(const BPJob &j, int dtype)
     // (uint16 images keep the vector kernels' rounding; windows cover
     // kMXMaxRatio; slice groups are a grid dimension)
     if (j.out_u16 || g->pixel_size / g->det_pitch > kMXMaxRatio || j.n_slices > 4 * 65535) return best;
+    // (below some 50 us of the vector kernels the extra launches cost more than is saved)
+    if ((double)j.n_slices * g->n_angles * g->nx * g->ny < 3e8) return best;
     const int64_t angle_bytes = (int64_t)((j.n_slices + 3) / 4) * g->n_det * 16;
     const int64_t fit = kMXTableBytes / angle_bytes;
     // the reflected kinds read rows k and N_p - k together: whole tables only
@@ -886,18 +898,18 @@ MXPlan mx_plan(const BPJob &j, int dtype)
     auto consider = [&](int kind) {
         MXPlan p;
         p.kind = kind;
-        const int run = kind == kMXQuarter ? g->n_angles / symmetric_sets(g) / 2 : g->n_angles;
+        const int run = kind == kMXQuarter ? g->n_angles / j.sets / 2 : g->n_angles;
         const int64_t cap = (kind == kMXQuarter ? fit / 2 : fit) & ~(int64_t)(kMXAngles - 1);
         if (fit < g->n_angles && cap <= 0) return;
         // (equal ranges)
         const int64_t ranges = fit >= g->n_angles ? 1 : (run + cap - 1) / cap;
         p.angles = ranges == 1 ? run : (int)((run + ranges - 1) / ranges + kMXAngles - 1) & ~(kMXAngles - 1);
-        const int per_launch = kind == kMXQuarter ? 2 * p.angles : p.angles;
+        p.per_launch = kind == kMXQuarter ? 2 * p.angles : p.angles;
         for (p.nt = 1; p.nt <= 2; ++p.nt) {
             int tx, ty;
             const int64_t items = mx_items(j, kind, p.nt, &tx, &ty);
             if (items >= (int64_t)1 << 22) continue;  // (grid of workgroups of 1024 below 2^32)
-            mx_parts(j, p, items, per_launch, per_launch == g->n_angles);
+            mx_parts(j, p, items, dtype);
             const double ns = bp_matrix_ns(j, p, items, dtype);
             if (ns < least) {
                 least = ns;
@@ -946,7 +958,7 @@ int launch_bp_matrix(const BPJob &j, const MXPlan &p, int dtype, void *scratch, 
     float *partial = reinterpret_cast<float *>(static_cast<char *>(scratch) + mx_scratch_bytes(j, p) - align256(p.parts * image_bytes(j)));
     a.partial = p.spread ? partial : nullptr;
     const int64_t items = mx_items(j, p.kind, p.nt, &a.tiles_x, &a.tiles_y);
-    const int sets = p.kind == kMXQuarter ? symmetric_sets(g) : 1;
+    const int sets = p.kind == kMXQuarter ? j.sets : 1;
     const int h = g->n_angles / sets / 2;                       // quarter turn
     const int run = p.kind == kMXQuarter ? h : g->n_angles;     // angles that one set's launches cover
     SplitArgs t{};
@@ -1145,7 +1157,7 @@ static int backproject_one(const xct_geometry *g, int32_t n_slices, const void *
     j.image = image;
     j.scale = scale;
     j.accumulate = accumulate ? 1 : 0;
-    j.path = choose_path(g);
+    j.path = choose_path(g, &j.sets);
     j.out_u16 = out_u16;
     j.code_a = code_a;
     j.code_b = code_b;
@@ -1384,7 +1396,7 @@ static BPJob slab_job(const xct_slab &sl, xct_geometry *virt, const void *filt)
     j.image = sl.image;
     j.scale = (float)weight;
     j.accumulate = 0;
-    j.path = choose_path(j.g);
+    j.path = choose_path(j.g, &j.sets);
     pair_slices(j);
     return j;
 }
@@ -1488,10 +1500,21 @@ int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_
                                                 : (two ? kGroupSym2 : kGroupSym1);
         groups[grp].push_back(j);
     }
-    bool any = false;
-    for (const auto &grp : groups) any = any || !grp.empty();
-    if (!any) return XCT_OK;
-    hipError_t e = launch_fill_u32(counters, kGroups * kXcds, 0u, s);
+    // A group whose items all fit on the device at once is launched with one
+    // workgroup per item: no counters, and no workgroup that asks every XCD's
+    // counter in turn before it ends (some 10 us of a call with one item each).
+    bool persistent[kGroups], any = false;
+    for (int grp = 0; grp < kGroups; ++grp) {
+        int64_t items = 0;
+        int spi = 1;
+        for (const BPJob &j : groups[grp]) {
+            const int64_t n = vector_items(j, &spi);
+            items += j.partial ? n * j.parts : n;
+        }
+        persistent[grp] = !groups[grp].empty() && items > vector_times(groups[grp][0].path, spi).per_cu * (int64_t)device_cus();
+        any = any || persistent[grp];
+    }
+    hipError_t e = any ? launch_fill_u32(counters, kGroups * kXcds, 0u, s) : hipSuccess;
     if (e != hipSuccess) return hip_fail(e);
     // each group reads its descriptors from its own part of the table
     BPSlab *group_table[kGroups];
@@ -1501,7 +1524,7 @@ int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_
         first += groups[grp].size();
     }
     for (int grp = kGroups - 1; grp >= 0; --grp)
-        if (int rc = launch_bp_jobs(groups[grp], filtered_t, counters + grp * kXcds, group_table[grp], s))
+        if (int rc = launch_bp_jobs(groups[grp], filtered_t, persistent[grp] ? counters + grp * kXcds : nullptr, group_table[grp], s))
             return rc;
     for (const auto &grp : groups)
         for (const BPJob &j : grp) {

@@ -845,35 +845,46 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_mirror_
 
 // ---------------------------------------------------------------- parts
 
-// Four voxels a thread; the parts' copies are read in turn.
-__global__ __launch_bounds__(256) void sum_parts_kernel(float *image, const float *partial, int parts, int64_t n, int accumulate,
+// Sum of the parts of one element (or four), added in order; the reads of
+// eight parts are in flight together.
+template <typename V>
+__device__ __forceinline__ V sum_parts(const V *first, int64_t stride, int parts, V v)
+{
+    int p = 0;
+    for (; p + 8 <= parts; p += 8) {
+        V w[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) w[i] = first[(p + i) * stride];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v += w[i];
+    }
+    for (; p < parts; ++p) v += first[p * stride];
+    return v;
+}
+
+// One element a thread, or four where all copies are 16-byte aligned.
+template <typename V>
+__global__ __launch_bounds__(256) void sum_parts_kernel(V *image, const V *partial, int parts, int64_t n, int accumulate,
                                                         const uint32_t *skip)
 {
     if (skip && *skip != 0) return;
-    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
-    const bool vec = (n & 3) == 0 && ((reinterpret_cast<uintptr_t>(image) | reinterpret_cast<uintptr_t>(partial)) & 15) == 0;
-    if (vec) {
-        if (i >= n) return;
-        float4 v = *reinterpret_cast<const float4 *>(accumulate ? image + i : partial + i);
-        for (int p = accumulate ? 0 : 1; p < parts; ++p) {
-            const float4 w = *reinterpret_cast<const float4 *>(partial + p * n + i);
-            v = make_float4(v.x + w.x, v.y + w.y, v.z + w.z, v.w + w.w);
-        }
-        *reinterpret_cast<float4 *>(image + i) = v;
-        return;
-    }
-    for (int64_t e = i; e < i + 4 && e < n; ++e) {
-        float v = accumulate ? image[e] : partial[e];
-        for (int p = accumulate ? 0 : 1; p < parts; ++p) v += partial[p * n + e];
-        image[e] = v;
-    }
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    image[i] = accumulate ? sum_parts(partial + i, n, parts, image[i]) : sum_parts(partial + n + i, n, parts - 1, partial[i]);
 }
 
 hipError_t launch_sum_parts(float *image, const float *partial, int parts, int64_t n, int accumulate,
                             const uint32_t *skip, hipStream_t s)
 {
+    typedef float v4 __attribute__((ext_vector_type(4)));
     (void)hipGetLastError();
-    hipLaunchKernelGGL(sum_parts_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, s, image, partial, parts, n, accumulate, skip);
+    // (small images keep one element a thread: more wavefronts share the latency)
+    if (n >= (1 << 20) && (n & 3) == 0 && ((reinterpret_cast<uintptr_t>(image) | reinterpret_cast<uintptr_t>(partial)) & 15) == 0)
+        hipLaunchKernelGGL(sum_parts_kernel<v4>, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, s, (v4 *)image,
+                           (const v4 *)partial, parts, n / 4, accumulate, skip);
+    else
+        hipLaunchKernelGGL(sum_parts_kernel<float>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, image, partial, parts, n,
+                           accumulate, skip);
     return hipGetLastError();
 }
 
