@@ -190,7 +190,7 @@ int xct_backproject(const xct_geometry *g, int32_t n_slices, const void *sino, i
 /* Back-projection with the volume-storage epilogue of the reconstruction
  * pipeline (Section V-A c, stage 4: slices normalised by a CT-number range and
  * quantised to 16-bit unsigned integers).  Each voxel's attenuation
- *   mu = scale * (A^T sino)      (FP32, as xct_backproject computes it)
+ *   mu = scale * (A^T sino)      (FP32, by the vector kernels at any size)
  * becomes the CT number HU = 1000 (mu - mu_water) / mu_water, and the range
  * [hu_min, hu_max] maps linearly onto the codes [0, 65535]:
  *   code = clamp(rint(fl(fl(mu * a) + b)), 0, 65535)
@@ -221,7 +221,12 @@ int xct_backproject_u16(const xct_geometry *g, int32_t n_slices, const void *sin
  * with the four slices' values side by side (and a transposed copy), made on
  * the stream in stream-ordered device memory: 32 N_x N_y bytes per group of
  * four slices, at most 1 GiB per chunk of groups (one group when a group
- * needs more), freed on the stream before the call returns.
+ * needs more), freed on the stream before the call returns.  Square slices of
+ * 512^2 and more under a uniform half turn (N_p even), unless a multiple of
+ * four, may instead be projected each from its own four turned copies, 32
+ * N_x N_y bytes per slice within the same 1 GiB; small calls keep at most
+ * 256 MiB of partial sums.  Under stream capture, or when such scratch cannot
+ * be allocated, neither is used.
  * Deterministic (gather form, no atomics).  Errors: XCT_EINVAL for
  * non-finite alpha, XCT_ETOOBIG beyond 65535 slices or 2^31 workgroups
  * (one per group of four slices, 256 bins and up to 16 angles), XCT_EHIP

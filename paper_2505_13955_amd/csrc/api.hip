@@ -1217,26 +1217,76 @@ int xct_backproject_u16(const xct_geometry *g, int32_t n_slices, const void *sin
                            (hipStream_t)stream);
 }
 
-constexpr int kFPPartSteps = 32;  // walk steps of a split forward projection's shortest part
+// Parts of a forward projection of `triples` workgroups walking `side` steps
+// each, `bytes` of sinogram.  Fewer workgroups than the device holds (four per
+// CU) take the time of one workgroup's walk (one 512^2 slice, 720 angles: 180
+// workgroups, 450 us), so walks are split until there are about two rounds of
+// them, down to 32 steps; then halved to 16 while one round holds them all, and
+// to 8 (four slices: shorter than one slice's stages) while each has a CU's LDS
+// to itself.  Three 64^2 slices, 90 angles: 58 us with 32 steps, 41 with 16, 37
+// with 8; five 256^2 slices, 360 angles: 87 us in eight parts of 32 steps (768
+// workgroups), 93 in ten, 95 in sixteen.
+static int fp_parts(int64_t triples, int side, int sl, size_t bytes)
+{
+    const int64_t cus = device_cus(), slots = 4 * cus;
+    if (triples >= slots) return 1;
+    int64_t p = std::max<int64_t>(1, std::min<int64_t>((2 * slots + triples - 1) / triples, side / 32));
+    while (side / (2 * p) >= 16 && triples * 2 * p <= slots) p *= 2;
+    while (sl == 4 && side / (2 * p) >= 8 && triples * 2 * p <= cus) p *= 2;
+    return p * bytes <= (size_t)kPartBytes ? (int)p : 1;
+}
+
+// Angle k is k pi / N_p, N_p even.
+static bool uniform_half_turn(const xct_geometry *g)
+{
+    if (g->n_angles & 1) return false;
+    for (int k = 0; k < g->n_angles; ++k)
+        if (std::fabs(g->angles[k] - k * (M_PI / g->n_angles)) > 1e-9) return false;
+    return true;
+}
 
 // P = (pixel^2 / pitch) A, the projector of the least-squares problem.
 static double projector_scale(const xct_geometry *g) { return g->pixel_size * g->pixel_size / g->det_pitch; }
 
 }  // extern "C"
 
-// sino = (base ? base : accumulate ? sino : 0) + alpha P image.
-static int forward_project(const xct_geometry *g, int32_t n_slices, const float *image, const float *base,
-                           float *sino, float alpha, int32_t accumulate, xct_stream stream)
+// Square slices under a uniform half turn: the projections of one slice at
+// angles k, k + H, N - k and H - k (H = N_p / 2) are those of the slice, and of
+// the slice turned, reflected and transposed, at angle k, so the first quarter
+// of the angles of four copies gives all rows, each weight shared by four
+// values as in a group of four slices.  That saves three quarters of one or two
+// slices' walks, and of more slices the walks of the last group's absent ones;
+// it costs the copies, 64 bytes of traffic per pixel, some 50 angles' worth of
+// three quarters of a walk.  1024^2, one slice: 16 angles 114 us against 122
+// without, 64 angles 148 against 274, 1440 angles 320 against 634; three
+// slices: 16 angles 212 against 204, 1440 angles 858 against 1057; seven
+// slices: 64 angles 831 against 823, 1440 angles 1815 against 2800.  Below
+// 512^2 a call is as long as its launches: one 256^2 slice, 360 angles, 46 us
+// against 43.
+static bool fp_turns(const xct_geometry *g, int n_slices)
 {
-    if (int rc = check_geometry(g, true)) return rc;
-    if (int rc = check_slices(g, n_slices)) return rc;
-    if (!image || !sino) return XCT_EINVAL;
-    if (!std::isfinite(alpha)) return XCT_EINVAL;
-    if (n_slices > 65535) return XCT_ETOOBIG;
-    hipStream_t s = (hipStream_t)stream;
+    if (n_slices % 4 == 0 || g->nx != g->ny || g->nx < 512) return false;
+    const int64_t saved = n_slices <= 2 ? 3 * n_slices : 4 - n_slices % 4;
+    return saved * g->n_angles >= (int64_t)144 * n_slices && uniform_half_turn(g);
+}
+
+// sino = (base ? base : accumulate ? sino : 0) + alpha P image; `scratch`:
+// with turned copies and split walks where they are faster.
+static int forward_form(const xct_geometry *g, int32_t n_slices, const float *image, const float *base,
+                        float *sino, float alpha, int32_t accumulate, bool scratch, hipStream_t s)
+{
     EntryRef t;
-    if (int rc = fp_tables(g, s, &t)) return rc;
+    bool turned = scratch && fp_turns(g, n_slices);
+    if (turned) {
+        xct_geometry quarter = *g;
+        quarter.n_angles = g->n_angles / 4 + 1;
+        if (int rc = fp_tables(&quarter, s, &t)) return rc;
+        turned = t->fp_four;
+    }
+    if (!turned)
+        if (int rc = fp_tables(g, s, &t)) return rc;
     FPArgs a{};
+    a.turned = turned;
     a.image = image;
     a.sino = sino;
     a.base = base;
@@ -1245,10 +1295,13 @@ static int forward_project(const xct_geometry *g, int32_t n_slices, const float 
     a.n_blocks = t->n_blocks;
     a.bin_blocks = (g->n_det + kFPBins - 1) / kFPBins;
     // four slices per workgroup share coordinates and weights; a call with
-    // one or two slices keeps one per workgroup
-    const int sl = (n_slices >= 3 && t->fp_four) ? 4 : 1;
+    // one or two slices, without turned copies, keeps one per workgroup
+    const int sl = turned || (n_slices >= 3 && t->fp_four) ? 4 : 1;
+    const int64_t groups = turned ? n_slices : (n_slices + sl - 1) / sl;
     // one workgroup per (slice group, bin block, angle block), indexed in 32 bits
-    if ((int64_t)a.n_blocks * a.bin_blocks * ((n_slices + sl - 1) / sl) >= ((int64_t)1 << 31)) return XCT_ETOOBIG;
+    const int64_t triples = (int64_t)a.n_blocks * a.bin_blocks * groups;
+    if (triples >= ((int64_t)1 << 31))
+        return turned ? forward_form(g, n_slices, image, base, sino, alpha, accumulate, false, s) : XCT_ETOOBIG;
     a.scale = (float)((double)alpha * projector_scale(g));
     a.accumulate = accumulate ? 1 : 0;
     a.n_angles = g->n_angles;
@@ -1256,21 +1309,8 @@ static int forward_project(const xct_geometry *g, int32_t n_slices, const float 
     a.nx = g->nx;
     a.ny = g->ny;
     a.n_slices = n_slices;
-    // A call with fewer workgroups than the device holds (four per CU) takes
-    // the time of one workgroup's walk over the image (one 512^2 slice, 720
-    // angles: 180 workgroups, 450 us), so its walks are split until there are
-    // about two rounds of them, down to kFPPartSteps steps.
-    a.parts = 1;
-    const int64_t triples = (int64_t)a.n_blocks * a.bin_blocks * ((n_slices + sl - 1) / sl);
-    const int64_t slots = 4 * (int64_t)device_cus();
     const size_t sino_bytes = sizeof(float) * (size_t)n_slices * g->n_angles * g->n_det;
-    if (triples < slots) {
-        const int64_t want = std::min<int64_t>((2 * slots + triples - 1) / triples, std::min(g->nx, g->ny) / kFPPartSteps);
-        if (want > 1 && want * sino_bytes <= (size_t)kPartBytes) a.parts = (int)want;
-    }
-    // (under capture a one-slice form stays whole, without scratch)
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (a.parts > 1 && (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)) a.parts = 1;
+    a.parts = scratch ? fp_parts(triples, std::min(g->nx, g->ny), sl, sino_bytes) : 1;
     if (sl == 1 && a.parts == 1) {
         const hipError_t e = launch_forward(a, 1, s);
         return e == hipSuccess ? XCT_OK : hip_fail(e);
@@ -1280,18 +1320,15 @@ static int forward_project(const xct_geometry *g, int32_t n_slices, const float 
     // memory (kQuadBytes, or one group when a group needs more).
     const int64_t plane = (int64_t)g->nx * g->ny;
     const int64_t group_bytes = sl == 4 ? 2 * plane * (int64_t)sizeof(float4) : 0;
-    const int64_t groups = (n_slices + sl - 1) / sl;
     const int64_t per = sl == 4 ? std::max<int64_t>(1, std::min<int64_t>(groups, kQuadBytes / group_bytes)) : groups;
     if (per < groups) a.parts = 1;
     keep_stream_pool();
     char *buf = nullptr;
     const size_t part_bytes = a.parts > 1 ? align256(a.parts * sino_bytes) : 0;
     hipError_t e = hipMallocAsync(reinterpret_cast<void **>(&buf), part_bytes + (size_t)(per * group_bytes), s);
-    if (e != hipSuccess && sl == 1) {  // no memory: the whole form needs none
+    if (e != hipSuccess && (turned || a.parts > 1)) {  // no memory for these: the form that needs the least
         (void)hipGetLastError();
-        a.parts = 1;
-        e = launch_forward(a, 1, s);
-        return e == hipSuccess ? XCT_OK : hip_fail(e);
+        return forward_form(g, n_slices, image, base, sino, alpha, accumulate, false, s);
     }
     if (e != hipSuccess) return hip_fail(e);
     a.partial = reinterpret_cast<float *>(buf);
@@ -1300,9 +1337,10 @@ static int forward_project(const xct_geometry *g, int32_t n_slices, const float 
     } else {
         float4 *quad = reinterpret_cast<float4 *>(buf + part_bytes), *quad_t = quad + per * plane;
         for (int64_t g0 = 0; g0 < groups && e == hipSuccess; g0 += per) {
-            const int64_t z = 4 * g0;
-            const int ns = (int)std::min<int64_t>(n_slices - z, 4 * per);
-            e = launch_forward_quads(image + z * plane, ns, g->nx, g->ny, quad, quad_t, s);
+            const int64_t z = turned ? g0 : 4 * g0;
+            const int ns = (int)std::min<int64_t>(n_slices - z, turned ? per : 4 * per);
+            e = turned ? launch_forward_turned(image + z * plane, ns, g->nx, quad, quad_t, s)
+                       : launch_forward_quads(image + z * plane, ns, g->nx, g->ny, quad, quad_t, s);
             if (e != hipSuccess) break;
             FPArgs c = a;
             c.image = image + z * plane;
@@ -1317,6 +1355,22 @@ static int forward_project(const xct_geometry *g, int32_t n_slices, const float 
     const hipError_t f = hipFreeAsync(buf, s);
     if (e == hipSuccess) e = f;
     return e == hipSuccess ? XCT_OK : hip_fail(e);
+}
+
+static int forward_project(const xct_geometry *g, int32_t n_slices, const float *image, const float *base,
+                           float *sino, float alpha, int32_t accumulate, xct_stream stream)
+{
+    if (int rc = check_geometry(g, true)) return rc;
+    if (int rc = check_slices(g, n_slices)) return rc;
+    if (!image || !sino) return XCT_EINVAL;
+    if (!std::isfinite(alpha)) return XCT_EINVAL;
+    if (n_slices > 65535) return XCT_ETOOBIG;
+    // under capture one or two slices take no scratch
+    hipStream_t s = (hipStream_t)stream;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    const bool scratch = hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+    if (!scratch) (void)hipGetLastError();
+    return forward_form(g, n_slices, image, base, sino, alpha, accumulate, scratch, s);
 }
 
 extern "C" {

@@ -294,7 +294,7 @@ __global__ __launch_bounds__(kFPBins, 4) void fp_tile_kernel(FPArgs a)
     float *out_lds = reinterpret_cast<float *>(tile);
 #pragma unroll
     for (int sl = 0; sl < SL; ++sl) {
-        if (sl >= nsl) break;
+        if (sl >= nsl && !(SL == 4 && a.turned)) break;
         __syncthreads();
 #pragma unroll
         for (int b = 0; b < kBinsPerThread; ++b)
@@ -302,14 +302,29 @@ __global__ __launch_bounds__(kFPBins, 4) void fp_tile_kernel(FPArgs a)
         __syncthreads();
         const int n = n0 + tid;
         if (n < a.n_det) {
-            const int64_t row0 = ((int64_t)(z0 + sl) * a.n_angles + k0) * a.n_det + n;
+            // rows of this slice in the order of the block's angles
+            int64_t row0 = (int64_t)(z0 + sl) * a.n_angles + k0, step = 1;
+            int first = 0, end = count;
+            if (SL == 4 && a.turned) {
+                // turned copy sl of slice z0 / 4: row k, k + H, N - k or H - k of
+                // the scan; angle 0 and the quarter's last give some rows twice
+                const int N = a.n_angles, H = N >> 1;
+                step = sl < 2 ? 1 : -1;
+                row0 = (int64_t)(z0 >> 2) * N + (sl == 0 ? k0 : sl == 1 ? k0 + H : sl == 2 ? N - k0 : H - k0);
+                if (sl >= 2) {
+                    if (k0 == 0) first = 1;
+                    if (2 * (k0 + count - 1) == H) --end;
+                }
+            }
+            row0 = row0 * a.n_det + n;
+            step *= a.n_det;
             float *out = (a.parts > 1 ? a.partial + (int64_t)part * a.n_slices * a.n_angles * a.n_det : a.sino) + row0;
             const float *base = a.base ? a.base + row0 : nullptr;
-            for (int qq = 0; qq < count; ++qq) {
+            for (int qq = first; qq < end; ++qq) {
                 const float v = out_lds[qq * kOutPitch + tid];
-                float *o = out + (int64_t)qq * a.n_det;
+                float *o = out + qq * step;
                 if (a.parts > 1) *o = v;
-                else if (base) *o = fmaf(a.scale, v, base[(int64_t)qq * a.n_det]);
+                else if (base) *o = fmaf(a.scale, v, base[qq * step]);
                 else *o = a.accumulate ? fmaf(a.scale, v, *o) : a.scale * v;
             }
         }
@@ -360,6 +375,42 @@ __global__ __launch_bounds__(256) void fp_quad_kernel(const float *img, int n_sl
     }
 }
 
+// Turned copies: for slice z of n x n pixels, quad[z][y][x] holds the slice's
+// value at (x, y) and those of the slice turned by a quarter, reflected in x,
+// and transposed; quad_t[z][x][y] the same.
+__global__ __launch_bounds__(256) void fp_turned_kernel(const float *img, int n, float4 *quad, float4 *quad_t)
+{
+    __shared__ float4 t[32][33];
+    const int x0 = blockIdx.x * 32, y0 = blockIdx.y * 32;
+    const int64_t plane = (int64_t)n * n, z = blockIdx.z;
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    const float *p = img + z * plane;
+#pragma unroll
+    for (int j = ty; j < 32; j += 8) {
+        const int x = x0 + tx, y = y0 + j;
+        float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        if (x < n && y < n) {
+            v = make_float4(p[(int64_t)y * n + x], p[(int64_t)x * n + n - 1 - y], p[(int64_t)y * n + n - 1 - x], p[(int64_t)x * n + y]);
+            quad[z * plane + (int64_t)y * n + x] = v;
+        }
+        t[j][tx] = v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = ty; j < 32; j += 8) {
+        const int x = x0 + j, y = y0 + tx;
+        if (x < n && y < n) quad_t[z * plane + (int64_t)x * n + y] = t[tx][j];
+    }
+}
+
+hipError_t launch_forward_turned(const float *image, int n_slices, int n, float4 *quad, float4 *quad_t, hipStream_t s)
+{
+    (void)hipGetLastError();
+    const dim3 grid((unsigned)((n + 31) / 32), (unsigned)((n + 31) / 32), (unsigned)n_slices);
+    hipLaunchKernelGGL(fp_turned_kernel, grid, dim3(256), 0, s, image, n, quad, quad_t);
+    return hipGetLastError();
+}
+
 hipError_t launch_forward_quads(const float *image, int n_slices, int nx, int ny, float4 *quad, float4 *quad_t,
                                 hipStream_t s)
 {
@@ -374,7 +425,7 @@ hipError_t launch_forward(const FPArgs &a, int sl, hipStream_t s)
     // one workgroup per (slice group, bin block, angle block) triple, split
     // so that no launch exceeds 2^32 - 1 work-items
     FPArgs c = a;
-    c.triples = (int32_t)((int64_t)a.n_blocks * a.bin_blocks * ((a.n_slices + sl - 1) / sl));
+    c.triples = (int32_t)((int64_t)a.n_blocks * a.bin_blocks * (a.turned ? a.n_slices : (a.n_slices + sl - 1) / sl));
     const int64_t total = (int64_t)c.triples * a.parts;
     const int64_t max_x = ((((int64_t)1 << 32) - 1) / kFPBins);
     (void)hipGetLastError();

@@ -207,6 +207,9 @@ struct FPArgs {
     // each, whose sums go to partial [parts][S][Np][Nc] and are added up after
     int32_t parts, triples;
     float *partial;
+    // four "slices" of a group are one slice's turned copies: quad holds
+    // [S][n][n], the plan covers angles 0 .. N_p / 4
+    int32_t turned;
 };
 // Host: angle table and blocks with their staging shapes (XCT_ETOOBIG when
 // some block has no one-slice shape; *four tells whether every block has a
@@ -215,6 +218,7 @@ int fp_plan(const xct_geometry *g, std::vector<FPAngle> &ang, std::vector<FPBloc
 // `sl`: slices per workgroup, 1 or 4 (four read a.quad and a.quad_t, written
 // by launch_forward_quads from the same image).
 hipError_t launch_forward(const FPArgs &a, int sl, hipStream_t s);
+hipError_t launch_forward_turned(const float *image, int n_slices, int n, float4 *quad, float4 *quad_t, hipStream_t s);
 hipError_t launch_forward_quads(const float *image, int n_slices, int nx, int ny, float4 *quad, float4 *quad_t,
                                 hipStream_t s);
 

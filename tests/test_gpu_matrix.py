@@ -152,6 +152,44 @@ def test_split_forward_projection(xct, case):
     assert rel_l2(r.cpu().numpy(), y.astype(np.float32) - ref) < TOL
 
 
+@pytest.mark.parametrize("case", [
+    # slices, side, angles, bins, centre, pixel: square slices whose quarter of
+    # a uniform half turn is walked for four turned copies
+    (1, 512, 48, 730, 361.7, 1.0),     # N_p / 4 a row of two copies, the fewest angles
+    (2, 512, 50, 730, 364.5, 1.0),     # N_p / 2 odd
+    (1, 515, 96, 733, 366.0, 1.0),     # odd side
+    (3, 512, 432, 300, 149.5, 0.4),    # a group of three
+    (1, 640, 98, 460, 229.1, 0.5),     # a small pixel: wide hats
+])
+def test_forward_projection_by_turned_copies(xct, case):
+    """Against the oracle; and by each row of the last angles of the quarter,
+    which two copies share, against a call under the same angles that are no
+    uniform half turn (its last angle apart)."""
+    S, n, na, nd, c, pixel = case
+    rng = np.random.default_rng(90 + na)
+    g = synth.Geometry(n_angles=na, n_det=nd, nx=n, ny=n, center=c, pixel_size=pixel)
+    x = rng.standard_normal((S, n, n))
+    y = rng.standard_normal((S, na, nd))
+    dx, dy = to_dev(x), to_dev(y)
+    say("turned copies", case)
+    p = xct.forward_project(dx, g)
+    r = torch.empty_like(dy)
+    xct.xct_forward_residual(g, dx, dy, r, -0.5)
+    acc = dy.clone()
+    xct.xct_forward_project(g, dx, acc, -0.5, accumulate=True)
+    ang = np.asarray(g.angles, dtype=np.float64).copy()
+    ang[-1] += 1e-3
+    other = xct.forward_project(dx, synth.Geometry(n_angles=na, n_det=nd, nx=n, ny=n, center=c, pixel_size=pixel,
+                                                   angles=ang))
+    torch.cuda.synchronize()
+    assert torch.equal(r, acc)
+    ref = oracle.forward(x.astype(np.float32).astype(np.float64), g)
+    assert rel_l2(p.cpu().numpy(), ref) < TOL
+    assert rel_l2(r.cpu().numpy(), y.astype(np.float32) - 0.5 * ref) < TOL
+    for k in range(na - 1):
+        assert rel_l2(p[:, k].cpu().numpy(), other[:, k].cpu().double().numpy()) < 2 * TOL, k
+
+
 # The vector kernels' gate (coordinates below 96 or 192 bins)
 TOL_VECTOR = 2e-5
 
