@@ -790,9 +790,9 @@ int launch_bp_parts(BPJob j, int dtype, float *partial, hipStream_t s)
 // ---------------------------------------------------------------- matrix-core back-projection
 
 // How a job takes the matrix-core kernel: the kind (what a coordinate
-// serves), 32-column tiles per item (0: it does not), and the angles per launch.
+// serves), columns per item (0: it does not), and the angles per launch.
 struct MXPlan {
-    int kind = kMXPlain, nt = 0;
+    int kind = kMXPlain, cols = 0;
     int angles = 0;    // per launch (of one quarter turn for kMXQuarter)
     int part_len = 0;  // angles added up at a time (see MXArgs)
     int per_launch = 0;   // angles of a launch
@@ -827,28 +827,31 @@ int mx_ops(int kind)
 }
 
 // Work items of a job on the matrix cores, and their tiles.
-int64_t mx_items(const BPJob &j, int kind, int nt, int *tiles_x, int *tiles_y)
+int64_t mx_items(const BPJob &j, int kind, int cols, int *tiles_x, int *tiles_y)
 {
     const bool all_x = kind == kMXPlain || kind == kMXMirror, all_y = kind == kMXPlain;
     *tiles_x = ((all_x ? j.g->nx : (j.g->nx + 1) / 2) + kMXTile - 1) / kMXTile;
     *tiles_y = ((all_y ? j.g->ny : (j.g->ny + 1) / 2) + kMXTile - 1) / kMXTile;
     const int64_t tiles = kind == kMXQuarter2 ? (int64_t)*tiles_x * (*tiles_x + 1) / 2 : (int64_t)*tiles_x * *tiles_y;
-    const int spi = 32 * nt / mx_ops(kind);
+    const int spi = cols / mx_ops(kind);
     return tiles * ((j.n_slices + spi - 1) / spi);
 }
 
 // Which kernels a job takes is decided by their times as measured: the vector
-// kernels' above; the matrix kernel's ns per angle that a round of one item per
-// CU takes are 440 with one 32-column tile, 720 with two
-//    (2048^2, 8 slices: 3.65 ms; 8192^2, 16 slices: 293 ms).
-// The matrix path's own passes over the rows (magnitudes, split table) are
-// added at the 4.5 TB/s they reach, with 15 us for their launches.
+// kernels' above; the matrix kernel's ns per angle are 665 for a round of one
+// 64-column item per CU, and for two items per CU 740 with 32 columns and 440
+// with 16 (16 x 2048^2 x 1800 angles in 64 columns 4.94 ms; 32 x 1024^2 x 1025
+// in 32 columns 1.59 ms; 4 x 4096^2 x 1023 in 16 columns 3.66 ms).  The matrix
+// path's own passes over the rows (magnitudes, split table) are added at the
+// 4.5 TB/s they reach, with 20 us for their launches.
 double bp_matrix_ns(const BPJob &j, const MXPlan &p, int64_t items, int dtype)
 {
-    const int64_t cus = device_cus(), rounds = ((p.spread ? p.parts : 1) * items + cus - 1) / cus;
+    const int64_t slots = (p.cols < 64 ? 2 : 1) * device_cus();
+    const int64_t rounds = ((p.spread ? p.parts : 1) * items + slots - 1) / slots;
     const double rows = (double)j.n_slices * j.g->n_angles * j.g->n_det;
     const double angles = p.spread ? (double)p.part_len / p.per_launch * j.g->n_angles : j.g->n_angles;
-    double ns = rounds * (p.nt == 2 ? 720.0 : 440.0) * angles + rows * (2 * dtype_size(dtype) + 4) / 4500.0 + 15000.0;
+    const double round = p.cols == 64 ? 665.0 : p.cols == 32 ? 740.0 : 440.0;
+    double ns = rounds * round * angles + rows * (2 * dtype_size(dtype) + 4) / 4500.0 + 20000.0;
     if (p.spread) ns += sum_ns(j, p.parts);
     return ns;
 }
@@ -905,9 +908,9 @@ MXPlan mx_plan(const BPJob &j, int dtype)
         const int64_t ranges = fit >= g->n_angles ? 1 : (run + cap - 1) / cap;
         p.angles = ranges == 1 ? run : (int)((run + ranges - 1) / ranges + kMXAngles - 1) & ~(kMXAngles - 1);
         p.per_launch = kind == kMXQuarter ? 2 * p.angles : p.angles;
-        for (p.nt = 1; p.nt <= 2; ++p.nt) {
+        for (p.cols = kind == kMXQuarter2 ? 32 : 16; p.cols <= 64; p.cols *= 2) {
             int tx, ty;
-            const int64_t items = mx_items(j, kind, p.nt, &tx, &ty);
+            const int64_t items = mx_items(j, kind, p.cols, &tx, &ty);
             if (items >= (int64_t)1 << 22) continue;  // (grid of workgroups of 1024 below 2^32)
             mx_parts(j, p, items, dtype);
             const double ns = bp_matrix_ns(j, p, items, dtype);
@@ -957,7 +960,7 @@ int launch_bp_matrix(const BPJob &j, const MXPlan &p, int dtype, void *scratch, 
     a.part_len = p.part_len;
     float *partial = reinterpret_cast<float *>(static_cast<char *>(scratch) + mx_scratch_bytes(j, p) - align256(p.parts * image_bytes(j)));
     a.partial = p.spread ? partial : nullptr;
-    const int64_t items = mx_items(j, p.kind, p.nt, &a.tiles_x, &a.tiles_y);
+    const int64_t items = mx_items(j, p.kind, p.cols, &a.tiles_x, &a.tiles_y);
     const int sets = p.kind == kMXQuarter ? j.sets : 1;
     const int h = g->n_angles / sets / 2;                       // quarter turn
     const int run = p.kind == kMXQuarter ? h : g->n_angles;     // angles that one set's launches cover
@@ -979,7 +982,7 @@ int launch_bp_matrix(const BPJob &j, const MXPlan &p, int dtype, void *scratch, 
             a.items = (int32_t)items;
             e = launch_split(t, dtype, s);
             const int parts = (a.n_angles + a.part_len - 1) / a.part_len;
-            if (e == hipSuccess) e = launch_bp_mfma(a, p.nt, p.kind, (int)(p.spread ? items * parts : items), s);
+            if (e == hipSuccess) e = launch_bp_mfma(a, p.cols, p.kind, (int)(p.spread ? items * parts : items), s);
             if (e == hipSuccess && p.spread)
                 e = launch_sum_parts(a.image, partial, parts, (int64_t)j.n_slices * g->nx * g->ny, a.accumulate, amax, s);
             if (e != hipSuccess) return hip_fail(e);
@@ -1170,7 +1173,7 @@ static int backproject_one(const xct_geometry *g, int32_t n_slices, const void *
     // Scratch in stream-ordered memory.  A stream under capture, or no memory,
     // takes the vector kernels, which need none (a split job's parts are then
     // added up inside its items, to the same bits).
-    const size_t bytes = p.nt ? mx_scratch_bytes(j, p) : part_bytes(j);
+    const size_t bytes = p.cols ? mx_scratch_bytes(j, p) : part_bytes(j);
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     void *scratch = nullptr;
     if (bytes && hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
@@ -1179,7 +1182,7 @@ static int backproject_one(const xct_geometry *g, int32_t n_slices, const void *
     }
     (void)hipGetLastError();
     if (!scratch) return launch_bp_jobs({j}, sino_t, nullptr, nullptr, s);
-    const int rc = p.nt ? launch_bp_matrix(j, p, sino_t, scratch, s) : launch_bp_parts(j, sino_t, static_cast<float *>(scratch), s);
+    const int rc = p.cols ? launch_bp_matrix(j, p, sino_t, scratch, s) : launch_bp_parts(j, sino_t, static_cast<float *>(scratch), s);
     const hipError_t e = hipFreeAsync(scratch, s);
     return rc ? rc : e == hipSuccess ? XCT_OK : hip_fail(e);
 }
@@ -1473,7 +1476,7 @@ static size_t batch_bytes(const xct_slab *slabs, int32_t n_slabs, int32_t filter
         BPJob j = slab_job(slabs[i], &virt, nullptr);
         plan_parts(j);
         const MXPlan p = mx_plan(j, filtered_t);
-        if (p.nt) {
+        if (p.cols) {
             *scratch = std::max(*scratch, mx_scratch_bytes(j, p));
         } else {
             int spi;
@@ -1539,7 +1542,7 @@ int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_
         if (int rc = geo_tables(j.g, s, &j.t)) return rc;
         plan_parts(j);
         const MXPlan p = with_scratch ? mx_plan(j, filtered_t) : MXPlan();
-        if (p.nt) {
+        if (p.cols) {
             if (int rc = launch_bp_matrix(j, p, filtered_t, ws + need, s)) return rc;
             continue;
         }

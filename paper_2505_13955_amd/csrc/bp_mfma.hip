@@ -26,59 +26,66 @@
 // LDS without registers and without instructions per sample.
 //
 // Workgroup: a 32 x 32 pixel tile (and its images under the symmetries) for
-// 32 NT columns, 1024 threads; a wavefront owns an 8 x 8 block, 64 NT / 2
-// accumulators a lane.  A stage is four angles: windows of 52 bins (31 sqrt 2
-// pixels of footprint and the block's reads past it) of every column, in one
-// of three LDS buffers: while stage s is added up, stage s + 1 is complete and
-// stage s + 2 in flight.  A block reads 13 bins from its own window start b at
-// each angle, as four groups of four bins b + 3j .. b + 3j + 3: groups
-// overlap by one bin, so a pixel's two taps always lie in one group and fit
-// the matrix unit's 2:4 sparse form (v_smfmac_f32_32x32x32: two stored
-// weights of every four bins, with their positions).  Samples reach the
-// operand layout through transposing LDS reads, which need no alignment of b.
+// COLS = 16, 32 or 64 columns, 1024 threads; a wavefront owns an 8 x 8 block as
+// four 4 x 4 quarters, COLS / 16 accumulators of 16 x 16 each.  A stage is four
+// angles: windows of 52 bins (31 sqrt 2 pixels of footprint and a quarter's
+// reads past it) of every column, in one of three LDS buffers: while stage s is
+// added up, stage s + 1 is complete and stage s + 2 in flight.  A quarter reads
+// 7 bins from its own window start b at each angle, as two groups of four bins
+// b .. b + 3 and b + 3 .. b + 6: the groups overlap by one bin, so a pixel's two
+// taps always lie in one group and fit the matrix unit's 2:4 sparse form
+// (v_smfmac_f32_16x16x32: two stored weights of every four bins, with their
+// positions; 16 pixels x four angles' two groups x 16 columns).  Samples reach
+// the operand layout through transposing LDS reads, which need no alignment of
+// b.  Up to 32 columns two workgroups share a CU (64 registers, 80 KB of LDS);
+// with 64 columns the accumulators alone take 64.
 //
-// What bounds it: power.  At 16 x 4096^2 x 3072 angles the matrix cores are
-// busy 63 % of the cycles, and the clock under that load is 1.72 GHz (2.1 to
-// 2.3 GHz in the vector kernels).  Measured there: 35.7 ms (23,100 GUPS)
-// against 56.4 to 57.4 ms for the vector kernel.  On the way: rows loaded and
-// split by the main kernel 44.5 ms; 16 x 16 tiles with two wavefronts per SIMD
-// 37.9 ms; copies set up with fewer scalar instructions 38.2 -> 35.9 ms.
+// What bounds it: with 64 columns vector instructions and matrix instructions
+// together (39 % and 52 % of the cycles at 2.07 GHz, 16 x 2048^2 x 1800 angles:
+// 4.94 ms, 24,450 GUPS; the vector kernels 8.4 ms); with 32 and 16 columns the
+// vector instructions that form the weights (84 and 87 %; 4 x 4096^2 x 1023
+// angles with 16 columns: 3.66 ms, 18,800 GUPS, the vector kernels 5.90 ms).
+// Blocks of 8 x 8 pixels with four groups of four bins and 32 x 32 tiles took
+// half the LDS reads but twice the cycles of the matrix unit and two more
+// selects a weight: 5.44 ms, and 4.50 ms with 16 columns.  LDS passes without
+// bank conflicts (half of the LDS cycles are conflicts, as only high halves are
+// read together) gained 1 to 2 % for 64 columns, less than their addressing
+// costs in the others.
 #include "xct_internal.h"
 
 namespace xct {
 
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-typedef _Float16 h16 __attribute__((ext_vector_type(16)));
+typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 typedef __fp16 g4 __attribute__((ext_vector_type(4)));
 typedef float f2 __attribute__((ext_vector_type(2)));
-typedef float f16v __attribute__((ext_vector_type(16)));
+typedef float f4v __attribute__((ext_vector_type(4)));
 typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u8v __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) char lds_char;
 
 constexpr int kMXThreads = 1024; // 16 wavefronts, one 8 x 8 block each
-constexpr int kMXChunk = 64;     // angles whose parameters are formed at a time
 constexpr int kRec = 16;         // bytes of a table record
 constexpr int kMXWindow = 52;    // window bins per angle
 // LDS bytes of a window: 16 dwords more than a multiple of the 64 banks, so
-// the 16 lanes of a transposing read (4 bins of 4 windows) meet distinct banks
+// the 16 lanes of one angle's transposing read (4 bins of 4 windows) meet
+// distinct banks
 constexpr int kRegion = kMXWindow * kRec;
 static_assert(kRegion % 256 == 64, "window stride");
 constexpr int kOutCols = 8;      // columns that go out through LDS together
-// The block's reads stay inside the window: a block starts at the bin below
-// 24 sqrt(2) r + 2 at most (r pixels per bin) and reads 13 bins; and its
-// pixels' coordinates stay below 12 bins after the block's start.
-static_assert(24 * 1.41422 * kMXMaxRatio + 2 < kMXWindow - 12, "window covers the last block");
-static_assert(7 * 1.41422 * kMXMaxRatio + 1.02 < 12, "block footprint");
+// A quarter's reads stay inside the window: it starts at the bin below 28 sqrt(2)
+// r + 2 at most (r bins per pixel) and reads 7 bins; and its pixels' coordinates
+// stay below 6 bins after its start.
+static_assert(28 * 1.41422 * kMXMaxRatio + 2 < kMXWindow - 6, "window covers the last quarter");
+static_assert(3 * 1.41422 * kMXMaxRatio + 1.02 < 6, "quarter footprint");
 
-template <int NT>
-constexpr int mx_buf_bytes() { return kMXAngles * 8 * NT * kRegion; }
-template <int NT>
+template <int COLS>
+constexpr int mx_buf_bytes() { return kMXAngles * (COLS / 4) * kRegion; }
+template <int COLS>
 constexpr int mx_lds_bytes()
 {
-    const int stage = 3 * mx_buf_bytes<NT>(), out = kOutCols * kMXTile * (kMXTile + 1) * 4;
+    const int stage = 3 * mx_buf_bytes<COLS>(), out = kOutCols * kMXTile * (kMXTile + 1) * 4;
     return stage > out ? stage : out;
 }
 
@@ -132,17 +139,19 @@ constexpr int mx_ops(int kind)
     return kind == kMXPlain ? 1 : kind == kMXMirror ? 2 : kind == kMXQuarter2 ? 8 : 4;
 }
 
-template <int NT, int KIND>
-__global__ __launch_bounds__(kMXThreads, 4) void bp_mfma_kernel(MXArgs a)
+template <int COLS, int KIND>
+__global__ __launch_bounds__(kMXThreads, COLS < 64 ? 8 : 4) void bp_mfma_kernel(MXArgs a)
 {
     constexpr int G = mx_ops(KIND);
+    constexpr int kMXChunk = COLS == 64 ? 64 : 32;  // angles whose parameters are formed at a time
     constexpr bool kQuarter = KIND == kMXQuarter || KIND == kMXQuarter2;
     constexpr bool kReflect = KIND == kMXMirror2 || KIND == kMXQuarter2;
-    constexpr int R = 8 * NT;               // windows per angle: window r is operation r % G of slice group r / G
+    constexpr int NT = COLS / 16;           // 16-column tiles
+    constexpr int R = COLS / 4;             // windows per angle: window r is operation r % G of slice group r / G
     constexpr int GPI = R / G;              // groups of four slices per item
-    constexpr int kBuf = mx_buf_bytes<NT>();
+    constexpr int kBuf = mx_buf_bytes<COLS>();
     static_assert(R % G == 0, "whole slice groups per item");
-    __shared__ __attribute__((aligned(16))) char buf[mx_lds_bytes<NT>()];
+    __shared__ __attribute__((aligned(16))) char buf[mx_lds_bytes<COLS>()];
     __shared__ float4 par[2 * kMXChunk];
     __shared__ int wst[2 * kMXChunk];
     if (a.amax[0] != 0) return;  // a row element is not finite: the vector kernels take the slab
@@ -186,9 +195,10 @@ __global__ __launch_bounds__(kMXThreads, 4) void bp_mfma_kernel(MXArgs a)
     const int64_t row_bytes = (int64_t)a.n_det * kRec, group_bytes = row_bytes * Np;
 
     // Per angle of the launch: the tile's first pixel's coordinate above the
-    // window start, C, S, the window start of a block at the tile's corner
+    // window start, C, S, the window start of a quarter at the tile's corner
     // (with 1/64 bin of margin), and the window start itself.
     auto make_params = [&](int chunk) {
+        if (lane >= kMXChunk) return;
         const int l = l0 + chunk * kMXChunk + lane, slot = (chunk & 1) * kMXChunk + lane;
         float4 p = make_float4(2.0f, 0.0f, 0.0f, 2.0f - 0.015625f);
         int B = 0;
@@ -199,7 +209,7 @@ __global__ __launch_bounds__(kMXThreads, 4) void bp_mfma_kernel(MXArgs a)
             p.x = (float)(U - Bd);
             p.y = (float)cd.x;
             p.z = (float)cd.y;
-            p.w = p.x + 7.0f * (fminf(p.y, 0.0f) + fminf(p.z, 0.0f)) - 0.015625f;
+            p.w = p.x + 3.0f * (fminf(p.y, 0.0f) + fminf(p.z, 0.0f)) - 0.015625f;
             B = (int)Bd;
         }
         par[slot] = p;
@@ -258,17 +268,18 @@ __global__ __launch_bounds__(kMXThreads, 4) void bp_mfma_kernel(MXArgs a)
         }
     };
 
-    const int half = lane >> 5, c = lane & 15;
-    const float px = (float)(lane & 7), py = (float)((lane >> 3) & 3);  // pixel of an 8 x 4 half block
-    // a transposing read: lane c of 16 supplies bin c / 4 of window c % 4
-    const int lane_off = (6 * half + (c >> 2)) * kRec + (4 * ((lane >> 4) & 1) + (c & 3)) * kRegion;
+    const int c = lane & 15, quad = lane >> 4;
+    const float px = (float)(c & 3), py = (float)(c >> 2);  // pixel of a 4 x 4 quarter of the block
+    // a transposing read: lane c of 16 supplies bin c / 4 of window c % 4 of
+    // this lane's angle of the four
+    const int lane_off = (c >> 2) * kRec + (quad * R + (c & 3)) * kRegion;
     const float bx = (float)((wave & 3) * 8), by = (float)((wave >> 2) * 8);  // block's corner in the tile
 
-    // Weights of 32 pixels (8 x 4) at the coordinate t in [0, 12) above the
-    // block's window start: group g = floor(t / 3) of the four holds 1 - f and
-    // f at its bins r = floor(t) mod 3 and r + 1.
+    // Weights of 16 pixels (4 x 4) at the coordinate t in [0, 6) above the
+    // quarter's window start: group floor(t / 3) of the two holds 1 - f and f at
+    // its bins r = floor(t) mod 3 and r + 1.
     struct Weights {
-        h8 hi, lo;
+        h4 hi, lo;
         int ix;
     };
     auto weights = [&](float t) {
@@ -276,16 +287,14 @@ __global__ __launch_bounds__(kMXThreads, 4) void bp_mfma_kernel(MXArgs a)
         const float f = __builtin_amdgcn_fractf(t);
         const float hi = (f + 6144.0f) - 6144.0f;  // to a multiple of 2^-11
         const float lo = f - hi;
-        const uint32_t ph = pack_h2(1.0f - hi, hi), pl = pack_h2(-lo, lo);
-        // 2 floor(t) in the low bits, then floor(t) mod 3 from a packed table
-        const uint32_t i2 = __float_as_uint((t - f) + 4194304.0f);
-        const uint32_t r = __builtin_amdgcn_ubfe(0x24924924u, i2, 2u);
-        const bool c3 = t < 3.0f, c6 = t < 6.0f, c9 = t < 9.0f;
-        const u4 dh = {c3 ? ph : 0u, !c3 && c6 ? ph : 0u, !c6 && c9 ? ph : 0u, c9 ? 0u : ph};
-        const u4 dl = {c3 ? pl : 0u, !c3 && c6 ? pl : 0u, !c6 && c9 ? pl : 0u, c9 ? 0u : pl};
-        w.hi = __builtin_bit_cast(h8, dh);
-        w.lo = __builtin_bit_cast(h8, dl);
-        w.ix = (int)(r * 0x5555u + 0x4444u);  // positions r and r + 1 in every group
+        const uint32_t ph = pack_h2(1.0f - hi, hi);
+        uint32_t pl;  // (-lo, lo)
+        asm("v_cvt_pk_f16_f32 %0, -%1, %1" : "=v"(pl) : "v"(lo));
+        const bool c3 = t < 3.0f;
+        w.hi = __builtin_bit_cast(h4, (u2){c3 ? ph : 0u, c3 ? 0u : ph});
+        w.lo = __builtin_bit_cast(h4, (u2){c3 ? pl : 0u, c3 ? 0u : pl});
+        // positions r and r + 1 in both groups: byte floor(t) of 44 99 ee 44 99 ee
+        w.ix = (int)__builtin_amdgcn_perm(0xee99u, 0x44ee9944u, (uint32_t)t);
         return w;
     };
     typedef const lds_char *ldsp;
@@ -294,14 +303,12 @@ __global__ __launch_bounds__(kMXThreads, 4) void bp_mfma_kernel(MXArgs a)
                                           (__attribute__((address_space(3))) g4 *)(p + off)));
     };
 
-    f16v acc[2][NT];
+    f4v acc[4][NT];  // the block's 4 x 4 quarters
     for (;;) {
 #pragma unroll
-        for (int m = 0; m < 2; ++m)
+        for (int m = 0; m < 4; ++m)
 #pragma unroll
-            for (int n = 0; n < NT; ++n)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[m][n][r] = 0.0f;
+            for (int n = 0; n < NT; ++n) acc[m][n] = (f4v){0.0f, 0.0f, 0.0f, 0.0f};
 
         if (wave < 2) make_params(wave);
         __syncthreads();
@@ -313,42 +320,45 @@ __global__ __launch_bounds__(kMXThreads, 4) void bp_mfma_kernel(MXArgs a)
         const int nst = (l1 - l0 + kMXAngles - 1) / kMXAngles;
         int cur = 0, nxt = kBuf, far = 2 * kBuf;  // buffers of stages s, s + 1 and s + 2
         for (int s = 0; s < nst;) {
-            // every 16 stages: the parameters of the 64 angles after the next (the
-            // slots that the last 16 stages used)
-            if (s > 0 && wave == ((s >> 4) & 15)) make_params((s >> 4) + 1);
-            const int s_end = min(nst, s + 16);
+            // at each chunk: the parameters of the one after it (in the slots of
+            // the one before it)
+            constexpr int kRun = kMXChunk / kMXAngles;
+            if (s > 0 && wave == (s / kRun & 15)) make_params(s / kRun + 1);
+            const int s_end = min(nst, s + kRun);
             for (; s < s_end; ++s) {
                 const int slot0 = (kMXAngles * s) & (2 * kMXChunk - 1);
                 const int slot2 = (kMXAngles * (s + 2)) & (2 * kMXChunk - 1);
                 stage(s + 2, __builtin_amdgcn_readfirstlane(wst[slot2 + sa]), (lds_char *)buf + far);
+                const float4 p = par[slot0 + quad];
+                const float u = fmaf(bx + px, p.y, fmaf(by + py, p.z, p.x));
+                const float v = fmaf(bx, p.y, fmaf(by, p.z, p.w));
 #pragma unroll
-                for (int k = 0; k < 2; ++k) {
-                    // this lane's angle of the pair is 2 k + half; both angles' window
-                    // starts give the addresses of its samples
-                    const float4 p = par[slot0 + 2 * k + half];
-                    const float fl = floorf(fmaf(bx, p.y, fmaf(by, p.z, p.w)));
-                    const float t = fmaf(bx + px, p.y, fmaf(by + py, p.z, p.x)) - fl;
-                    const int o = (int)fl * kRec;
-                    const ldsp p0 = (ldsp)buf + (cur + (2 * k) * (R * kRegion) + __builtin_amdgcn_readlane(o, 0)) + lane_off;
-                    const ldsp p1 = (ldsp)buf + (cur + (2 * k + 1) * (R * kRegion) + __builtin_amdgcn_readlane(o, 32)) + lane_off;
-                    const Weights w[2] = {weights(t), weights(fmaf(4.0f, p.z, t))};
+                for (int m = 0; m < 4; ++m) {
+                    const float ux = m & 1 ? fmaf(4.0f, p.y, u) : u, vx = m & 1 ? fmaf(4.0f, p.y, v) : v;
+                    const float fl = floorf(m & 2 ? fmaf(4.0f, p.z, vx) : vx);
+                    const Weights w = weights((m & 2 ? fmaf(4.0f, p.z, ux) : ux) - fl);
+                    const ldsp at = (ldsp)buf + cur + (int)fl * kRec + lane_off;
+                    // (the 64-column kernel's registers hold all tiles' samples at once)
+                    constexpr int kGroup = COLS == 64 ? NT : 1;
 #pragma unroll
-                    for (int n = 0; n < NT; ++n) {
-                        const int q = n * 8 * kRegion;
-                        const u2 x0 = rd(p0, q), x1 = rd(p0, q + 3 * kRec), x2 = rd(p1, q), x3 = rd(p1, q + 3 * kRec);
-                        const u2 y0 = rd(p0, q + 8), y1 = rd(p0, q + 8 + 3 * kRec);
-                        const u2 y2 = rd(p1, q + 8), y3 = rd(p1, q + 8 + 3 * kRec);
-                        const h16 hi = __builtin_bit_cast(h16, (u8v){x0[0], x0[1], x1[0], x1[1], x2[0], x2[1], x3[0], x3[1]});
-                        const h16 lo = __builtin_bit_cast(h16, (u8v){y0[0], y0[1], y1[0], y1[1], y2[0], y2[1], y3[0], y3[1]});
+                    for (int n0 = 0; n0 < NT; n0 += kGroup) {
+                        h8 hi[kGroup], lo[kGroup];
 #pragma unroll
-                        for (int m = 0; m < 2; ++m)
-                            acc[m][n] = __builtin_amdgcn_smfmac_f32_32x32x32_f16(w[m].hi, hi, acc[m][n], w[m].ix, 0, 0);
+                        for (int n = 0; n < kGroup; ++n) {
+                            const int q = (n0 + n) * 4 * kRegion;
+                            const u2 x0 = rd(at, q), x1 = rd(at, q + 3 * kRec), y0 = rd(at, q + 8), y1 = rd(at, q + 8 + 3 * kRec);
+                            hi[n] = __builtin_bit_cast(h8, (u4){x0[0], x0[1], x1[0], x1[1]});
+                            lo[n] = __builtin_bit_cast(h8, (u4){y0[0], y0[1], y1[0], y1[1]});
+                        }
 #pragma unroll
-                        for (int m = 0; m < 2; ++m)
-                            acc[m][n] = __builtin_amdgcn_smfmac_f32_32x32x32_f16(w[m].lo, hi, acc[m][n], w[m].ix, 0, 0);
+                        for (int n = 0; n < kGroup; ++n)
+                            acc[m][n0 + n] = __builtin_amdgcn_smfmac_f32_16x16x32_f16(w.hi, hi[n], acc[m][n0 + n], w.ix, 0, 0);
 #pragma unroll
-                        for (int m = 0; m < 2; ++m)
-                            acc[m][n] = __builtin_amdgcn_smfmac_f32_32x32x32_f16(w[m].hi, lo, acc[m][n], w[m].ix, 0, 0);
+                        for (int n = 0; n < kGroup; ++n)
+                            acc[m][n0 + n] = __builtin_amdgcn_smfmac_f32_16x16x32_f16(w.lo, hi[n], acc[m][n0 + n], w.ix, 0, 0);
+#pragma unroll
+                        for (int n = 0; n < kGroup; ++n)
+                            acc[m][n0 + n] = __builtin_amdgcn_smfmac_f32_16x16x32_f16(w.hi, lo[n], acc[m][n0 + n], w.ix, 0, 0);
                     }
                 }
                 const int old = cur;
@@ -374,21 +384,20 @@ __global__ __launch_bounds__(kMXThreads, 4) void bp_mfma_kernel(MXArgs a)
 #pragma unroll
         for (int n = 0; n < NT; ++n) {
 #pragma unroll 1
-            for (int c0 = 0; c0 < 32; c0 += kOutCols) {
-                if (g0 + (8 * n + c0 / 4) / G >= n_groups) break;
+            for (int c0 = 0; c0 < 16; c0 += kOutCols) {
+                if (g0 + (4 * n + c0 / 4) / G >= n_groups) break;
                 __syncthreads();
-                const int col = lane & 31;
-                if (col >= c0 && col < c0 + kOutCols) {
-                    float *o = out + ((col - c0) * kMXTile + (int)by) * kPitch + (int)bx + 4 * half;
+                if (c >= c0 && c < c0 + kOutCols) {
+                    float *o = out + ((c - c0) * kMXTile + (int)by + quad) * kPitch + (int)bx;
 #pragma unroll
-                    for (int m = 0; m < 2; ++m)
+                    for (int m = 0; m < 4; ++m)
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) o[(4 * m + (r >> 2)) * kPitch + (r & 3)] = acc[m][n][r];
+                        for (int r = 0; r < 4; ++r) o[4 * (m >> 1) * kPitch + 4 * (m & 1) + r] = acc[m][n][r];
                 }
                 __syncthreads();
 #pragma unroll 1
                 for (int cc = 0; cc < kOutCols; ++cc) {
-                    const int r = 8 * n + (c0 + cc) / 4, op = r % G;
+                    const int r = 4 * n + (c0 + cc) / 4, op = r % G;
                     const int z = 4 * (g0 + r / G) + (cc & 3);
                     const bool reflected = KIND == kMXQuarter2 ? op >= 4 : kReflect && op >= 2;
                     const int turn = kQuarter ? op & 3 : op & 1;  // 0: Q, 1: R^2, 2: R^3, 3: R
@@ -533,7 +542,7 @@ hipError_t launch_split(const SplitArgs &a, int dtype, hipStream_t s)
     return hipGetLastError();
 }
 
-template <int NT>
+template <int COLS>
 static hipError_t launch_mx(const MXArgs &a, int kind, int grid, hipStream_t s)
 {
     auto go = [&](auto kernel) {
@@ -541,18 +550,19 @@ static hipError_t launch_mx(const MXArgs &a, int kind, int grid, hipStream_t s)
         return hipGetLastError();
     };
     switch (kind) {
-    case kMXPlain: return go(bp_mfma_kernel<NT, kMXPlain>);
-    case kMXMirror: return go(bp_mfma_kernel<NT, kMXMirror>);
-    case kMXMirror2: return go(bp_mfma_kernel<NT, kMXMirror2>);
-    case kMXQuarter: return go(bp_mfma_kernel<NT, kMXQuarter>);
-    default: return go(bp_mfma_kernel<NT, kMXQuarter2>);
+    case kMXPlain: return go(bp_mfma_kernel<COLS, kMXPlain>);
+    case kMXMirror: return go(bp_mfma_kernel<COLS, kMXMirror>);
+    case kMXMirror2: return go(bp_mfma_kernel<COLS, kMXMirror2>);
+    case kMXQuarter: return go(bp_mfma_kernel<COLS, kMXQuarter>);
+    default: return go(bp_mfma_kernel<COLS == 16 ? 32 : COLS, kMXQuarter2>);  // (32 columns at least)
     }
 }
 
-hipError_t launch_bp_mfma(const MXArgs &a, int nt, int kind, int grid, hipStream_t s)
+hipError_t launch_bp_mfma(const MXArgs &a, int cols, int kind, int grid, hipStream_t s)
 {
     (void)hipGetLastError();
-    return nt == 2 ? launch_mx<2>(a, kind, grid, s) : launch_mx<1>(a, kind, grid, s);
+    return cols == 64 ? launch_mx<64>(a, kind, grid, s) : cols == 32 ? launch_mx<32>(a, kind, grid, s)
+                                                                     : launch_mx<16>(a, kind, grid, s);
 }
 
 }  // namespace xct

@@ -133,7 +133,7 @@ struct SplitArgs {
     int32_t n_angles, n_det, n_slices;
     int32_t rows, k_first, k_jump, split;  // table row l is angle k_first + l, plus k_jump for l >= split
 };
-hipError_t launch_bp_mfma(const MXArgs &a, int nt, int kind, int grid, hipStream_t s);
+hipError_t launch_bp_mfma(const MXArgs &a, int cols, int kind, int grid, hipStream_t s);
 hipError_t launch_absmax(const void *sino, int dtype, int n_slices, int64_t per_slice, uint32_t *amax, hipStream_t s);
 hipError_t launch_split(const SplitArgs &a, int dtype, hipStream_t s);
 

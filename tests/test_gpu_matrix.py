@@ -24,6 +24,8 @@ pytestmark = pytest.mark.gpu
 # magnitude per bin, and interpolation keeps sqrt(2/3) of it: 3 2^-19 sqrt(3) =
 # 1.0e-5.
 TOL = 1e-5
+# The vector kernels' gate (coordinates below 96 or 192 bins)
+TOL_VECTOR = 2e-5
 
 
 @pytest.fixture(scope="module")
@@ -76,6 +78,67 @@ def test_adjoint_matches_oracle(xct, case):
     for z in range(S):
         assert rel_l2(img[z].cpu().numpy(), ref[z]) < TOL, z
     assert rel_l2(acc.cpu().numpy() - base.astype(np.float32), -0.5 * ref) < TOL
+
+
+@pytest.mark.parametrize("case", [
+    # slices, nx, ny, angles, bins, centre, pixel, angle set
+    (16, 700, 300, 501, 770, 383.1, 0.07, "half"),   # plain, 16 columns, the image within a few bins
+    (30, 515, 490, 301, 729, 363.7, 1.1, "rand"),    # 32 columns, the largest pixel
+    (61, 413, 390, 301, 600, 299.7, 1.0, "half"),    # 64 columns
+    (7, 600, 501, 501, 900, 449.5, 1.1, "rand"),     # mirror, 16
+    (15, 600, 501, 301, 900, 449.5, 1.0, "rand"),    # 32
+    (31, 430, 411, 301, 600, 299.5, 0.8, "rand"),    # 64
+    (4, 813, 811, 602, 1160, 579.5, 1.0, "half"),    # mirror with reflection, 16
+    (8, 613, 611, 501, 900, 449.0, 1.0, "half"),     # 32
+    (15, 513, 511, 401, 727, 363.0, 1.0, "half"),    # 64
+    (3, 800, 800, 600, 1140, 569.5, 1.0, "turn"),    # quarter turn, 16
+    (7, 800, 800, 400, 1140, 569.5, 1.0, "turn"),    # 32
+    (15, 602, 602, 404, 860, 429.5, 1.0, "turn"),    # 64
+    (9, 514, 514, 640, 740, 369.0, 1.0, "full"),     # two half-turn sets, 16
+    (4, 1030, 1030, 300, 1460, 729.5, 1.0, "half"),  # quarter turn with reflection, 32
+    (8, 1030, 1030, 180, 1460, 729.5, 1.0, "half"),  # 64
+])
+def test_adjoint_by_columns(xct, case):
+    """Every kind and column count of the matrix-core kernel."""
+    S, nx, ny, na, nd, c, px, kind = case
+    rng = np.random.default_rng(950 + S)
+    if kind == "turn":  # arbitrary angles and the same a quarter turn on
+        a = np.sort(rng.uniform(0.01, 0.5 * math.pi, na // 2))
+        a = np.concatenate([a, a + 0.5 * math.pi])
+    else:
+        a = _angles(kind, na, rng)
+    g = synth.Geometry(n_angles=na, n_det=nd, nx=nx, ny=ny, center=c, pixel_size=px, angles=a)
+    q = rng.standard_normal((S, na, nd)) * np.linspace(0.5, 2.0, S)[:, None, None]
+    say("adjoint by columns", case)
+    img = xct.project_adjoint(to_dev(q), g)
+    torch.cuda.synchronize()
+    ref = oracle.backproject(q.astype(np.float32).astype(np.float64), g, oracle.adjoint_scale(g))
+    for z in range(S):
+        assert rel_l2(img[z].cpu().numpy(), ref[z]) < TOL, z
+
+
+@pytest.mark.parametrize("case", [
+    (61, 413, 390, 301, 600, 299.7),   # 64 columns, plain
+    (4, 813, 811, 602, 1160, 579.5),   # 16 columns, mirror with reflection
+    (4, 1030, 1030, 300, 1460, 729.5),  # 32 columns, quarter turn with reflection
+])
+def test_non_finite_rows_leave_the_matrix_cores(xct, case):
+    """The slab takes vector kernels (not always xct_backproject's: slices in
+    pairs): the same pixels stay finite, and lie within those kernels' gate."""
+    S, nx, ny, na, nd, c = case
+    g = synth.Geometry(n_angles=na, n_det=nd, nx=nx, ny=ny, center=c)
+    say("non-finite", case)
+    for bad in (float("nan"), float("-inf")):
+        q = torch.randn(S, na, nd, generator=torch.Generator().manual_seed(5)).cuda()
+        q[S - 1, na // 3, nd // 2] = bad
+        img = xct.project_adjoint(q, g)
+        want = torch.empty_like(img)
+        xct.xct_backproject(g, q, want, 1.0)
+        torch.cuda.synchronize()
+        assert not torch.isfinite(img).all()
+        assert torch.equal(torch.isfinite(img), torch.isfinite(want))
+        ok = torch.isfinite(want)
+        assert rel_l2(img[ok].cpu().numpy(), want[ok].cpu().double().numpy()) < TOL_VECTOR
 
 
 @pytest.mark.parametrize("case", [0, 4, 7, 9])
@@ -188,10 +251,6 @@ def test_forward_projection_by_turned_copies(xct, case):
     assert rel_l2(r.cpu().numpy(), y.astype(np.float32) - 0.5 * ref) < TOL
     for k in range(na - 1):
         assert rel_l2(p[:, k].cpu().numpy(), other[:, k].cpu().double().numpy()) < 2 * TOL, k
-
-
-# The vector kernels' gate (coordinates below 96 or 192 bins)
-TOL_VECTOR = 2e-5
 
 
 @pytest.mark.parametrize("case", [
