@@ -1099,10 +1099,12 @@ __global__ __launch_bounds__(256) void filter_fused_kernel(FilterArgs a, int in_
         // B + s NS, then the next group's samples: loads complete in order,
         // so the wait for these factors does not wait for the prefetch
         float HA[16], HB[16];
+        const int A2 = T == 0 ? NS / 2 - 8 * NS : A;
+        const int B1 = T == 0 ? NS / 2 + 8 * NS : B, B2 = T == 0 ? NS : B, B3 = T == 0 ? -7 * NS : B;
 #pragma unroll
         for (int s = 0; s < 16; ++s) {
-            HA[s] = a.H[A + s * NS];
-            HB[s] = a.H[B + s * NS];
+            HA[s] = a.H[(s < 8 ? A : A2) + s * NS];
+            HB[s] = a.H[(s < 8 ? B1 : s < 15 ? B2 : B3) + s * NS];
         }
         const float HM = a.H[M];
         if constexpr (FEP) {
@@ -1171,40 +1173,61 @@ __global__ __launch_bounds__(256) void filter_fused_kernel(FilterArgs a, int in_
         }
         dft<16, false>(xa);
         dft<16, false>(xb);
-        // Z at position A + s NS is xa[dft_slot<16>(s)]; Z' replaces it there.
-#define XA(s) xa[dft_slot<16>(s)]
-#define XB(s) xb[dft_slot<16>(s)]
-        if (T == 0) {
-            // butterfly 0: pairs (s NS, (16 - s) NS), with bins 0 and M/2
-            // paired with themselves (H[M]: the real row's Nyquist bin);
-            // butterfly NS/2: pairs (NS/2 + s NS, NS/2 + (15 - s) NS);
-            // W^(s NS) = exp(-2 pi i s / 32)
-            float2 d;
-            spectrum_pair(XA(0), XA(0), make_float2(1.0f, 0.0f), HA[0], HM, XA(0), d);
-            spectrum_pair(XA(8), XA(8), make_float2(0.0f, -1.0f), HA[8], HA[8], XA(8), d);
+        // Z at position A + s NS is xa[dft_slot<16>(s)]; pairs (A + s NS, M - A -
+        // s NS = B + (15 - s) NS) take W^(T + s NS).  Thread 0's butterflies 0
+        // and NS/2 are their own mirrors: it exchanges values so that its pairs
+        // stand in the same places (s < 8: (s NS, (16 - s) NS); s >= 8: NS/2 +
+        // (s - 8) NS and its mirror), except bins 0 and M/2, which pair with
+        // themselves (H[M]: the real row's Nyquist bin).  Taking its 17 pairs in
+        // a branch of their own, after the other lanes' 16, cost its wavefront
+        // (the row's last) as much again: 360 rows of 367 bins 16 us against
+        // 13, 20000 of 1449 151 against 147, a front end of 57600 rows of 2900
+        // 947 against 925 (bound by vector instructions, 93 % of the cycles).
+        float2 ya[16], yb[16];
 #pragma unroll
-            for (int s = 1; s < 8; ++s)
-                spectrum_pair(XA(s), XA(16 - s), root<false>(s, 32), HA[s], HA[16 - s], XA(s), XA(16 - s));
-#pragma unroll
-            for (int s = 0; s < 8; ++s)
-                spectrum_pair(XB(s), XB(15 - s), root<false>(2 * s + 1, 64), HB[s], HB[15 - s], XB(s), XB(15 - s));
+        for (int s = 0; s < 16; ++s) {
+            ya[s] = xa[dft_slot<16>(s)];
+            yb[s] = xb[dft_slot<16>(s)];
         }
-        if (T != 0) {
-            // pairs (A + s NS, M - A - s NS = B + (15 - s) NS), W^(T + s NS)
+        const bool first_wave = __builtin_amdgcn_readfirstlane(T) == 0;
+        float2 z0 = make_float2(0.0f, 0.0f), z8 = z0;
+        const float2 WT2 = T == 0 ? root<false>(-15, 64) : WT;  // times exp(-2 pi i s / 32): W^(NS/2 + (s - 8) NS)
+        auto sel = [&](float2 u, float2 v) { return make_float2(T == 0 ? u.x : v.x, T == 0 ? u.y : v.y); };
+        if (first_wave) {
+            if (T == 0) {
+                float2 d;
+                spectrum_pair(ya[0], ya[0], make_float2(1.0f, 0.0f), HA[0], HM, z0, d);
+                spectrum_pair(ya[8], ya[8], make_float2(0.0f, -1.0f), HB[15], HB[15], z8, d);
+            }
+            float2 ta[8];
 #pragma unroll
-            for (int s = 0; s < 16; ++s)
-                spectrum_pair(XA(s), XB(15 - s), turn<false>(WT, s, 32), HA[s], HB[15 - s], XA(s), XB(15 - s));
+            for (int s = 0; s < 8; ++s) ta[s] = ya[8 + s];
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+                ya[8 + s] = sel(yb[s], ya[8 + s]);
+                yb[s] = sel(yb[8 + s], yb[s]);
+                if (s < 7) yb[8 + s] = sel(ta[s + 1], yb[8 + s]);
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < 16; ++s)
+            spectrum_pair(ya[s], yb[15 - s], turn<false>(s < 8 ? WT : WT2, s, 32), HA[s], HB[15 - s], ya[s], yb[15 - s]);
+        if (first_wave) {
+            float2 ta[8];
+#pragma unroll
+            for (int s = 0; s < 8; ++s) ta[s] = ya[8 + s];
+#pragma unroll
+            for (int s = 0; s < 7; ++s) ya[9 + s] = sel(yb[8 + s], ya[9 + s]);
+            ya[8] = sel(z8, ya[8]);
+            ya[0] = sel(z0, ya[0]);
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+                yb[8 + s] = sel(yb[s], yb[8 + s]);
+                yb[s] = sel(ta[s], yb[s]);
+            }
         }
         // P3^H: DFT^H over s (inputs in natural order), conj twiddles, to A + t NS
         {
-            float2 ya[16], yb[16];
-#pragma unroll
-            for (int s = 0; s < 16; ++s) {
-                ya[s] = XA(s);
-                yb[s] = XB(s);
-            }
-#undef XA
-#undef XB
             dft<16, true>(ya);
             dft<16, true>(yb);
             float2 pA[16], pB[16];
