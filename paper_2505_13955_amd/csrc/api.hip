@@ -839,19 +839,22 @@ int64_t mx_items(const BPJob &j, int kind, int cols, int *tiles_x, int *tiles_y)
 
 // Which kernels a job takes is decided by their times as measured: the vector
 // kernels' above; the matrix kernel's ns per angle are 665 for a round of one
-// 64-column item per CU, and for two items per CU 740 with 32 columns and 440
-// with 16 (16 x 2048^2 x 1800 angles in 64 columns 4.94 ms; 32 x 1024^2 x 1025
-// in 32 columns 1.59 ms; 4 x 4096^2 x 1023 in 16 columns 3.66 ms).  The matrix
-// path's own passes over the rows (magnitudes, split table) are added at the
-// 4.5 TB/s they reach, with 20 us for their launches.
+// 64-column item per CU, and for two items per CU (one) 740 (490) with 32
+// columns and 440 (290) with 16 (16 x 2048^2 x 1800 angles in 64 columns 4.94
+// ms; 32 x 1024^2 x 1025 in 32 columns 1.57 ms; 4 x 4096^2 x 1023 in 16 columns
+// 3.63 ms; 4 x 4096^2 x 3072, 2080 items of 32 columns or 4096 of 16: 9.1 and
+// 9.7 ms).  The matrix path's own passes over the rows (magnitudes, split
+// table) are added at the 4.5 TB/s they reach, with 30 us for their launches (4
+// x 512^2 x 721 angles: 102 us in matrix form, 94 in vector form).
 double bp_matrix_ns(const BPJob &j, const MXPlan &p, int64_t items, int dtype)
 {
-    const int64_t slots = (p.cols < 64 ? 2 : 1) * device_cus();
-    const int64_t rounds = ((p.spread ? p.parts : 1) * items + slots - 1) / slots;
     const double rows = (double)j.n_slices * j.g->n_angles * j.g->n_det;
     const double angles = p.spread ? (double)p.part_len / p.per_launch * j.g->n_angles : j.g->n_angles;
-    const double round = p.cols == 64 ? 665.0 : p.cols == 32 ? 740.0 : 440.0;
-    double ns = rounds * round * angles + rows * (2 * dtype_size(dtype) + 4) / 4500.0 + 20000.0;
+    const VectorTimes t = p.cols == 64   ? VectorTimes{1, 665, 665}
+                          : p.cols == 32 ? VectorTimes{2, 740, 490}
+                                         : VectorTimes{2, 440, 290};
+    double ns = vector_rounds(t, (p.spread ? p.parts : 1) * items) * angles;
+    ns += rows * (2 * dtype_size(dtype) + 4) / 4500.0 + 30000.0;
     if (p.spread) ns += sum_ns(j, p.parts);
     return ns;
 }

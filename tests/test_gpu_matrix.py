@@ -82,21 +82,30 @@ def test_adjoint_matches_oracle(xct, case):
 
 @pytest.mark.parametrize("case", [
     # slices, nx, ny, angles, bins, centre, pixel, angle set
-    (16, 700, 300, 501, 770, 383.1, 0.07, "half"),   # plain, 16 columns, the image within a few bins
-    (30, 515, 490, 301, 729, 363.7, 1.1, "rand"),    # 32 columns, the largest pixel
-    (61, 413, 390, 301, 600, 299.7, 1.0, "half"),    # 64 columns
-    (7, 600, 501, 501, 900, 449.5, 1.1, "rand"),     # mirror, 16
-    (15, 600, 501, 301, 900, 449.5, 1.0, "rand"),    # 32
-    (31, 430, 411, 301, 600, 299.5, 0.8, "rand"),    # 64
-    (4, 813, 811, 602, 1160, 579.5, 1.0, "half"),    # mirror with reflection, 16
-    (8, 613, 611, 501, 900, 449.0, 1.0, "half"),     # 32
-    (15, 513, 511, 401, 727, 363.0, 1.0, "half"),    # 64
-    (3, 800, 800, 600, 1140, 569.5, 1.0, "turn"),    # quarter turn, 16
-    (7, 800, 800, 400, 1140, 569.5, 1.0, "turn"),    # 32
-    (15, 602, 602, 404, 860, 429.5, 1.0, "turn"),    # 64
-    (9, 514, 514, 640, 740, 369.0, 1.0, "full"),     # two half-turn sets, 16
-    (4, 1030, 1030, 300, 1460, 729.5, 1.0, "half"),  # quarter turn with reflection, 32
-    (8, 1030, 1030, 180, 1460, 729.5, 1.0, "half"),  # 64
+    # ragged tiles and slice groups, most with parts of their own
+    (16, 700, 300, 501, 770, 383.1, 0.07, "half"),   # plain, the image within a few bins
+    (30, 515, 490, 301, 729, 363.7, 1.1, "rand"),    # the largest pixel
+    (61, 413, 390, 301, 600, 299.7, 1.0, "half"),
+    (7, 600, 501, 501, 900, 449.5, 1.1, "rand"),     # mirror
+    (15, 600, 501, 301, 900, 449.5, 1.0, "rand"),
+    (31, 430, 411, 301, 600, 299.5, 0.8, "rand"),
+    (4, 813, 811, 602, 1160, 579.5, 1.0, "half"),    # mirror with reflection
+    (8, 613, 611, 501, 900, 449.0, 1.0, "half"),
+    (15, 513, 511, 401, 727, 363.0, 1.0, "half"),
+    (3, 800, 800, 600, 1140, 569.5, 1.0, "turn"),    # quarter turn
+    (7, 800, 800, 400, 1140, 569.5, 1.0, "turn"),
+    (15, 602, 602, 404, 860, 429.5, 1.0, "turn"),
+    (9, 514, 514, 640, 740, 369.0, 1.0, "full"),     # two half-turn sets
+    (4, 1030, 1030, 300, 1460, 729.5, 1.0, "half"),  # quarter turn, reflected set
+    (8, 1030, 1030, 180, 1460, 729.5, 1.0, "half"),
+    # items that fill one round of the device
+    (64, 512, 500, 150, 729, 363.7, 1.0, "half"),      # plain, 64 columns
+    (32, 700, 690, 101, 1000, 499.5, 1.0, "rand"),     # mirror, 64
+    (16, 990, 1010, 81, 1440, 719.5, 1.0, "rand"),     # 32
+    (16, 1020, 1010, 101, 1450, 724.5, 1.0, "half"),   # mirror with reflection, 64
+    (32, 700, 700, 80, 1000, 499.5, 1.0, "turn"),      # quarter turn, 64
+    (4, 1950, 1950, 100, 2780, 1389.5, 1.0, "half"),   # quarter turn with reflection, 32
+    (8, 1400, 1400, 240, 1990, 994.5, 1.0, "half"),    # 64
 ])
 def test_adjoint_by_columns(xct, case):
     """Every kind and column count of the matrix-core kernel."""
