@@ -13,7 +13,7 @@ for the FP32-stored sinogram, from the median of the per-step times; the FP16-
 and BF16-stored runs (FP32 arithmetic) are reported beside it.  Every storage
 leg carries its error against the FP64 oracle fed the decoded stored sinogram,
 per slice (relative L2 and max-abs over one pixel of every 64 x 64 tile), and
-its fraction of the FP32 vector and LDS rooflines.  Further legs: the
+its fraction of the matrix cores' rate.  Further legs: the
 64 x 2048^2 slab through xct_fbp_batch, the slab with an odd angle count (the
 back-projector without the quarter-turn symmetry), the raw-counts pipeline,
 the uneven batch, the offset scan and the differentiable projector pair.
@@ -38,18 +38,20 @@ if ROOT not in sys.path:
 METRIC = "GUPS (voxel×angle updates/s) for FBP, fp32 vs fp16-storage, at stated L2 error"
 FLOPS_PER_UPDATE = 6  # coordinate FMA (2), fraction (1), interpolation FMA (2), accumulate (1)
 FP32_VECTOR_PEAK_TFLOPS = 157.3
-LDS_BYTES_PER_UPDATE = 8  # one (a, d) FP32 pair per interpolation
-# LDS read peak: 64 banks x 4 bytes per clock per CU, 256 CUs, 2.4 GHz
-LDS_PEAK_BYTES_PER_CLK_CU = 256
 CUS, CLOCK_HZ = 256, 2.4e9
-LDS_PEAK_TBPS = LDS_PEAK_BYTES_PER_CLK_CU * CUS * CLOCK_HZ / 1e12
+# The matrix-core back-projection: three 2:4 sparse FP16 products of 16 x 16 x
+# 32 (dense-equivalent flops) per 16 pixels x 16 columns x 4 angles, each 16
+# cycles of one of a CU's four matrix units
+MATRIX_FLOPS_PER_UPDATE = 3 * 2 * 16 * 16 * 32 / (16 * 16 * 4)
+MATRIX_PEAK_TFLOPS = CUS * 4 * (2 * 16 * 16 * 32 / 16) * CLOCK_HZ / 1e12
 HBM_PEAK_GBPS = 8000.0
-# HBM bytes of one FP32 back-projection launch of the full 16-slice slab:
-# rocprofv3 FETCH_SIZE x 2.0 plus WRITE_SIZE x 1.0 (the factors under which a
-# plain 1 GiB device copy reads and writes 1 GiB), from the counter passes in
-# profiles/bp_sym_kernel_slab16_8192.txt (None while no counter pass has been
-# taken on the current kernel build).
-BP_TRAFFIC_BYTES = 9.887e10
+# HBM bytes of one FP32 back-projection of the full 16-slice slab (three ranges
+# of angles, each its split table and its launch, and the pass that finds the
+# magnitudes): rocprofv3 FETCH_SIZE x 2.0 plus WRITE_SIZE x 1.0 (the factors
+# under which a plain 1 GiB device copy reads and writes 1 GiB), from the
+# counter passes in profiles/bp_mfma_kernel.txt (None while no counter pass has
+# been taken on the current kernel build).
+BP_TRAFFIC_BYTES = 2.286e11
 
 
 def parse():
@@ -101,12 +103,10 @@ def _alu_roofline(kernel, updates, ms):
             "frac": achieved / FP32_VECTOR_PEAK_TFLOPS}
 
 
-def _lds_roofline(kernel, updates, ms):
-    achieved = LDS_BYTES_PER_UPDATE * updates / (ms * 1e-3) / 1e12
-    return {"kernel": kernel, "bound": "lds", "achieved": achieved, "peak": LDS_PEAK_TBPS,
-            "unit": "TB/s", "frac": achieved / LDS_PEAK_TBPS,
-            "bytes_per_clk_per_cu": achieved * 1e12 / (CUS * CLOCK_HZ),
-            "peak_bytes_per_clk_per_cu": LDS_PEAK_BYTES_PER_CLK_CU}
+def _matrix_roofline(kernel, updates, ms):
+    achieved = MATRIX_FLOPS_PER_UPDATE * updates / (ms * 1e-3) / 1e12
+    return {"kernel": kernel, "bound": "mfma", "achieved": achieved, "peak": MATRIX_PEAK_TFLOPS,
+            "unit": "TFLOP/s", "frac": achieved / MATRIX_PEAK_TFLOPS}
 
 
 def tile_pixels(ny, nx, seed, full_rows=0):
@@ -194,7 +194,7 @@ def measure_raw_pipeline(xct, torch, synth, spec, p64, filt, stream, steps, warm
 
 def measure_fbp_batch_c3(xct, torch, spec, p64, stream, steps, warmup):
     """The same FP32 slab through xct_fbp_batch (filter into the workspace,
-    one persistent back-projection launch, the FBP weight applied by the
+    back-projection, the FBP weight applied by the
     library)."""
     g = spec.geom
     S = p64.shape[0]
@@ -230,7 +230,7 @@ def measure_c2(xct, torch, configs, stream, steps, warmup, with_oracle):
     out = {"workload": "64 x 2048^2, 1800 angles over [0,pi), 2900 bins, Shepp-Logan, 20 drifting "
                        "ellipses, Poisson 1e5 photons; FP32; xct_fbp_batch",
            "ms": ms, "gups": updates / (ms * 1e-3) / 1e9, "updates": updates,
-           "roofline": _alu_roofline("bp_sym_kernel<float, 96, 2>", updates, ms)}
+           "roofline": _matrix_roofline("filter + bp_mfma_kernel (whole call)", updates, ms)}
     log(f"c2: {ms:.3f} ms, {out['gups']:.0f} GUPS")
     if with_oracle:
         per = {}
@@ -262,7 +262,7 @@ def measure_generic_angles(xct, torch, configs, stream, steps, warmup, with_orac
     out = {"workload": f"{S} x 8192^2, 6143 angles over [0,pi) (odd count), 8192 bins, Hann, FP32; "
                        "xct_backproject",
            "bp_ms": bp_ms, "bp_gups": updates / (bp_ms * 1e-3) / 1e9, "updates": updates,
-           "roofline": _alu_roofline("back-projection without quarter-turn symmetry", updates, bp_ms)}
+           "roofline": _matrix_roofline("bp_mfma_kernel<16, kMXMirror2>", updates, bp_ms)}
     log(f"generic angles: back-projection {bp_ms:.3f} ms, {out['bp_gups']:.0f} GUPS")
     if with_oracle:
         l2, mx, _, _ = slice_errors(torch, img[0], p[0], g, spec.window, tile_pixels(8192, 8192, 70))
@@ -300,7 +300,7 @@ def measure_offset_scan(xct, torch, configs, stream, steps, warmup):
 
 def measure_uneven_batch(xct, torch, configs, encode_storage, stream, steps, warmup):
     """Filter + back-projection of the uneven batch (24 x 512^2, 12 x 1024^2,
-    4 x 2048^2, BF16-stored, Ram-Lak) in one persistent launch per kernel,
+    4 x 2048^2, BF16-stored, Ram-Lak) in one call,
     against the same slabs launched one at a time."""
     specs = configs.c5()
     slabs = []
@@ -319,11 +319,11 @@ def measure_uneven_batch(xct, torch, configs, encode_storage, stream, steps, war
     log(f"uneven batch: {ms:.3f} ms in one launch, {sum(alone):.3f} ms slab by slab")
     return {
         "workload": "24 x 512^2 (720 angles), 12 x 1024^2 (1440), 4 x 2048^2 (2048); bf16 storage, "
-                    "Ram-Lak; xct_fbp_batch, one persistent back-projection launch",
+                    "Ram-Lak; xct_fbp_batch",
         "ms": ms, "gups": updates / (ms * 1e-3) / 1e9,
         "slab_by_slab_ms": alone, "slab_by_slab_gups": updates / (sum(alone) * 1e-3) / 1e9,
         "updates": updates,
-        "roofline": _alu_roofline("filter + bp_sym_kernel<float, 96, 2> (whole call)", updates, ms),
+        "roofline": _matrix_roofline("filter + bp_mfma_kernel (whole call)", updates, ms),
     }
 
 
@@ -446,8 +446,7 @@ def main():
             "bp_ms": b_ms,
             "bp_gups": updates / (b_ms * 1e-3) / 1e9,
             "wall_ms_per_step": 1e3 * t_wall / args.steps,
-            "roofline": _alu_roofline("bp_sym_kernel<float, 96, 2>", updates, b_ms),
-            "roofline_lds": _lds_roofline("bp_sym_kernel<float, 96, 2>", updates, b_ms),
+            "roofline": _matrix_roofline("bp_mfma_kernel<64, kMXQuarter>", updates, b_ms),
         }
         log(st, json.dumps({k: round(v, 3) for k, v in r.items() if isinstance(v, float)}))
         got = image[samp_slice].cpu().numpy()[rows, :].ravel().astype(np.float64)
@@ -546,10 +545,10 @@ def main():
     roof = dict(m["roofline"])
     roof.update({
         "traffic": BP_TRAFFIC_BYTES if (main_st == "f32" and args.filtered == "f32" and S == 16) else None,
-        "traffic_unit": "bytes per launch",
+        "traffic_unit": "bytes per back-projection",
         "algorithmic_bytes": (S * g.n_angles * g.n_det * (4 if args.filtered == "f32" else 2)
                               + 4 * S * g.nx * g.ny),
-        "flops_per_update": FLOPS_PER_UPDATE,
+        "flops_per_update": MATRIX_FLOPS_PER_UPDATE,
         "updates_per_launch": updates,
     })
     out = {
@@ -579,7 +578,6 @@ def main():
         "bp_ms": m["bp_ms"],
         "storage": results,
         "roofline": roof,
-        "roofline_lds": m["roofline_lds"],
         "cpu_baseline": cpu,
     }
     out.update(extra)

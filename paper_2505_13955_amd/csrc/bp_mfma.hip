@@ -40,11 +40,12 @@
 // b.  Up to 32 columns two workgroups share a CU (64 registers, 80 KB of LDS);
 // with 64 columns the accumulators alone take 64.
 //
-// What bounds it: with 64 columns vector instructions and matrix instructions
-// together (39 % and 52 % of the cycles at 2.07 GHz, 16 x 2048^2 x 1800 angles:
-// 4.94 ms, 24,450 GUPS; the vector kernels 8.4 ms); with 32 and 16 columns the
-// vector instructions that form the weights (84 and 87 %; 4 x 4096^2 x 1023
-// angles with 16 columns: 3.66 ms, 18,800 GUPS, the vector kernels 5.90 ms).
+// What bounds it: with 64 columns the matrix cores, the vector instructions and
+// the LDS together (0.52 of the matrix units' cycles, 0.39 vector instructions a
+// cycle and CU, LDS 0.73 at 2.07 GHz; 16 x 2048^2 x 1800 angles: 4.94 ms, 24,450
+// GUPS; the vector kernels 8.4 ms); with 32 and 16 columns the vector
+// instructions that form the weights (0.84 and 0.87; 4 x 4096^2 x 1023 angles
+// with 16 columns: 3.63 ms, 18,900 GUPS, the vector kernels 5.90 ms).
 // Blocks of 8 x 8 pixels with four groups of four bins and 32 x 32 tiles took
 // half the LDS reads but twice the cycles of the matrix unit and two more
 // selects a weight: 5.44 ms, and 4.50 ms with 16 columns.  LDS passes without

@@ -1182,7 +1182,7 @@ __global__ __launch_bounds__(256) void filter_fused_kernel(FilterArgs a, int in_
         // a branch of their own, after the other lanes' 16, cost its wavefront
         // (the row's last) as much again: 360 rows of 367 bins 16 us against
         // 13, 20000 of 1449 151 against 147, a front end of 57600 rows of 2900
-        // 947 against 925 (bound by vector instructions, 93 % of the cycles).
+        // 947 against 925 (bound by vector instructions, 0.93 a cycle and CU).
         float2 ya[16], yb[16];
 #pragma unroll
         for (int s = 0; s < 16; ++s) {
