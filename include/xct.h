@@ -224,8 +224,8 @@ int xct_backproject_u16(const xct_geometry *g, int32_t n_slices, const void *sin
  * needs more), freed on the stream before the call returns.  Square slices of
  * 512^2 and more under a uniform half turn (N_p even), unless a multiple of
  * four, may instead be projected each from its own four turned copies, 32
- * N_x N_y bytes per slice within the same 1 GiB; small calls keep at most
- * 256 MiB of partial sums.  Under stream capture, or when such scratch cannot
+ * N_x N_y bytes per slice within the same 1 GiB; calls of few rounds of
+ * workgroups keep partial sinograms, within 1.25 GiB of the copies and them.  Under stream capture, or when such scratch cannot
  * be allocated, neither is used.
  * Deterministic (gather form, no atomics).  Errors: XCT_EINVAL for
  * non-finite alpha, XCT_ETOOBIG beyond 65535 slices or 2^31 workgroups

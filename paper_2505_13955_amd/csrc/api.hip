@@ -1224,7 +1224,7 @@ int xct_backproject_u16(const xct_geometry *g, int32_t n_slices, const void *sin
 }
 
 // Parts of a forward projection of `triples` workgroups walking `side` steps
-// each, `bytes` of sinogram.  Fewer workgroups than the device holds (four per
+// each, `bytes` of sinogram, `room` for parts of it.  Fewer workgroups than the device holds (four per
 // CU) take the time of one workgroup's walk (one 512^2 slice, 720 angles: 180
 // workgroups, 450 us), so walks are split until there are about two rounds of
 // them, down to 32 steps; then halved to 16 while one round holds them all, and
@@ -1232,10 +1232,25 @@ int xct_backproject_u16(const xct_geometry *g, int32_t n_slices, const void *sin
 // to itself.  Three 64^2 slices, 90 angles: 58 us with 32 steps, 41 with 16, 37
 // with 8; five 256^2 slices, 360 angles: 87 us in eight parts of 32 steps (768
 // workgroups), 93 in ten, 95 in sixteen.
-static int fp_parts(int64_t triples, int side, int sl, size_t bytes)
+static int fp_parts(int64_t triples, int side, int sl, size_t bytes, size_t room)
 {
     const int64_t cus = device_cus(), slots = 4 * cus;
-    if (triples >= slots) return 1;
+    if (triples >= slots) {
+        // More than one round ends with a tail of some 0.9 rounds of whole
+        // walks (1024^2, 1440 angles, 4 to 32 slices: 1.45 ms a round of 1024
+        // workgroups and 1.3 ms besides).  Parts shorten it, for some 16 steps
+        // each and the passes over their sums: 8 slices 2.88 ms whole, 2.30 in
+        // two parts, 2.08 in four; 64 slices of 512^2, 720 angles: 2.28, 2.18,
+        // 2.30; 8 of 2048^2, 1024 angles: 11.9, 9.3, 8.4.
+        double best = 0.0;
+        int parts = 1;
+        for (int64_t p = 1; p <= 4 && side / p >= 64 && (p == 1 || (size_t)p * bytes <= room); ++p) {
+            const double us = 1.41 * (side + 16.0 * p) * triples / slots + 1.27 * side / p +
+                              (p > 1 ? 15.0 + p * bytes / 2e6 : 0.0);
+            if (p == 1 || us < best) best = us, parts = (int)p;
+        }
+        return parts;
+    }
     int64_t p = std::max<int64_t>(1, std::min<int64_t>((2 * slots + triples - 1) / triples, side / 32));
     while (side / (2 * p) >= 16 && triples * 2 * p <= slots) p *= 2;
     while (sl == 4 && side / (2 * p) >= 8 && triples * 2 * p <= cus) p *= 2;
@@ -1315,19 +1330,21 @@ static int forward_form(const xct_geometry *g, int32_t n_slices, const float *im
     a.nx = g->nx;
     a.ny = g->ny;
     a.n_slices = n_slices;
+    a.parts = 1;
     const size_t sino_bytes = sizeof(float) * (size_t)n_slices * g->n_angles * g->n_det;
-    a.parts = scratch ? fp_parts(triples, std::min(g->nx, g->ny), sl, sino_bytes) : 1;
+    // Four slices per workgroup read four-slice copies of the image and of
+    // its transpose, made chunk by chunk of slice groups in stream-ordered
+    // memory (kQuadBytes, or one group when a group needs more); what is left
+    // of the memory that the pool keeps is room for parts.
+    const int64_t plane = (int64_t)g->nx * g->ny;
+    const int64_t group_bytes = sl == 4 ? 2 * plane * (int64_t)sizeof(float4) : 0;
+    const int64_t per = sl == 4 ? std::max<int64_t>(1, std::min<int64_t>(groups, kQuadBytes / group_bytes)) : groups;
+    const int64_t room = std::max<int64_t>(kPartBytes, kQuadBytes + kPartBytes - per * group_bytes);
+    if (scratch && per == groups) a.parts = fp_parts(triples, std::min(g->nx, g->ny), sl, sino_bytes, (size_t)room);
     if (sl == 1 && a.parts == 1) {
         const hipError_t e = launch_forward(a, 1, s);
         return e == hipSuccess ? XCT_OK : hip_fail(e);
     }
-    // Four slices per workgroup read four-slice copies of the image and of
-    // its transpose, made chunk by chunk of slice groups in stream-ordered
-    // memory (kQuadBytes, or one group when a group needs more).
-    const int64_t plane = (int64_t)g->nx * g->ny;
-    const int64_t group_bytes = sl == 4 ? 2 * plane * (int64_t)sizeof(float4) : 0;
-    const int64_t per = sl == 4 ? std::max<int64_t>(1, std::min<int64_t>(groups, kQuadBytes / group_bytes)) : groups;
-    if (per < groups) a.parts = 1;
     keep_stream_pool();
     char *buf = nullptr;
     const size_t part_bytes = a.parts > 1 ? align256(a.parts * sino_bytes) : 0;

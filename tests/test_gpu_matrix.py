@@ -205,6 +205,7 @@ def test_batch_of_split_and_matrix_slabs(xct, storage):
     (2, 256, 256, 90, 367, 183.0, "half"),
     (3, 200, 64, 33, 301, 150.0, "rand"),    # four-slice form, walks of different lengths
     (5, 97, 131, 60, 170, 84.5, "full"),
+    (16, 420, 400, 1500, 600, 297.7, "half"),  # more workgroups than the device holds
 ])
 def test_split_forward_projection(xct, case):
     """Calls too small to fill the device, whose walks over the image are split."""
