@@ -519,10 +519,12 @@ struct BPJob {
 #ifndef XCT_SYM_MAX_SLICES
 #define XCT_SYM_MAX_SLICES 2  // slices per work item of the symmetric kernel (1 or 2)
 #endif
-// Slices (pairs of slices) per work item of a job alone.
+// Slices (pairs of slices) per work item of a job alone; 3 where three slices
+// go as a pair and one.
 int item_slices(const BPJob &j)
 {
     if (j.path == kPathGeneric) return 1;
+    if (j.path == kPathPairs && j.n_slices == 3) return 3;
     return std::min(j.path == kPathPairs ? (j.n_slices + 1) / 2 : j.n_slices, XCT_SYM_MAX_SLICES);
 }
 
@@ -547,7 +549,7 @@ int64_t plan_tiles(const BPJob &j, int sl, int *tx, int *ty)
     if (j.path == kPathPairs) {
         *tx = (j.g->nx + kTile - 1) / kTile;
         *ty = (j.g->ny + kTile - 1) / kTile;
-        return (int64_t)*tx * *ty * ((j.n_slices + 2 * sl - 1) / (2 * sl));
+        return (int64_t)*tx * *ty * (sl == 3 ? (j.n_slices + 2) / 3 : (j.n_slices + 2 * sl - 1) / (2 * sl));
     }
     if (j.path == kPathMirror) {  // the upper ceil(N_y/2) rows
         *tx = (j.g->nx + kTile - 1) / kTile;
@@ -568,22 +570,28 @@ int64_t plan_tiles(const BPJob &j, int sl, int *tx, int *ty)
 constexpr size_t kGenericStageBytes = 32 * 1024;
 constexpr size_t kSymStageBytes = 37 * 1024;
 constexpr size_t kSym2StageBytes = XCT_SYM2_STAGE_KB * 1024;
+// (three 512-thread workgroups per CU, whose registers the mirror kernels
+// leave: three slices of 1600^2, 1500 angles 1.74 ms with two, 1.35 with three;
+// a mirror launch of more than two items per CU, 8 x 2048^2 x 1801, 5.24
+// to 5.33 and 4.90 to 5.23, while 512 items of 1001^2 take 1 to 2 % longer in shorter stages)
+constexpr size_t kMirrorStageBytes = 49 * 1024;
 constexpr int kPartStages = 1;  // LDS stages of the shortest part of a split job
 
 // Window, angles (pairs) per stage and LDS bytes of a vector kernel whose
-// widest window needs W entries, for `spi` slices per work item.
+// widest window needs W entries, for `items` items of `spi` slices.
 struct VectorShape { int win, kb; size_t lds; };
 
-VectorShape vector_shape(int path, int W, int spi)
+VectorShape vector_shape(int path, int W, int spi, int64_t items)
 {
     VectorShape v;
-    const size_t budget = spi == 2 ? kSym2StageBytes : kSymStageBytes;
+    const bool three = spi == 3 || (spi == 2 && path != kPathSymmetric && items > 2 * (int64_t)device_cus());
+    const size_t budget = three ? kMirrorStageBytes : spi == 2 ? kSym2StageBytes : kSymStageBytes;
     v.win = path == kPathGeneric ? W : bp_sym_window(W);  // choose_path only routes windows that fit here
     if (path == kPathSymmetric) {
         v.kb = (int)std::max<size_t>(1, budget / (4 * (size_t)v.win * spi * sizeof(float4) + 24));
         v.lds = bp_sym_lds_bytes(v.win, v.kb, spi);
     } else if (path == kPathMirror || path == kPathPairs) {
-        v.kb = (int)std::max<size_t>(1, budget / ((size_t)v.win * spi * sizeof(float4) + sizeof(float4)));
+        v.kb = (int)std::max<size_t>(1, budget / bp_mirror_lds_bytes(v.win, 1, spi));
         v.lds = bp_mirror_lds_bytes(v.win, v.kb, spi);
     } else {
         v.kb = (int)std::max<size_t>(1, std::min<size_t>(64, kGenericStageBytes / (8 * (size_t)v.win + 16)));
@@ -606,12 +614,14 @@ int64_t vector_items(const BPJob &j, int *spi)
 //    and 770; one slice: four, 1300 and 710.
 //  * mirror (and slices in pairs), two slices (pairs): two items, 750 (8192^2,
 //    4 slices: 140 ms) and 580; one: four, 1270 and 630.
+//  * a pair and one slice: three items, 870 and 465.
 //  * generic: four items, 580 (2048^2, 16 slices: 19.0 ms) and 485.
 struct VectorTimes { int per_cu; double full, alone; };
 
 VectorTimes vector_times(int path, int spi)
 {
     if (path == kPathGeneric) return {4, 580, 485};
+    if (spi == 3) return {3, 870, 465};
     if (path == kPathSymmetric) return spi == 2 ? VectorTimes{2, 1180, 770} : VectorTimes{4, 1300, 710};
     return spi == 2 ? VectorTimes{2, 750, 580} : VectorTimes{4, 1270, 630};
 }
@@ -654,7 +664,7 @@ void plan_parts(BPJob &j)
     int spi;
     const int64_t items = vector_items(j, &spi);
     if (j.out_u16 || items >= vector_times(j.path, spi).per_cu * (int64_t)device_cus()) return;
-    const VectorShape v = vector_shape(j.path, window_entries(j.g->pixel_size / j.g->det_pitch), spi);
+    const VectorShape v = vector_shape(j.path, window_entries(j.g->pixel_size / j.g->det_pitch), spi, items);
     const int units = j.path == kPathSymmetric ? j.g->n_angles / 2 : j.g->n_angles;
     const int64_t most = std::min<int64_t>(units / (kPartStages * v.kb), kPartBytes / image_bytes(j));
     BPJob t = j;
@@ -692,7 +702,7 @@ int launch_bp_jobs(std::vector<BPJob> jobs, int dtype, unsigned int *counters, B
     std::stable_sort(jobs.begin(), jobs.end(),
                      [](const BPJob &a, const BPJob &b) { return a.g->n_angles > b.g->n_angles; });
     // two slices (pairs) per work item when every slab has at least two
-    int spi = XCT_SYM_MAX_SLICES;
+    int spi = item_slices(jobs[0]);
     bool split = gate != nullptr;
     for (const BPJob &j : jobs) {
         spi = std::min(spi, item_slices(j));
@@ -740,7 +750,7 @@ int launch_bp_jobs(std::vector<BPJob> jobs, int dtype, unsigned int *counters, B
     b.total_items = items;
     b.counter = counters;
     b.gate = gate;
-    const VectorShape v = vector_shape(path, W, spi);
+    const VectorShape v = vector_shape(path, W, spi, items);
     W = v.win;
     b.kb = v.kb;
     const size_t lds = v.lds;
@@ -1521,7 +1531,7 @@ size_t xct_fbp_workspace_bytes(const xct_slab *slabs, int32_t n_slabs, int32_t f
 int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_t window,
                   int32_t filtered_t, void *workspace, size_t workspace_bytes, xct_stream stream)
 {
-    static_assert(7 * kXcds * sizeof(unsigned int) <= 256, "work counters exceed their region");
+    static_assert(8 * kXcds * sizeof(unsigned int) <= 256, "work counters exceed their region");
     if (int rc = check_slabs(slabs, n_slabs, true)) return rc;
     if (!dtype_ok(sino_t) || !dtype_ok(filtered_t)) return XCT_EDTYPE;
     if (window < XCT_RAM_LAK || window > XCT_HANN) return XCT_EDTYPE;
@@ -1543,7 +1553,7 @@ int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_
     // symmetric kernel, each with one slice (pair) per item or two.  A slab takes
     // the kernel variant a call with that slab alone takes, so the images
     // equal separate calls bit for bit.
-    enum { kGroupGeneric = 0, kGroupPairs1, kGroupPairs2, kGroupMirror1, kGroupMirror2, kGroupSym1, kGroupSym2, kGroups };
+    enum { kGroupGeneric = 0, kGroupPairs1, kGroupPairs2, kGroupPairs3, kGroupMirror1, kGroupMirror2, kGroupSym1, kGroupSym2, kGroups };
     std::vector<BPJob> groups[kGroups];
     // back-projection geometry of offset slabs (virtual detector); lives until
     // the launches below have read it
@@ -1570,9 +1580,9 @@ int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_
             j.partial = partial;
             partial += part_bytes(j) / sizeof(float);
         }
-        const int two = item_slices(j) == 2;
+        const int spi = item_slices(j), two = spi == 2;
         const int grp = j.path == kPathGeneric  ? kGroupGeneric
-                        : j.path == kPathPairs  ? (two ? kGroupPairs2 : kGroupPairs1)
+                        : j.path == kPathPairs  ? (spi == 3 ? kGroupPairs3 : two ? kGroupPairs2 : kGroupPairs1)
                         : j.path == kPathMirror ? (two ? kGroupMirror2 : kGroupMirror1)
                                                 : (two ? kGroupSym2 : kGroupSym1);
         groups[grp].push_back(j);

@@ -662,12 +662,16 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_sym_ker
 // so again one coordinate and one ds_read_b128 serve two updates, where the
 // generic kernel forms a coordinate and reads 8 bytes for each.  8 slices of
 // 2048^2 at 2049 angles, axis off the half bins: 9.39 ms generic, 6.04 ms.
+//
+// Three slices (THREE, SL = 2) leave the second pair's entry half empty: it
+// holds (a, d) alone, so that a pixel reads 24 bytes of LDS instead of 32.
+// Three slices of 1600^2, 1500 angles: 1.88 ms in two pairs, 1.35 so.
 size_t bp_mirror_lds_bytes(int win, int kb, int sl)
 {
-    return (size_t)kb * sizeof(float4) + (size_t)kb * win * sl * sizeof(float4);
+    return (size_t)kb * sizeof(float4) + (size_t)kb * win * (sl == 3 ? 24 : 16 * sl);
 }
 
-template <typename T, int W, int SL, bool PARTS, bool MIRROR>
+template <typename T, int W, int SL, bool PARTS, bool MIRROR, bool THREE>
 __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_mirror_kernel(BPBatch arg)
 {
     KBatch *b = kernarg_batch();
@@ -678,8 +682,9 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_mirror_
     constexpr int PX = 4096 / kThreads;  // pixels per thread
     constexpr int ROWS = PX / 4;         // lattice rows per thread
     constexpr int RS = kThreads / 16;    // lattice row stride
-    constexpr int PER = W * SL;          // float4 per angle
-    constexpr int SPI = MIRROR ? SL : 2 * SL;  // slices per item
+    constexpr int PER = THREE ? W + W / 2 : W * SL;          // float4 per angle
+    constexpr int SPI = THREE ? 3 : MIRROR ? SL : 2 * SL;  // slices per item
+    static_assert(!THREE || (SL == 2 && !MIRROR), "three slices: a pair and one");
     const int kb = b->kb;
     float4 *par = lds4;                  // (u(tile centre) - B, C, S, B as int bits)
     float4 *win = lds4 + kb;
@@ -783,7 +788,9 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_mirror_
                     if (m < W) {
                         const float f0 = v[u][0], fd = v[u][1] - f0, m0 = v[u][2], md = v[u][3] - m0;
                         const float mf = -(float)m;
-                        win[kk * PER + sidx * W + m] = make_float4(fmaf(mf, fd, f0), fd, fmaf(mf, md, m0), md);
+                        const float2 one = make_float2(fmaf(mf, fd, f0), fd);
+                        if (THREE && sidx) reinterpret_cast<float2 *>(win + kk * PER + W)[m] = one;
+                        else win[kk * PER + sidx * W + m] = make_float4(one.x, one.y, fmaf(mf, md, m0), md);
                     }
                 }
             }
@@ -803,6 +810,11 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_mirror_
                         const int pi = cc * 4 + aa;
 #pragma unroll
                         for (int s = 0; s < SL; ++s) {
+                            if (THREE && s == 1) {
+                                const float2 a = reinterpret_cast<const float2 *>(wk + W)[n];
+                                acc[s][0][pi] += fmaf(u, a.y, a.x);
+                                continue;
+                            }
                             const float4 a = wk[s * W + n];
                             acc[s][0][pi] += fmaf(u, a.y, a.x);   // Q
                             acc[s][1][pi] += fmaf(u, a.w, a.z);   // R^2 Q, or Q of the next slice
@@ -831,7 +843,7 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_mirror_
                         const int pi = cc * 4 + aa;
                         store_voxel(sl, plane + (int64_t)i * NX + j, acc[s][0][pi]);
                         if constexpr (!MIRROR) {
-                            if (2 * s + 1 < nsl) store_voxel(sl, plane + (int64_t)NX * NY + (int64_t)i * NX + j, acc[s][1][pi]);
+                            if (!(THREE && s == 1) && 2 * s + 1 < nsl) store_voxel(sl, plane + (int64_t)NX * NY + (int64_t)i * NX + j, acc[s][1][pi]);
                         } else if (2 * i + 1 < NY)
                             store_voxel(sl, plane + (int64_t)(NY - 1 - i) * NX + (NX - 1 - j), acc[s][1][pi]);
                     }
@@ -972,18 +984,18 @@ static auto with_sym(int dtype, int win, F &&f)
     return f(bp_sym_kernel<bf16_t, 192, SL, PARTS>, th);
 }
 
-template <int SL, bool PARTS, bool MIRROR, typename F>
+template <int SL, bool PARTS, bool MIRROR, bool THREE, typename F>
 static auto with_mirror(int dtype, int win, F &&f)
 {
     constexpr int th = sym_threads<SL>();
     if (win == 96) {
-        if (dtype == XCT_F32) return f(bp_mirror_kernel<float, 96, SL, PARTS, MIRROR>, th);
-        if (dtype == XCT_F16) return f(bp_mirror_kernel<f16_t, 96, SL, PARTS, MIRROR>, th);
-        return f(bp_mirror_kernel<bf16_t, 96, SL, PARTS, MIRROR>, th);
+        if (dtype == XCT_F32) return f(bp_mirror_kernel<float, 96, SL, PARTS, MIRROR, THREE>, th);
+        if (dtype == XCT_F16) return f(bp_mirror_kernel<f16_t, 96, SL, PARTS, MIRROR, THREE>, th);
+        return f(bp_mirror_kernel<bf16_t, 96, SL, PARTS, MIRROR, THREE>, th);
     }
-    if (dtype == XCT_F32) return f(bp_mirror_kernel<float, 192, SL, PARTS, MIRROR>, th);
-    if (dtype == XCT_F16) return f(bp_mirror_kernel<f16_t, 192, SL, PARTS, MIRROR>, th);
-    return f(bp_mirror_kernel<bf16_t, 192, SL, PARTS, MIRROR>, th);
+    if (dtype == XCT_F32) return f(bp_mirror_kernel<float, 192, SL, PARTS, MIRROR, THREE>, th);
+    if (dtype == XCT_F16) return f(bp_mirror_kernel<f16_t, 192, SL, PARTS, MIRROR, THREE>, th);
+    return f(bp_mirror_kernel<bf16_t, 192, SL, PARTS, MIRROR, THREE>, th);
 }
 
 template <bool PARTS, typename F>
@@ -994,8 +1006,11 @@ static auto with_kernel(int path, int dtype, int win, int sl, F &&f)
         if (dtype == XCT_F16) return f(bp_generic_kernel<f16_t, PARTS>, kBPThreads);
         return f(bp_generic_kernel<bf16_t, PARTS>, kBPThreads);
     }
-    if (path == kPathMirror) return sl == 2 ? with_mirror<2, PARTS, true>(dtype, win, f) : with_mirror<1, PARTS, true>(dtype, win, f);
-    if (path == kPathPairs) return sl == 2 ? with_mirror<2, PARTS, false>(dtype, win, f) : with_mirror<1, PARTS, false>(dtype, win, f);
+    if (path == kPathMirror) return sl == 2 ? with_mirror<2, PARTS, true, false>(dtype, win, f) : with_mirror<1, PARTS, true, false>(dtype, win, f);
+    if (path == kPathPairs) {
+        if (sl == 3) return with_mirror<2, PARTS, false, true>(dtype, win, f);
+        return sl == 2 ? with_mirror<2, PARTS, false, false>(dtype, win, f) : with_mirror<1, PARTS, false, false>(dtype, win, f);
+    }
     return sl == 2 ? with_sym<2, PARTS>(dtype, win, f) : with_sym<1, PARTS>(dtype, win, f);
 }
 
@@ -1008,7 +1023,7 @@ hipError_t launch_bp(int path, const BPBatch &b, int dtype, int sl, bool parts, 
 int bp_block_threads(int path, int sl)
 {
     if (path == kPathGeneric) return kBPThreads;
-    return sl == 2 ? sym_threads<2>() : sym_threads<1>();
+    return sl >= 2 ? sym_threads<2>() : sym_threads<1>();
 }
 
 int bp_max_blocks_per_cu(int path, int dtype, int win, int sl, bool parts, size_t lds)

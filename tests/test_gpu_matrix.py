@@ -269,6 +269,8 @@ def test_forward_projection_by_turned_copies(xct, case):
     (3, 200, 130, 200, 330, 164.7, 1.2, "half"),   # two pairs, the second half empty, split
     (5, 100, 300, 64, 430, 214.2, 1.5, "half"),    # three pairs, wide windows
     (4, 96, 96, 48, 200, 99.4, 2.0, "rand"),       # the widest windows that fit
+    (3, 100, 300, 70, 430, 214.2, 1.7, "rand"),    # a pair and one, wide windows
+    (3, 333, 190, 90, 400, 199.3, 0.9, "half"),    # ragged tiles
     (3, 60, 44, 21, 260, 129.3, 3.0, "half"),      # too wide for pairs: generic
 ])
 def test_slices_in_pairs(xct, case):
