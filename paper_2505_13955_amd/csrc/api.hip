@@ -570,10 +570,11 @@ int64_t plan_tiles(const BPJob &j, int sl, int *tx, int *ty)
 constexpr size_t kGenericStageBytes = 32 * 1024;
 constexpr size_t kSymStageBytes = 37 * 1024;
 constexpr size_t kSym2StageBytes = XCT_SYM2_STAGE_KB * 1024;
-// (three 512-thread workgroups per CU, whose registers the mirror kernels
-// leave: three slices of 1600^2, 1500 angles 1.74 ms with two, 1.35 with three;
-// a mirror launch of more than two items per CU, 8 x 2048^2 x 1801, 5.24
-// to 5.33 and 4.90 to 5.23, while 512 items of 1001^2 take 1 to 2 % longer in shorter stages)
+// (three 512-thread workgroups per CU, or six of 256, whose registers the
+// mirror kernels leave: three slices of 1600^2, 1500 angles 1.74 ms with two,
+// 1.35 with three; where there are items for them also the others: 8 x 2048^2 x
+// 1801 5.24 to 5.33 ms and 4.90 to 5.23, one slice of 3000^2, 2001 angles, 2.73
+// and 1.91, while 512 items of 1001^2 take 1 to 2 % longer in shorter stages)
 constexpr size_t kMirrorStageBytes = 49 * 1024;
 constexpr int kPartStages = 1;  // LDS stages of the shortest part of a split job
 
@@ -585,7 +586,8 @@ VectorShape vector_shape(int path, int W, int spi, int64_t items)
 {
     VectorShape v;
     const bool three = spi == 3 || (spi == 2 && path != kPathSymmetric && items > 2 * (int64_t)device_cus());
-    const size_t budget = three ? kMirrorStageBytes : spi == 2 ? kSym2StageBytes : kSymStageBytes;
+    const bool six = spi == 1 && path != kPathSymmetric && items > 4 * (int64_t)device_cus();
+    const size_t budget = three ? kMirrorStageBytes : six ? kMirrorStageBytes / 2 : spi == 2 ? kSym2StageBytes : kSymStageBytes;
     v.win = path == kPathGeneric ? W : bp_sym_window(W);  // choose_path only routes windows that fit here
     if (path == kPathSymmetric) {
         v.kb = (int)std::max<size_t>(1, budget / (4 * (size_t)v.win * spi * sizeof(float4) + 24));
@@ -594,7 +596,10 @@ VectorShape vector_shape(int path, int W, int spi, int64_t items)
         v.kb = (int)std::max<size_t>(1, budget / bp_mirror_lds_bytes(v.win, 1, spi));
         v.lds = bp_mirror_lds_bytes(v.win, v.kb, spi);
     } else {
-        v.kb = (int)std::max<size_t>(1, std::min<size_t>(64, kGenericStageBytes / (8 * (size_t)v.win + 16)));
+        // (more than four items per CU: stages that let eight workgroups share
+        // it; 8 x 2048^2 x 1025 angles 4.67 ms with the longer stages, 3.83)
+        const size_t bytes = items > 4 * (int64_t)device_cus() ? kGenericStageBytes * 3 / 5 : kGenericStageBytes;
+        v.kb = (int)std::max<size_t>(1, std::min<size_t>(64, bytes / (8 * (size_t)v.win + 16)));
         v.lds = bp_generic_lds_bytes(v.win, v.kb);
     }
     return v;
