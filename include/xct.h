@@ -178,7 +178,10 @@ int xct_preprocess_filter(const xct_geometry *g, int32_t n_rows, int32_t row_beg
  * widened exactly and everything after is FP32.  Kernel choice (results agree
  * to FP32 rounding): calls of 1.5e10 voxel updates and more with enough slices
  * run on the matrix cores, FP32 operands split into two FP16 halves each
- * (pixels up to 1.1 bins wide, finite rows; up to 1 GiB of scratch); of the
+ * (pixels up to 1.1 bins wide; finite rows in which every run of 32 samples, a
+ * slice's rows following each other, is all zero or reaches 2^-20 of the
+ * slice's largest magnitude, so that a far larger sample elsewhere takes no
+ * bits from it; up to 1 GiB of scratch); of the
  * rest, square even slices with an angle set closed under
  * quarter turns and 2c integral take the quarter-turn symmetric kernel; any
  * other slice with 2c integral the mirror kernel (pixel pairs reflected

@@ -834,7 +834,7 @@ bool reflected_set(const xct_geometry *g)
     return true;
 }
 
-size_t mx_words_bytes(int n_slices) { return align256(sizeof(uint32_t) * (size_t)(n_slices + 1)); }
+size_t mx_words_bytes(int n_slices) { return align256(sizeof(uint32_t) * (2 * (size_t)n_slices + 1)); }
 
 int mx_ops(int kind)
 {
@@ -954,7 +954,7 @@ size_t mx_scratch_bytes(const BPJob &j, const MXPlan &p)
 
 // The slices' magnitudes, then for each range of angles its split table and
 // its back-projection, and last the vector kernels, whose launch does nothing
-// unless some row element is not finite.
+// unless some row element is not finite or some slice's range too wide.
 int launch_bp_matrix(const BPJob &j, const MXPlan &p, int dtype, void *scratch, hipStream_t s)
 {
     const xct_geometry *g = j.g;

@@ -12,10 +12,11 @@
 //
 // Precision.  FP32 operands are split into two FP16 halves: samples scaled by
 // a power of two (per slice, so that its largest magnitude lies in
-// [2^14, 2^15)) as high + low with at most 2^-23 of the sample or 2^-40 of the
-// slice's largest magnitude left over, weights as a multiple of 2^-11 and a
-// remainder of at most 2^-12 held to 2^-24.  The products high high, low high
-// and high low are accumulated in FP32 (low low is below 2^-24).  Coordinates
+// [2^14, 2^15)) as high + low with at most 2^-23 of the sample or 2^-39 of the
+// slice's largest magnitude left over (kMXRange bounds the latter), weights as a
+// multiple of 2^-11 and a remainder of at most 2^-12 held to 2^-24.  The
+// products high high, low high and high low are accumulated in FP32 (low low is
+// below 2^-23 of the sample a tap).  Coordinates
 // are formed relative to an FP64 window anchor as in bp.hip, over windows half
 // as wide.  Measured against the FP64 values the images are closer than the
 // vector kernels' (white noise rows: 2e-6 against 5e-6 relative).
@@ -52,6 +53,8 @@
 // bank conflicts (half of the LDS cycles are conflicts, as only high halves are
 // read together) gained 1 to 2 % for 64 columns, less than their addressing
 // costs in the others.
+#include <type_traits>
+
 #include "xct_internal.h"
 
 namespace xct {
@@ -89,6 +92,19 @@ constexpr int mx_lds_bytes()
     const int stage = 3 * mx_buf_bytes<COLS>(), out = kOutCols * kMXTile * (kMXTile + 1) * 4;
     return stage > out ? stage : out;
 }
+
+// What the split holds: the low halves end 2^-39 below the slice's largest
+// magnitude, so a sample far smaller than that maximum keeps fewer bits than in
+// FP32.  A slab is split only where every run of kMXRun samples of a slice
+// (rows following each other) that is not all zero reaches kMXRange of the
+// slice's largest magnitude; there the halves leave 2^-19 of the run's at
+// most.  Pixels that see nothing but runs at the limit are 2.2e-6 off the FP64
+// values (2.05e-6 far from it), the vector kernels' 5.3e-6; at 2^-22 4.9e-6, at
+// 2^-24 1.8e-5.  Detector rows come nowhere near the limit: the least run of
+// noise-free phantom rows of 8192 bins is 2^-14 of the largest, of rows with
+// noise 2^-9.
+constexpr int kMXRun = 32;
+constexpr float kMXRange = 0x1p-20f;
 
 constexpr uint32_t kBeyondRow = 0x40000000u;  // past any row: the buffer unit returns zeros there
 
@@ -436,19 +452,37 @@ __global__ __launch_bounds__(kMXThreads, COLS < 64 ? 8 : 4) void bp_mfma_kernel(
     }
 }
 
-// Largest magnitude of every slice (as float bits) in amax[1 + slice], and
-// amax[0] != 0 when some element is not finite.  Bound by memory (64 x 1800 x
-// 2900 FP32: 245 us, 5.4 TB/s), and where the rows are still in cache by the
-// workgroups' atomics on a few words: 16 bytes a load where every slice is so
-// aligned (VEC), eight in flight, and 1024 workgroups (4 x 2048 x 2898: 21 us;
-// single elements and 4096 workgroups 54 us, 4096 workgroups 39).
+// Largest magnitude over groups of LANES lanes (a power of two up to 32), in
+// every lane of the group.
+template <int LANES>
+__device__ __forceinline__ uint32_t group_max(uint32_t m)
+{
+    auto dpp = [&](auto ctrl) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, decltype(ctrl)::value, 0xf, 0xf, true); };
+    if constexpr (LANES >= 2) m = max(m, dpp(std::integral_constant<int, 0xB1>()));    // lanes 1 0 3 2
+    if constexpr (LANES >= 4) m = max(m, dpp(std::integral_constant<int, 0x4E>()));    // lanes 2 3 0 1
+    if constexpr (LANES >= 8) m = max(m, dpp(std::integral_constant<int, 0x141>()));   // mirrored in 8 lanes
+    if constexpr (LANES >= 16) m = max(m, dpp(std::integral_constant<int, 0x140>()));  // mirrored in 16 lanes
+    if constexpr (LANES >= 32) m = max(m, (uint32_t)__shfl_xor((int)m, 16, 64));
+    return m;
+}
+
+// Magnitudes of every slice: the largest (as float bits) in amax[1 + z], minus
+// the least magnitude that a run of kMXRun samples reaches, of those that are
+// not all zero, in amax[1 + n_slices + z] (0: none), and amax[0] != 0 when some
+// element is not finite.  Bound by memory (64 x 1800 x 2900 FP32: 225 us, 5.9
+// TB/s), and where the rows are still in cache by the workgroups' atomics on one
+// line: 16 bytes a load where every slice is so aligned (VEC), eight in flight,
+// and few, large workgroups (4 x 2048 x 2898: 16 us with 256 workgroups of 1024
+// threads, 33 with 1024 of 256; 24 x 720 x 727: 11 us, 4.7 TB/s).
+constexpr int kMagThreads = 1024;
 template <typename T, bool VEC>
-__global__ __launch_bounds__(256) void absmax_kernel(const T *sino, int64_t per_slice, uint32_t *amax, int z0)
+__global__ __launch_bounds__(kMagThreads) void absmax_kernel(const T *sino, int64_t per_slice, uint32_t *amax, int z0, int n_slices)
 {
     const int z = z0 + blockIdx.y;
     const T *p = sino + z * per_slice;
-    const int64_t stride = (int64_t)gridDim.x * 256;
-    uint32_t m = 0;
+    const int64_t stride = (int64_t)gridDim.x * kMagThreads;
+    constexpr int kPer = VEC ? 16 / (int)sizeof(T) : 1;  // samples of a lane's load
+    uint32_t m = 0, least = 0;
     // magnitudes: of an FP16 element its bits, of the others float bits
     auto bits = [](T v) -> uint32_t {
         if constexpr (sizeof(T) == 4) return __float_as_uint(v) & 0x7fffffffu;
@@ -465,55 +499,77 @@ __global__ __launch_bounds__(256) void absmax_kernel(const T *sino, int64_t per_
         }
         return r;
     };
-    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if constexpr (VEC) {
-        const u4 *pv = reinterpret_cast<const u4 *>(p);
-        const int64_t n = per_slice / (16 / (int)sizeof(T));
-        for (; i + 7 * stride < n; i += 8 * stride) {
-            u4 v[8];
+    auto load = [&](int64_t i) {
+        if constexpr (VEC) return reinterpret_cast<const u4 *>(p)[i];
+        else return p[i];
+    };
+    auto take = [&](auto v) {
+        uint32_t r;
+        if constexpr (VEC) r = bits4(v);
+        else r = bits(v);
+        r = group_max<kMXRun / kPer>(r);
+        m = max(m, r);
+        least = max(least, 0u - r);
+    };
+    const int64_t n = per_slice / kPer;
+    int64_t i = (int64_t)blockIdx.x * kMagThreads + threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    // (whole wavefronts at a time: the runs' maxima are taken across lanes)
+    for (; i - lane < n; i += 8 * stride) {
+        decltype(load(0)) v[8];
+        if (i - lane + 63 + 7 * stride < n) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = pv[i + j * stride];
+            for (int j = 0; j < 8; ++j) v[j] = load(i + j * stride);
+        } else {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) m = max(m, bits4(v[j]));
+            for (int j = 0; j < 8; ++j) {
+                const decltype(load(0)) zero{};
+                v[j] = zero;
+                if (i + j * stride < n) v[j] = load(i + j * stride);
+            }
         }
-        for (; i < n; i += stride) m = max(m, bits4(pv[i]));
-    } else {
-        for (; i + 7 * stride < per_slice; i += 8 * stride) {
-            T v[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = p[i + j * stride];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) m = max(m, bits(v[j]));
-        }
-        for (; i < per_slice; i += stride) m = max(m, bits(p[i]));
+        for (int j = 0; j < 8; ++j) take(v[j]);
     }
-    if constexpr (__is_same(T, f16_t)) m = __float_as_uint((float)__builtin_bit_cast(f16_t, (uint16_t)m));
+    if constexpr (__is_same(T, f16_t)) {
+        m = __float_as_uint((float)__builtin_bit_cast(f16_t, (uint16_t)m));
+        least = 0u - __float_as_uint((float)__builtin_bit_cast(f16_t, (uint16_t)(0u - least)));
+    }
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
-    __shared__ uint32_t part[4];
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = m;
+    for (int off = 32; off > 0; off >>= 1) {
+        m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
+        least = max(least, (uint32_t)__shfl_xor((int)least, off, 64));
+    }
+    __shared__ uint32_t part[2][kMagThreads / 64];
+    if (lane == 0) {
+        part[0][threadIdx.x >> 6] = m;
+        part[1][threadIdx.x >> 6] = least;
+    }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        m = max(max(part[0], part[1]), max(part[2], part[3]));
-        atomicMax(amax + 1 + z, m);
-        if (m >= 0x7f800000u) atomicOr(amax, 1u);
+    if (threadIdx.x < 2) {
+        uint32_t v = 0;
+#pragma unroll
+        for (int w = 0; w < kMagThreads / 64; ++w) v = max(v, part[threadIdx.x][w]);
+        if (v) atomicMax(amax + 1 + z + threadIdx.x * n_slices, v);
+        if (threadIdx.x == 0 && v >= 0x7f800000u) atomicOr(amax, 1u);
     }
 }
 
 hipError_t launch_absmax(const void *sino, int dtype, int n_slices, int64_t per_slice, uint32_t *amax, hipStream_t s)
 {
-    hipError_t e = launch_fill_u32(amax, 1 + n_slices, 0u, s);
+    hipError_t e = launch_fill_u32(amax, 1 + 2 * (int64_t)n_slices, 0u, s);
     if (e != hipSuccess) return e;
-    // 8 loads a thread, at most 1024 workgroups over all slices (8 per slice at least)
+    // 8 loads a thread; one workgroup per CU, or two (2 per slice at least) where
+    // whole numbers per slice come close to that
     const int64_t size = dtype == XCT_F32 ? 4 : 2;
     const bool vec = (reinterpret_cast<uintptr_t>(sino) & 15) == 0 && (per_slice * size & 15) == 0;
-    const int64_t loads = vec ? per_slice * size / 16 : per_slice, want = (loads + 256 * 8 - 1) / (256 * 8);
-    const int64_t cap = n_slices < 128 ? 1024 / n_slices : 8;
+    const int64_t loads = vec ? per_slice * size / 16 : per_slice, want = (loads + kMagThreads * 8 - 1) / (kMagThreads * 8);
+    const int64_t cap = n_slices < 16 ? (256 + n_slices - 1) / n_slices : n_slices < 256 ? 512 / n_slices : 2;
     for (int z = 0; z < n_slices; z += 65535) {
         const dim3 grid((unsigned)(want < cap ? want : cap), (unsigned)(n_slices - z < 65535 ? n_slices - z : 65535));
         auto go = [&](auto *p, auto kernel, auto kernel_vec) {
-            if (vec) hipLaunchKernelGGL(kernel_vec, grid, dim3(256), 0, s, p, per_slice, amax, z);
-            else hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, p, per_slice, amax, z);
+            if (vec) hipLaunchKernelGGL(kernel_vec, grid, dim3(kMagThreads), 0, s, p, per_slice, amax, z, n_slices);
+            else hipLaunchKernelGGL(kernel, grid, dim3(kMagThreads), 0, s, p, per_slice, amax, z, n_slices);
         };
         if (dtype == XCT_F32) go((const float *)sino, absmax_kernel<float, false>, absmax_kernel<float, true>);
         else if (dtype == XCT_F16) go((const f16_t *)sino, absmax_kernel<f16_t, false>, absmax_kernel<f16_t, true>);
@@ -528,12 +584,19 @@ hipError_t launch_absmax(const void *sino, int dtype, int n_slices, int64_t per_
 // 16-byte records (four slices' high halves, then their low halves) of the
 // scaled samples.  Row l of the table is row k_first + l of the slab, plus
 // k_jump from row `split` on.  One thread per record, rows read and written
-// along bins: bound by memory (16 x 3072 x 4096: 0.37 ms, 4.4 TB/s).
+// along bins: bound by memory (16 x 3072 x 4096: 0.37 ms, 4.4 TB/s).  A slice
+// whose range is wider than the halves hold sends the slab to the vector
+// kernels: the launches behind this one see amax[0].
 template <typename T>
 __global__ __launch_bounds__(256) void split_kernel(SplitArgs a)
 {
     if (a.amax[0] != 0) return;
     const int n = blockIdx.x * 256 + threadIdx.x, g = blockIdx.z;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 4 && 4 * g + (int)threadIdx.x < a.n_slices) {
+        const uint32_t *w = a.amax + 1 + 4 * g + threadIdx.x;
+        const uint32_t least = 0u - w[a.n_slices];
+        if (least != 0 && __uint_as_float(least) < __uint_as_float(w[0]) * kMXRange) atomicOr(a.amax, 1u);
+    }
     if (n >= a.n_det) return;
     for (int l = blockIdx.y; l < a.rows; l += gridDim.y) {
         const int64_t row = a.k_first + l + (l >= a.split ? a.k_jump : 0);

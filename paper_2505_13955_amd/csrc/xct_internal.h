@@ -108,7 +108,10 @@ struct MXArgs {
     int64_t table;         // device address of the split table [S/4][n_angles][Nc]
     float *image;          // [S][Ny][Nx]
     const double2 *csd;    // [Np] (cos, sin) * pixel / pitch
-    const uint32_t *amax;  // [0]: a row element is not finite; [1 + z]: slice z's largest magnitude (float bits)
+    // [0]: a row element is not finite, or a slice's range is too wide; [1 + z]: slice
+    // z's largest magnitude (float bits); [1 + n_slices + z]: minus the least that a
+    // run of its samples reaches
+    const uint32_t *amax;
     double center;
     // angles of this launch: k_first .. , with k_jump more from the
     // half_set'th on (quarter-turn kinds: two runs a quarter turn apart)
@@ -129,7 +132,7 @@ hipError_t launch_sum_parts(float *image, const float *partial, int parts, int64
 struct SplitArgs {
     const void *sino;      // [S][n_angles][Nc]
     uint4 *table;          // [S/4][rows][Nc]
-    const uint32_t *amax;
+    uint32_t *amax;        // as MXArgs::amax; sets [0]
     int32_t n_angles, n_det, n_slices;
     int32_t rows, k_first, k_jump, split;  // table row l is angle k_first + l, plus k_jump for l >= split
 };

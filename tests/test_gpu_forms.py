@@ -1,0 +1,78 @@
+"""GPU tests of where one call takes one kernel form or another: which slabs
+the matrix cores hold, and what a form must not change for the caller."""
+
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from tests.gpu_util import rel_l2, say, to_dev
+
+pytestmark = pytest.mark.gpu
+
+# The gate of the vector kernels: coordinates below 96 or 192 bins.
+TOL = 2e-5
+
+
+@pytest.fixture(scope="module")
+def xct():
+    import paper_2505_13955_amd as pkg
+
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    pkg.load_library()
+    return pkg
+
+
+def on_matrix_cores(xct, g, S, filtered=torch.float32):
+    """Whether a call of this slab alone has a split table: the workspace behind
+    the counters, the descriptor and the rows holds the magnitudes, the table and
+    a whole number of partial images."""
+    a256 = lambda b: (b + 255) // 256 * 256
+    size = 4 if filtered == torch.float32 else 2
+    sino = torch.empty((S, g.n_angles, g.n_det), device="cuda")
+    scratch = xct.xct_fbp_workspace_bytes([(g, sino, None)], filtered) - 512 - a256(sino.numel() * size)
+    rest = scratch - a256(4 * (2 * S + 1)) - a256((S + 3) // 4 * g.n_angles * g.n_det * 16)
+    return rest >= 0 and any(rest == a256(p * 4 * S * g.nx * g.ny) for p in [0] + list(range(2, 65)))
+
+
+@pytest.mark.parametrize("case", [
+    # slices, nx, ny, angles, bins, centre
+    (61, 413, 390, 301, 600, 299.7),    # plain
+    (4, 813, 811, 602, 1160, 579.5),    # mirror with reflection
+    (4, 1030, 1030, 300, 1460, 729.5),  # quarter turn
+])
+def test_wide_range_of_magnitudes(xct, case):
+    """Samples far smaller than the slice's largest keep their bits: a disc of
+    pixels that sees nothing but columns 2^-e as large as the rest, and every
+    pixel that one huge bin's ray does not meet."""
+    S, nx, ny, na, nd, c = case
+    g = synth.Geometry(n_angles=na, n_det=nd, nx=nx, ny=ny, center=c)
+    assert on_matrix_cores(xct, g, S)
+    rng = np.random.default_rng(61)
+    q = rng.standard_normal((S, na, nd)).astype(np.float32)
+    inner = np.abs(np.arange(nd) - c) <= 70
+    x, y = np.arange(nx) - 0.5 * (nx - 1), np.arange(ny) - 0.5 * (ny - 1)
+    disc = x[None, :] ** 2 + y[:, None] ** 2 <= 67.0 ** 2
+    parts = [np.where(inner, q, 0.0), np.where(inner, 0.0, q)]
+    ref_in, ref_out = (oracle.backproject(p.astype(np.float64), g, oracle.adjoint_scale(g)) for p in parts)
+    assert np.all(ref_out[:, disc] == 0.0)
+    for e in (0, 17, 22, 40):  # 17: still within what the split holds
+        say("wide range", case, e)
+        img = xct.project_adjoint(to_dev(parts[0] * np.float32(2.0 ** -e) + parts[1]), g).cpu().numpy()
+        ref = ref_in * 2.0 ** -e + ref_out
+        for z in range(S):
+            assert rel_l2(img[z][disc], ref[z][disc]) < TOL, (e, z)
+            assert rel_l2(img[z], ref[z]) < TOL, (e, z)
+    k, n, z = na // 3, int(c) + 40, S - 1
+    hot = q.copy()
+    hot[z, k, n] = 1e10
+    say("one huge bin", case)
+    img = xct.project_adjoint(to_dev(hot), g).cpu().numpy()
+    off = np.abs(x[None, :] * math.cos(g.angles[k]) + y[:, None] * math.sin(g.angles[k]) + c - n) > 1.001
+    ref = ref_in + ref_out
+    for s in range(S):
+        at = off if s == z else np.ones_like(off)
+        assert rel_l2(img[s][at], ref[s][at]) < TOL, s
