@@ -1311,16 +1311,19 @@ static bool fp_turns(const xct_geometry *g, int n_slices)
 static int forward_form(const xct_geometry *g, int32_t n_slices, const float *image, const float *base,
                         float *sino, float alpha, int32_t accumulate, bool scratch, hipStream_t s)
 {
+    // (the whole set's plan also where the turned copies need a quarter's alone:
+    // a later call under capture takes it, and may not be its geometry's first)
     EntryRef t;
+    if (int rc = fp_tables(g, s, &t)) return rc;
     bool turned = scratch && fp_turns(g, n_slices);
     if (turned) {
         xct_geometry quarter = *g;
         quarter.n_angles = g->n_angles / 4 + 1;
-        if (int rc = fp_tables(&quarter, s, &t)) return rc;
-        turned = t->fp_four;
+        EntryRef q;
+        if (int rc = fp_tables(&quarter, s, &q)) return rc;
+        turned = q->fp_four;
+        if (turned) t = q;
     }
-    if (!turned)
-        if (int rc = fp_tables(g, s, &t)) return rc;
     FPArgs a{};
     a.turned = turned;
     a.image = image;
