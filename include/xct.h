@@ -254,7 +254,9 @@ int xct_forward_residual(const xct_geometry *g, int32_t n_slices, const float *i
  * Same kernels as xct_backproject with scale = fl32(alpha pixel^2 / pitch),
  * the matrix cores at any size that they are faster for, and the angles of a
  * call too small to fill the device split into parts whose images are added
- * up in a fixed order.  The least-squares gradient
+ * up in a fixed order (whole walks of the vector kernels under stream capture,
+ * or without memory for scratch: the same within FP32 rounding).  The
+ * least-squares gradient
  * 2 P^T (P x - y) is alpha = -2 applied to the residual y - P x. */
 int xct_project_adjoint(const xct_geometry *g, int32_t n_slices, const float *sino, float *image,
                         float alpha, int32_t accumulate, xct_stream stream);
@@ -273,7 +275,9 @@ typedef struct {
 } xct_slab;
 
 /* Bytes of device workspace xct_fbp_batch needs for these slabs when the
- * filtered rows are kept as `filtered_t` (0 on invalid arguments). */
+ * filtered rows are kept as `filtered_t` (0 on invalid arguments), on the
+ * current device: the forms chosen, and so the bytes, depend on its number of
+ * compute units. */
 size_t xct_fbp_workspace_bytes(const xct_slab *slabs, int32_t n_slabs, int32_t filtered_t);
 
 /* Filtered back-projection of a batch of slabs, possibly of different sizes
@@ -288,12 +292,15 @@ size_t xct_fbp_workspace_bytes(const xct_slab *slabs, int32_t n_slabs, int32_t f
  * walks all (slab, slice, tile) work items, most expensive slab first; the
  * work counters and the table of slab descriptors also live in the
  * workspace.  Slabs that the matrix cores are faster for are launched on their
- * own before it, and the angles of a slab too small to fill the device are
- * split into parts (work items of their own in a small batch, added up inside
- * the item in a large one).  The variant and the parts depend on the slab
- * alone, so the images equal those of separate calls bit for bit.  (A workspace
- * that covers only the counters, table and filtered rows is accepted: every
- * slab then takes the vector kernels.)  workspace: device, 256-byte aligned,
+ * own before it (their operands split as in xct_backproject).  A slab too small
+ * to fill the device has its angles split into parts, work items of their own
+ * whose images are added up in a fixed order, or takes the matrix cores, where
+ * the batch does not fill the device either; in a batch that does, it is walked
+ * whole in the one launch.  So the images of a slab equal those of a separate
+ * call bit for bit where both take the same form (always for slabs that fill
+ * the device, and in batches that do not), and within FP32 rounding otherwise.
+ * (A workspace that covers only the counters, table and filtered rows is
+ * accepted: every slab is then walked whole by the vector kernels.)  workspace: device, 256-byte aligned,
  * at least xct_fbp_workspace_bytes(); its contents are scratch, and calls
  * that share a workspace must not overlap.  1 <= n_slabs <= 65536. */
 int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_t window,

@@ -510,9 +510,9 @@ struct BPJob {
     int sets = 0;           // half-turn sets of the symmetric path
     int32_t out_u16 = 0;
     float code_a = 0.0f, code_b = 0.0f;
-    // Vector kernels: the angles (pairs) that are added up at a time, and the
-    // parts' copies of the image when each is a work item of its own.
-    int32_t parts = 1, part_len = std::numeric_limits<int32_t>::max() / 2;
+    // Vector kernels: the parts that the job's angles (pairs) are split into
+    // where there is room for the parts' copies of the image (partial).
+    int32_t parts = 1, part_len = 0;
     float *partial = nullptr;
 };
 
@@ -642,6 +642,15 @@ double vector_rounds(const VectorTimes &t, int64_t n)
     return (n / slots) * t.full + last;
 }
 
+// The share of a job's whole walks in rounds that fill the device.
+double vector_share_ns(const BPJob &j)
+{
+    int spi;
+    const int64_t items = vector_items(j, &spi);
+    const VectorTimes t = vector_times(j.path, spi);
+    return (double)items / (t.per_cu * (double)device_cus()) * t.full * j.g->n_angles;
+}
+
 size_t image_bytes(const BPJob &j) { return sizeof(float) * (size_t)j.n_slices * j.g->nx * j.g->ny; }
 
 // Adding up parts: a launch and its scratch, and the passes over the images at 4 TB/s.
@@ -661,9 +670,10 @@ double bp_vector_ns(const BPJob &j)
 // a call with fewer items than the device has slots leaves some idle and takes
 // the time of one walk (one 256^2 slice, 360 angles: four items, 194 us).  Its
 // angles are split into the parts, of kPartStages LDS stages or more, whose
-// rounds and sum take least, and the parts' images are added up.  The split
-// depends on the job alone: in a batch with enough items the same parts are
-// added up one after the other inside each item, to the same bits.
+// rounds and sum take least, each part a work item with its own copy of the
+// image, and the copies are added up.  (Parts added up inside an item, without
+// copies, cost a pass over the item's pixels each: 64 slabs of one 512^2 slice,
+// 720 angles, in one batch 2.53 ms, 1.98 in whole walks.)
 void plan_parts(BPJob &j)
 {
     int spi;
@@ -711,7 +721,7 @@ int launch_bp_jobs(std::vector<BPJob> jobs, int dtype, unsigned int *counters, B
     bool split = gate != nullptr;
     for (const BPJob &j : jobs) {
         spi = std::min(spi, item_slices(j));
-        split = split || j.parts > 1;
+        split = split || j.partial;
     }
     std::vector<BPSlab> desc(jobs.size());
     int W = 0;
@@ -740,7 +750,6 @@ int launch_bp_jobs(std::vector<BPJob> jobs, int dtype, unsigned int *counters, B
         sl.scale = j.scale;
         sl.accumulate = j.accumulate;
         sl.part_len = j.part_len;
-        sl.parts = j.parts;
         sl.partial = j.partial;
         sl.out_u16 = j.out_u16;
         sl.code_a = j.code_a;
@@ -808,6 +817,7 @@ int launch_bp_parts(BPJob j, int dtype, float *partial, hipStream_t s)
 // serves), columns per item (0: it does not), and the angles per launch.
 struct MXPlan {
     int kind = kMXPlain, cols = 0;
+    double ns = 0;     // its time, estimated
     int angles = 0;    // per launch (of one quarter turn for kMXQuarter)
     int part_len = 0;  // angles added up at a time (see MXArgs)
     int per_launch = 0;   // angles of a launch
@@ -933,7 +943,7 @@ MXPlan mx_plan(const BPJob &j, int dtype)
             mx_parts(j, p, items, dtype);
             const double ns = bp_matrix_ns(j, p, items, dtype);
             if (ns < least) {
-                least = ns;
+                least = p.ns = ns;
                 best = p;
             }
         }
@@ -1189,8 +1199,7 @@ static int backproject_one(const xct_geometry *g, int32_t n_slices, const void *
     MXPlan p;
     if (updates >= least) p = mx_plan(j, sino_t);
     // Scratch in stream-ordered memory.  A stream under capture, or no memory,
-    // takes the vector kernels, which need none (a split job's parts are then
-    // added up inside its items, to the same bits).
+    // takes whole walks of the vector kernels, which need none.
     const size_t bytes = p.cols ? mx_scratch_bytes(j, p) : part_bytes(j);
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     void *scratch = nullptr;
@@ -1496,44 +1505,68 @@ static BPJob slab_job(const xct_slab &sl, xct_geometry *virt, const void *filt)
     return j;
 }
 
-// Bytes of the workspace's base (counters, table, filtered rows) and of the
-// scratch behind it: the slabs' matrix-core launches use it in turn, then the
-// vector launch keeps its split slabs' partial images there (`spread`: their
-// parts are work items of their own, in a batch that would not fill the
-// device otherwise).
-static size_t batch_bytes(const xct_slab *slabs, int32_t n_slabs, int32_t filtered_t, size_t *scratch, bool *spread)
+// How a batch takes its slabs (in their order): each slab's job (its rows not
+// yet set) and, where it takes the matrix cores, its plan there.
+struct BatchPlan {
+    std::vector<xct_geometry> virt;  // virtual detectors of offset slabs
+    std::vector<BPJob> jobs;
+    std::vector<MXPlan> mx;
+    size_t base = 0;     // bytes of the workspace's counters, table and filtered rows
+    size_t scratch = 0;  // bytes behind it: the matrix-core launches use them in turn, then the split slabs' copies
+    bool spread = false; // the vector launch splits the slabs that ask for it
+};
+
+// A slab alone is split, or goes to the matrix cores, partly because it leaves
+// the device idle otherwise.  In a batch that is no reason where the slabs fill
+// the device together: slabs that the matrix cores are not faster for per
+// share of the device join the one vector launch when that is estimated to
+// take less than their launches in turn (64 slabs of one 512^2 slice, 720
+// angles: 2.0 ms, and 2.5 on the matrix cores; 32 of four slices 2.4 and 3.3),
+// and parts are work items of their own in a vector launch that would not fill
+// the device without them.
+static void plan_batch(const xct_slab *slabs, int32_t n_slabs, int32_t filtered_t, BatchPlan &b)
 {
-    size_t bytes = 256 + table_bytes(n_slabs), parts = 0;
-    int64_t items = 0;
-    *scratch = 0;
+    b.virt.resize(n_slabs);
+    b.jobs.resize(n_slabs);
+    b.mx.resize(n_slabs);
+    b.base = 256 + table_bytes(n_slabs);
+    double turns = 0, shares = 0, walk = 0;
+    auto joins = [&](int i) { return b.mx[i].cols && b.mx[i].ns >= vector_share_ns(b.jobs[i]); };
     for (int i = 0; i < n_slabs; ++i) {
         const xct_geometry &g = slabs[i].geom;
-        bytes += align256((size_t)slabs[i].n_slices * g.n_angles * filtered_bins(slabs[i]) *
-                          dtype_size(filtered_t));
-        xct_geometry virt;
-        BPJob j = slab_job(slabs[i], &virt, nullptr);
+        b.base += align256((size_t)slabs[i].n_slices * g.n_angles * filtered_bins(slabs[i]) * dtype_size(filtered_t));
+        BPJob &j = b.jobs[i] = slab_job(slabs[i], &b.virt[i], nullptr);
         plan_parts(j);
-        const MXPlan p = mx_plan(j, filtered_t);
-        if (p.cols) {
-            *scratch = std::max(*scratch, mx_scratch_bytes(j, p));
+        b.mx[i] = mx_plan(j, filtered_t);
+        if (!joins(i)) continue;
+        turns += b.mx[i].ns;
+        shares += vector_share_ns(j);
+        walk = std::max(walk, vector_times(j.path, item_slices(j)).full * g.n_angles);
+    }
+    // (the vector launch ends with a tail of half a walk on average)
+    const bool join = n_slabs > 1 && shares + 0.5 * walk < turns;
+    size_t parts = 0;
+    int64_t items = 0;
+    for (int i = 0; i < n_slabs; ++i) {
+        if (join && joins(i)) b.mx[i] = MXPlan();
+        if (b.mx[i].cols) {
+            b.scratch = std::max(b.scratch, mx_scratch_bytes(b.jobs[i], b.mx[i]));
         } else {
             int spi;
-            items += vector_items(j, &spi);
-            parts += part_bytes(j);
+            items += vector_items(b.jobs[i], &spi);
+            parts += part_bytes(b.jobs[i]);
         }
     }
-    *spread = items < 2 * (int64_t)device_cus() && parts <= (size_t)kPartBytes;
-    if (*spread) *scratch = std::max(*scratch, parts);
-    return bytes;
+    b.spread = items < 2 * (int64_t)device_cus() && parts <= (size_t)kPartBytes;
+    if (b.spread) b.scratch = std::max(b.scratch, parts);
 }
 
 size_t xct_fbp_workspace_bytes(const xct_slab *slabs, int32_t n_slabs, int32_t filtered_t)
 {
     if (check_slabs(slabs, n_slabs, false) || !dtype_ok(filtered_t)) return 0;
-    size_t scratch;
-    bool spread;
-    const size_t bytes = batch_bytes(slabs, n_slabs, filtered_t, &scratch, &spread);
-    return bytes + scratch;
+    BatchPlan b;
+    plan_batch(slabs, n_slabs, filtered_t, b);
+    return b.base + b.scratch;
 }
 
 int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_t window,
@@ -1543,14 +1576,12 @@ int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_
     if (int rc = check_slabs(slabs, n_slabs, true)) return rc;
     if (!dtype_ok(sino_t) || !dtype_ok(filtered_t)) return XCT_EDTYPE;
     if (window < XCT_RAM_LAK || window > XCT_HANN) return XCT_EDTYPE;
-    size_t scratch;
-    bool spread;
-    const size_t need = batch_bytes(slabs, n_slabs, filtered_t, &scratch, &spread);
-    if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < need) return XCT_EWORKSPACE;
-    // without the scratch every slab takes the vector kernels, parts inside their items
-    const bool with_scratch = workspace_bytes >= need + scratch;
-    spread = spread && with_scratch;
-    float *partial = reinterpret_cast<float *>(static_cast<char *>(workspace) + need);
+    BatchPlan b;
+    plan_batch(slabs, n_slabs, filtered_t, b);
+    if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < b.base) return XCT_EWORKSPACE;
+    // without the scratch every slab takes whole walks of the vector kernels
+    const bool with_scratch = workspace_bytes >= b.base + b.scratch;
+    float *partial = reinterpret_cast<float *>(static_cast<char *>(workspace) + b.base);
     hipStream_t s = (hipStream_t)stream;
 
     char *ws = static_cast<char *>(workspace);
@@ -1559,13 +1590,9 @@ int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_
     size_t off = 256 + table_bytes(n_slabs);
     // Launch groups: the generic kernel; slices in pairs, the mirror and the
     // symmetric kernel, each with one slice (pair) per item or two.  A slab takes
-    // the kernel variant a call with that slab alone takes, so the images
-    // equal separate calls bit for bit.
+    // the vector kernel that a call with that slab alone takes.
     enum { kGroupGeneric = 0, kGroupPairs1, kGroupPairs2, kGroupPairs3, kGroupMirror1, kGroupMirror2, kGroupSym1, kGroupSym2, kGroups };
     std::vector<BPJob> groups[kGroups];
-    // back-projection geometry of offset slabs (virtual detector); lives until
-    // the launches below have read it
-    std::vector<xct_geometry> virt(n_slabs);
     for (int i = 0; i < n_slabs; ++i) {
         const xct_slab &sl = slabs[i];
         const xct_geometry *g = &sl.geom;
@@ -1576,15 +1603,14 @@ int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_
         if (int rc = offset ? xct_filter_offset(g, sl.n_slices, sl.sino, sino_t, filt, filtered_t, window, sl.offset_overlap, stream)
                             : xct_filter(g, sl.n_slices, sl.sino, sino_t, filt, filtered_t, window, stream))
             return rc;
-        BPJob j = slab_job(sl, &virt[i], filt);
+        BPJob &j = b.jobs[i];
+        j.sino = filt;
         if (int rc = geo_tables(j.g, s, &j.t)) return rc;
-        plan_parts(j);
-        const MXPlan p = with_scratch ? mx_plan(j, filtered_t) : MXPlan();
-        if (p.cols) {
-            if (int rc = launch_bp_matrix(j, p, filtered_t, ws + need, s)) return rc;
+        if (with_scratch && b.mx[i].cols) {
+            if (int rc = launch_bp_matrix(j, b.mx[i], filtered_t, ws + b.base, s)) return rc;
             continue;
         }
-        if (spread && part_bytes(j)) {
+        if (with_scratch && b.spread && part_bytes(j)) {
             j.partial = partial;
             partial += part_bytes(j) / sizeof(float);
         }

@@ -111,7 +111,6 @@ __device__ __forceinline__ void select_slab(KBatch *b, int s, BPSlab &out)
     out.sets = d->sets;
     if constexpr (PARTS) {
         out.part_len = d->part_len;
-        out.parts = d->parts;
         out.partial = d->partial;
     }
 }
@@ -135,19 +134,22 @@ __device__ __forceinline__ void store_voxel(const BPSlab &sl, int64_t idx, float
     }
 }
 
-// Parts of a work item (see BPSlab): the item's index within its part, and the
-// parts [begin, end) it covers.  An item of one part stores to that part's copy.
+// The angles (symmetric path: pairs) [begin, end) of a work item, of `units` in
+// all, and the item's index within its part: an item of a split slab covers one
+// part and stores to that part's copy (see BPSlab).
 template <bool PARTS>
-__device__ __forceinline__ int64_t item_parts(BPSlab &sl, int64_t local, int64_t per_part, int64_t voxels, int &begin, int &end)
+__device__ __forceinline__ int64_t item_part(BPSlab &sl, int64_t local, int64_t per_part, int64_t voxels, int units, int &begin,
+                                             int &end)
 {
     begin = 0;
-    end = PARTS ? sl.parts : 1;
+    end = units;
     if (!PARTS || !sl.partial) return local;
-    begin = __builtin_amdgcn_readfirstlane((int)(local / per_part));
-    end = begin + 1;
-    sl.image = sl.partial + begin * voxels;
+    const int part = __builtin_amdgcn_readfirstlane((int)(local / per_part));
+    begin = part * sl.part_len;
+    end = min(units, begin + sl.part_len);
+    sl.image = sl.partial + part * voxels;
     sl.accumulate = 0;
-    return local - begin * per_part;
+    return local - part * per_part;
 }
 
 // Slab of a work item: the last slab whose first item is at or before it
@@ -252,9 +254,9 @@ __global__ __launch_bounds__(kBPThreads) void bp_generic_kernel(BPBatch arg)
         BPSlab sl;
         select_slab<PARTS>(b, find_slab(b, item), sl);
         const int tiles = sl.tiles_x * sl.tiles_y;
-        int part, part_end;
-        const int64_t local = item_parts<PARTS>(sl, item - sl.item_begin, (int64_t)tiles * sl.n_slices,
-                                         (int64_t)sl.n_slices * sl.nx * sl.ny, part, part_end);
+        int k_begin, k_end;
+        const int64_t local = item_part<PARTS>(sl, item - sl.item_begin, (int64_t)tiles * sl.n_slices,
+                                               (int64_t)sl.n_slices * sl.nx * sl.ny, sl.n_angles, k_begin, k_end);
         const int z = __builtin_amdgcn_readfirstlane((int)(local / tiles));
         const int t = __builtin_amdgcn_readfirstlane((int)(local - (int64_t)z * tiles));
         const int ty = t / sl.tiles_x, tx = t - ty * sl.tiles_x;
@@ -264,12 +266,10 @@ __global__ __launch_bounds__(kBPThreads) void bp_generic_kernel(BPBatch arg)
         const int Np = sl.n_angles, Nc = sl.n_det;
         const T *q = static_cast<const T *>(sl.sino) + (int64_t)z * Np * Nc;
 
-        for (; part < part_end; ++part) {
         float acc[16];
 #pragma unroll
         for (int p = 0; p < 16; ++p) acc[p] = 0.0f;
 
-        const int k_begin = PARTS ? part * sl.part_len : 0, k_end = PARTS ? min(Np, (part + 1) * sl.part_len) : Np;
         for (int k0 = k_begin; k0 < k_end; k0 += kb) {
             const int nk = min(kb, k_end - k0);
             __syncthreads();
@@ -310,20 +310,14 @@ __global__ __launch_bounds__(kBPThreads) void bp_generic_kernel(BPBatch arg)
             }
         }
 
-        // (opaque copies: the store addresses are formed here, not kept in
-        // registers through the accumulation of every part)
-        int i0s = i0, j0s = j0;
-        if constexpr (PARTS) asm volatile("" : "+s"(i0s), "+s"(j0s));
         const int64_t plane = (int64_t)z * sl.nx * sl.ny;
 #pragma unroll
         for (int bb = 0; bb < 4; ++bb) {
 #pragma unroll
             for (int aa = 0; aa < 4; ++aa) {
-                const int i = i0s + py + 16 * bb, j = j0s + px + 16 * aa;
+                const int i = i0 + py + 16 * bb, j = j0 + px + 16 * aa;
                 if (i < sl.ny && j < sl.nx) store_voxel(sl, plane + (int64_t)i * sl.nx + j, acc[bb * 4 + aa]);
             }
-        }
-        if (PARTS) sl.accumulate = 1;
         }
     }
 }
@@ -446,9 +440,9 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_sym_ker
         BPSlab sl;
         select_slab<PARTS>(b, find_slab(b, item), sl);
         const int tiles = sl.tiles_x * sl.tiles_y;
-        int part, part_end;
-        const int64_t local = item_parts<PARTS>(sl, item - sl.item_begin, (int64_t)tiles * ((sl.n_slices + SL - 1) / SL),
-                                         (int64_t)sl.n_slices * sl.nx * sl.ny, part, part_end);
+        int k_begin, k_end;
+        const int64_t local = item_part<PARTS>(sl, item - sl.item_begin, (int64_t)tiles * ((sl.n_slices + SL - 1) / SL),
+                                               (int64_t)sl.n_slices * sl.nx * sl.ny, sl.n_angles / 2, k_begin, k_end);
         // slice group and tile (the 64-bit division runs on the vector unit;
         // pin the results back to scalars)
         const int zg = __builtin_amdgcn_readfirstlane((int)(local / tiles));
@@ -471,7 +465,6 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_sym_ker
         const int64_t sl_stride = (int64_t)Np * Nc;  // elements between slices
         const int64_t h_stride = (int64_t)H * Nc;    // from row k to row k + H
 
-        for (; part < part_end; ++part) {
         float acc[SL][4][PX];
 #pragma unroll
         for (int s = 0; s < SL; ++s)
@@ -482,11 +475,10 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_sym_ker
 
         // stages of up to kb angle pairs k0 .. k0+nk-1 (with k0+H ..); kc
         // counts pairs over the sets, and a stage never crosses a set
-        const int kc_begin = PARTS ? part * sl.part_len : 0, kc_end = PARTS ? min(sl.sets * H, (part + 1) * sl.part_len) : sl.sets * H;
-        for (int kc = kc_begin, nk = 0; kc < kc_end; kc += nk) {
+        for (int kc = k_begin, nk = 0; kc < k_end; kc += nk) {
             const int set = kc / H;
             const int k0 = kc + set * H;
-            nk = min(PARTS ? min(kb, kc_end - kc) : kb, (set + 1) * H - kc);
+            nk = min(PARTS ? min(kb, k_end - kc) : kb, (set + 1) * H - kc);
             __syncthreads();
             if (tid < nk) {
                 const double2 cd = sl.csd[k0 + tid];
@@ -614,10 +606,6 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_sym_ker
             }
         }
 
-        // (opaque copies: the store addresses are formed here, not kept in
-        // registers through the accumulation of every part)
-        int i0s = i0, j0s = j0;
-        if constexpr (PARTS) asm volatile("" : "+s"(i0s), "+s"(j0s));
 #pragma unroll
         for (int s = 0; s < SL; ++s) {
             if (s >= nsl) break;
@@ -626,7 +614,7 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_sym_ker
             for (int cc = 0; cc < ROWS; ++cc) {
 #pragma unroll
                 for (int aa = 0; aa < 4; ++aa) {
-                    const int i = i0s + py + RS * cc, j = j0s + px + 16 * aa;
+                    const int i = i0 + py + RS * cc, j = j0 + px + 16 * aa;
                     if (i < half && j < half) {
                         const int pi = cc * 4 + aa;
                         // Q = (i, j); R Q = (N-1-j, i); R^2 Q = (N-1-i, N-1-j); R^3 Q = (j, N-1-i)
@@ -638,8 +626,6 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_sym_ker
                     }
                 }
             }
-        }
-        if (PARTS) sl.accumulate = 1;
         }
     }
 }
@@ -699,9 +685,9 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_mirror_
         BPSlab sl;
         select_slab<PARTS>(b, find_slab(b, item), sl);
         const int tiles = sl.tiles_x * sl.tiles_y;
-        int part, part_end;
-        const int64_t local = item_parts<PARTS>(sl, item - sl.item_begin, (int64_t)tiles * ((sl.n_slices + SPI - 1) / SPI),
-                                         (int64_t)sl.n_slices * sl.nx * sl.ny, part, part_end);
+        int k_begin, k_end;
+        const int64_t local = item_part<PARTS>(sl, item - sl.item_begin, (int64_t)tiles * ((sl.n_slices + SPI - 1) / SPI),
+                                               (int64_t)sl.n_slices * sl.nx * sl.ny, sl.n_angles, k_begin, k_end);
         const int zg = __builtin_amdgcn_readfirstlane((int)(local / tiles));
         const int t = __builtin_amdgcn_readfirstlane((int)(local - (int64_t)zg * tiles));
         int ty, tx;
@@ -717,7 +703,6 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_mirror_
             uniform64(reinterpret_cast<int64_t>(static_cast<const T *>(sl.sino) + (int64_t)z0 * Np * Nc)));
         const int64_t sl_stride = (int64_t)Np * Nc;
 
-        for (; part < part_end; ++part) {
         float acc[SL][2][PX];
 #pragma unroll
         for (int s = 0; s < SL; ++s)
@@ -726,7 +711,6 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_mirror_
 #pragma unroll
                 for (int p = 0; p < PX; ++p) acc[s][r][p] = 0.0f;
 
-        const int k_begin = PARTS ? part * sl.part_len : 0, k_end = PARTS ? min(Np, (part + 1) * sl.part_len) : Np;
         for (int k0 = k_begin, nk = 0; k0 < k_end; k0 += nk) {
             nk = min(kb, k_end - k0);
             __syncthreads();
@@ -826,10 +810,6 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_mirror_
             }
         }
 
-        // (opaque copies: the store addresses are formed here, not kept in
-        // registers through the accumulation of every part)
-        int i0s = i0, j0s = j0;
-        if constexpr (PARTS) asm volatile("" : "+s"(i0s), "+s"(j0s));
 #pragma unroll
         for (int s = 0; s < SL; ++s) {
             if ((MIRROR ? s : 2 * s) >= nsl) break;
@@ -838,7 +818,7 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_mirror_
             for (int cc = 0; cc < ROWS; ++cc) {
 #pragma unroll
                 for (int aa = 0; aa < 4; ++aa) {
-                    const int i = i0s + py + RS * cc, j = j0s + px + 16 * aa;
+                    const int i = i0 + py + RS * cc, j = j0 + px + 16 * aa;
                     if (i < HY && j < NX) {
                         const int pi = cc * 4 + aa;
                         store_voxel(sl, plane + (int64_t)i * NX + j, acc[s][0][pi]);
@@ -849,8 +829,6 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_mirror_
                     }
                 }
             }
-        }
-        if (PARTS) sl.accumulate = 1;
         }
     }
 }

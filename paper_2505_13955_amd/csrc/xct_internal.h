@@ -43,11 +43,10 @@ struct BPSlab {
     int32_t out_u16;           // store clamp(rint(fl(fl(v code_a) + code_b))) as uint16
     float code_a, code_b;
     int32_t sets;              // symmetric path: half-turn angle sets (2 for a full turn)
-    // The angles (symmetric path: angle pairs) are added up part_len at a
-    // time, each part stored or added to the image on its own: all parts in
-    // one work item, or (partial) one item per part, part slowest, into its
-    // own copy of the slab's images, [part][S][Ny][Nx].
-    int32_t part_len, parts;
+    // A split slab (partial): one work item per part of part_len angles
+    // (symmetric path: angle pairs), part slowest, into the part's own copy of
+    // the slab's images, [part][S][Ny][Nx].
+    int32_t part_len;
     float *partial;
 };
 

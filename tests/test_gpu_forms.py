@@ -121,3 +121,57 @@ def test_forward_projection_captured_after_an_eager_call(xct, case):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(p, first)
+
+
+@pytest.mark.parametrize("case", [
+    # slabs, slices, nx, ny, angles, bins: what a slab alone takes
+    (140, 1, 256, 256, 90, 367),    # parts
+    (14, 8, 400, 300, 500, 520),    # the matrix cores
+])
+def test_batch_that_fills_the_device_walks_whole(xct, case):
+    """Slabs that alone are split, or on the matrix cores, because they would
+    leave the device idle: in a batch that fills it they are walked whole by the
+    vector kernels, as xct_backproject walks them, to the bit."""
+    n, S, nx, ny, na, nd = case
+    g = synth.Geometry(n_angles=na, n_det=nd, nx=nx, ny=ny, center=(nd - 1) / 2.0)
+    p = torch.randn((n, S, na, nd), generator=torch.Generator().manual_seed(na)).cuda()
+    img = torch.empty((n, S, ny, nx), device="cuda")
+    say("full batch", case)
+    xct.xct_fbp_batch([(g, p[i], img[i]) for i in range(n)], "hann")
+    q = torch.empty_like(p[0])
+    want = torch.empty_like(img[0])
+    for i in (0, 1, n // 2, n - 1):
+        xct.xct_filter(g, p[i], q, "hann")
+        xct.xct_backproject(g, q, want, math.pi / na)
+        torch.cuda.synchronize()
+        assert torch.equal(want, img[i]), i
+        alone = xct.fbp(p[i], g, "hann")
+        assert rel_l2(alone.cpu().numpy(), img[i].cpu().double().numpy()) < TOL
+    ref = oracle.fbp(p[n - 1].double().cpu().numpy(), g, "hann")
+    assert rel_l2(img[n - 1].cpu().numpy(), ref) < TOL
+
+
+@pytest.mark.parametrize("case", [
+    # slices, side, angles, bins: what an eager call takes
+    (1, 256, 360, 367),    # parts
+    (4, 512, 720, 727),    # parts
+    (4, 813, 602, 1160),   # the matrix cores
+])
+def test_adjoint_captured_after_an_eager_call(xct, case):
+    """Under capture there is no scratch: whole walks of the vector kernels, as
+    xct_backproject takes them below its limit, to the bit."""
+    S, n, na, nd = case
+    g = synth.Geometry(n_angles=na, n_det=nd, nx=n, ny=n, center=(nd - 1) / 2.0)
+    q = torch.randn((S, na, nd), generator=torch.Generator().manual_seed(n)).cuda()
+    say("captured adjoint", case)
+    img = xct.project_adjoint(q, g)
+    graph = captured(lambda: xct.xct_project_adjoint(g, q, img))
+    want = torch.empty_like(img)
+    for k in range(3):
+        q.copy_(torch.randn(q.shape, generator=torch.Generator().manual_seed(k)))
+        eager = xct.project_adjoint(q, g)
+        graph.replay()
+        xct.xct_backproject(g, q, want, 1.0)
+        torch.cuda.synchronize()
+        assert torch.equal(img, want)
+        assert rel_l2(img.cpu().numpy(), eager.cpu().double().numpy()) < TOL
