@@ -297,8 +297,8 @@ size_t xct_fbp_workspace_bytes(const xct_slab *slabs, int32_t n_slabs, int32_t f
  * whose images are added up in a fixed order, or takes the matrix cores, where
  * the batch does not fill the device either; in a batch that does, it is walked
  * whole in the one launch.  So the images of a slab equal those of a separate
- * call bit for bit where both take the same form (always for slabs that fill
- * the device, and in batches that do not), and within FP32 rounding otherwise.
+ * call bit for bit where both take the same form, and within FP32 rounding
+ * otherwise.
  * (A workspace that covers only the counters, table and filtered rows is
  * accepted: every slab is then walked whole by the vector kernels.)  workspace: device, 256-byte aligned,
  * at least xct_fbp_workspace_bytes(); its contents are scratch, and calls

@@ -506,6 +506,7 @@ struct BPJob {
     void *image;
     float scale;
     int32_t accumulate;
+    int cus = device_cus();  // (once per job: plans weigh some hundred forms)
     int path;
     int sets = 0;           // half-turn sets of the symmetric path
     int32_t out_u16 = 0;
@@ -582,11 +583,11 @@ constexpr int kPartStages = 1;  // LDS stages of the shortest part of a split jo
 // widest window needs W entries, for `items` items of `spi` slices.
 struct VectorShape { int win, kb; size_t lds; };
 
-VectorShape vector_shape(int path, int W, int spi, int64_t items)
+VectorShape vector_shape(int path, int W, int spi, int64_t items, int cus)
 {
     VectorShape v;
-    const bool three = spi == 3 || (spi == 2 && path != kPathSymmetric && items > 2 * (int64_t)device_cus());
-    const bool six = spi == 1 && path != kPathSymmetric && items > 4 * (int64_t)device_cus();
+    const bool three = spi == 3 || (spi == 2 && path != kPathSymmetric && items > 2 * (int64_t)cus);
+    const bool six = spi == 1 && path != kPathSymmetric && items > 4 * (int64_t)cus;
     const size_t budget = three ? kMirrorStageBytes : six ? kMirrorStageBytes / 2 : spi == 2 ? kSym2StageBytes : kSymStageBytes;
     v.win = path == kPathGeneric ? W : bp_sym_window(W);  // choose_path only routes windows that fit here
     if (path == kPathSymmetric) {
@@ -598,7 +599,7 @@ VectorShape vector_shape(int path, int W, int spi, int64_t items)
     } else {
         // (more than four items per CU: stages that let eight workgroups share
         // it; 8 x 2048^2 x 1025 angles 4.67 ms with the longer stages, 3.83)
-        const size_t bytes = items > 4 * (int64_t)device_cus() ? kGenericStageBytes * 3 / 5 : kGenericStageBytes;
+        const size_t bytes = items > 4 * (int64_t)cus ? kGenericStageBytes * 3 / 5 : kGenericStageBytes;
         v.kb = (int)std::max<size_t>(1, std::min<size_t>(64, bytes / (8 * (size_t)v.win + 16)));
         v.lds = bp_generic_lds_bytes(v.win, v.kb);
     }
@@ -633,9 +634,9 @@ VectorTimes vector_times(int path, int spi)
 
 // Rounds of n items, in ns per angle (a last round fills the CUs from one
 // item each up to per_cu).
-double vector_rounds(const VectorTimes &t, int64_t n)
+double vector_rounds(const VectorTimes &t, int64_t n, int64_t cus)
 {
-    const int64_t cus = device_cus(), slots = t.per_cu * cus, rest = n % slots;
+    const int64_t slots = t.per_cu * cus, rest = n % slots;
     const double last = rest == 0      ? 0
                         : rest <= cus ? t.alone
                                       : t.alone + (t.full - t.alone) * (double)(rest - cus) / (double)(slots - cus);
@@ -648,7 +649,7 @@ double vector_share_ns(const BPJob &j)
     int spi;
     const int64_t items = vector_items(j, &spi);
     const VectorTimes t = vector_times(j.path, spi);
-    return (double)items / (t.per_cu * (double)device_cus()) * t.full * j.g->n_angles;
+    return (double)items / (t.per_cu * (double)j.cus) * t.full * j.g->n_angles;
 }
 
 size_t image_bytes(const BPJob &j) { return sizeof(float) * (size_t)j.n_slices * j.g->nx * j.g->ny; }
@@ -661,9 +662,9 @@ double bp_vector_ns(const BPJob &j)
     int spi;
     const int64_t items = vector_items(j, &spi);
     const VectorTimes t = vector_times(j.path, spi);
-    if (j.parts < 2) return vector_rounds(t, items) * j.g->n_angles;
+    if (j.parts < 2) return vector_rounds(t, items, j.cus) * j.g->n_angles;
     const double per_part = (double)j.part_len * (j.path == kPathSymmetric ? 2 : 1);
-    return vector_rounds(t, items * j.parts) * per_part + sum_ns(j, j.parts);
+    return vector_rounds(t, items * j.parts, j.cus) * per_part + sum_ns(j, j.parts);
 }
 
 // Parts of a small job's angles: a workgroup walks all angles of its tile, so
@@ -678,8 +679,8 @@ void plan_parts(BPJob &j)
 {
     int spi;
     const int64_t items = vector_items(j, &spi);
-    if (j.out_u16 || items >= vector_times(j.path, spi).per_cu * (int64_t)device_cus()) return;
-    const VectorShape v = vector_shape(j.path, window_entries(j.g->pixel_size / j.g->det_pitch), spi, items);
+    if (j.out_u16 || items >= vector_times(j.path, spi).per_cu * (int64_t)j.cus) return;
+    const VectorShape v = vector_shape(j.path, window_entries(j.g->pixel_size / j.g->det_pitch), spi, items, j.cus);
     const int units = j.path == kPathSymmetric ? j.g->n_angles / 2 : j.g->n_angles;
     const int64_t most = std::min<int64_t>(units / (kPartStages * v.kb), kPartBytes / image_bytes(j));
     BPJob t = j;
@@ -764,7 +765,7 @@ int launch_bp_jobs(std::vector<BPJob> jobs, int dtype, unsigned int *counters, B
     b.total_items = items;
     b.counter = counters;
     b.gate = gate;
-    const VectorShape v = vector_shape(path, W, spi, items);
+    const VectorShape v = vector_shape(path, W, spi, items, jobs[0].cus);
     W = v.win;
     b.kb = v.kb;
     const size_t lds = v.lds;
@@ -878,7 +879,7 @@ double bp_matrix_ns(const BPJob &j, const MXPlan &p, int64_t items, int dtype)
     const VectorTimes t = p.cols == 64   ? VectorTimes{1, 665, 665}
                           : p.cols == 32 ? VectorTimes{2, 740, 490}
                                          : VectorTimes{2, 440, 290};
-    double ns = vector_rounds(t, (p.spread ? p.parts : 1) * items) * angles;
+    double ns = vector_rounds(t, (p.spread ? p.parts : 1) * items, j.cus) * angles;
     ns += rows * (2 * dtype_size(dtype) + 4) / 4500.0 + 30000.0;
     if (p.spread) ns += sum_ns(j, p.parts);
     return ns;
@@ -1483,7 +1484,7 @@ static size_t table_bytes(int32_t n_slabs) { return align256(sizeof(BPSlab) * (s
 // Back-projection job of a batch's slab over its filtered rows `filt`: the
 // slab's geometry (`virt`: its copy with the virtual detector of an offset
 // scan) and weight.
-static BPJob slab_job(const xct_slab &sl, xct_geometry *virt, const void *filt)
+static BPJob slab_job(const xct_slab &sl, xct_geometry *virt)
 {
     BPJob j;
     j.g = &sl.geom;
@@ -1496,7 +1497,6 @@ static BPJob slab_job(const xct_slab &sl, xct_geometry *virt, const void *filt)
         weight = 2.0 * M_PI / sl.geom.n_angles;
     }
     j.n_slices = sl.n_slices;
-    j.sino = filt;
     j.image = sl.image;
     j.scale = (float)weight;
     j.accumulate = 0;
@@ -1505,14 +1505,27 @@ static BPJob slab_job(const xct_slab &sl, xct_geometry *virt, const void *filt)
     return j;
 }
 
+// Filtered rows of a slab in the workspace, and the bytes of the workspace's
+// counters, table and filtered rows.
+static size_t rows_bytes(const xct_slab &sl, int32_t filtered_t)
+{
+    return align256((size_t)sl.n_slices * sl.geom.n_angles * filtered_bins(sl) * dtype_size(filtered_t));
+}
+
+static size_t base_bytes(const xct_slab *slabs, int32_t n_slabs, int32_t filtered_t)
+{
+    size_t bytes = 256 + table_bytes(n_slabs);
+    for (int i = 0; i < n_slabs; ++i) bytes += rows_bytes(slabs[i], filtered_t);
+    return bytes;
+}
+
 // How a batch takes its slabs (in their order): each slab's job (its rows not
 // yet set) and, where it takes the matrix cores, its plan there.
 struct BatchPlan {
     std::vector<xct_geometry> virt;  // virtual detectors of offset slabs
     std::vector<BPJob> jobs;
     std::vector<MXPlan> mx;
-    size_t base = 0;     // bytes of the workspace's counters, table and filtered rows
-    size_t scratch = 0;  // bytes behind it: the matrix-core launches use them in turn, then the split slabs' copies
+    size_t scratch = 0;  // bytes behind the base: the matrix-core launches use them in turn, then the split slabs' copies
     bool spread = false; // the vector launch splits the slabs that ask for it
 };
 
@@ -1529,19 +1542,16 @@ static void plan_batch(const xct_slab *slabs, int32_t n_slabs, int32_t filtered_
     b.virt.resize(n_slabs);
     b.jobs.resize(n_slabs);
     b.mx.resize(n_slabs);
-    b.base = 256 + table_bytes(n_slabs);
     double turns = 0, shares = 0, walk = 0;
     auto joins = [&](int i) { return b.mx[i].cols && b.mx[i].ns >= vector_share_ns(b.jobs[i]); };
     for (int i = 0; i < n_slabs; ++i) {
-        const xct_geometry &g = slabs[i].geom;
-        b.base += align256((size_t)slabs[i].n_slices * g.n_angles * filtered_bins(slabs[i]) * dtype_size(filtered_t));
-        BPJob &j = b.jobs[i] = slab_job(slabs[i], &b.virt[i], nullptr);
+        BPJob &j = b.jobs[i] = slab_job(slabs[i], &b.virt[i]);
         plan_parts(j);
         b.mx[i] = mx_plan(j, filtered_t);
         if (!joins(i)) continue;
         turns += b.mx[i].ns;
         shares += vector_share_ns(j);
-        walk = std::max(walk, vector_times(j.path, item_slices(j)).full * g.n_angles);
+        walk = std::max(walk, vector_times(j.path, item_slices(j)).full * j.g->n_angles);
     }
     // (the vector launch ends with a tail of half a walk on average)
     const bool join = n_slabs > 1 && shares + 0.5 * walk < turns;
@@ -1566,7 +1576,7 @@ size_t xct_fbp_workspace_bytes(const xct_slab *slabs, int32_t n_slabs, int32_t f
     if (check_slabs(slabs, n_slabs, false) || !dtype_ok(filtered_t)) return 0;
     BatchPlan b;
     plan_batch(slabs, n_slabs, filtered_t, b);
-    return b.base + b.scratch;
+    return base_bytes(slabs, n_slabs, filtered_t) + b.scratch;
 }
 
 int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_t window,
@@ -1576,38 +1586,47 @@ int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_
     if (int rc = check_slabs(slabs, n_slabs, true)) return rc;
     if (!dtype_ok(sino_t) || !dtype_ok(filtered_t)) return XCT_EDTYPE;
     if (window < XCT_RAM_LAK || window > XCT_HANN) return XCT_EDTYPE;
-    BatchPlan b;
-    plan_batch(slabs, n_slabs, filtered_t, b);
-    if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < b.base) return XCT_EWORKSPACE;
-    // without the scratch every slab takes whole walks of the vector kernels
-    const bool with_scratch = workspace_bytes >= b.base + b.scratch;
-    float *partial = reinterpret_cast<float *>(static_cast<char *>(workspace) + b.base);
+    const size_t base = base_bytes(slabs, n_slabs, filtered_t);
+    if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < base) return XCT_EWORKSPACE;
     hipStream_t s = (hipStream_t)stream;
 
     char *ws = static_cast<char *>(workspace);
     unsigned int *counters = reinterpret_cast<unsigned int *>(ws);
     BPSlab *table = reinterpret_cast<BPSlab *>(ws + 256);
-    size_t off = 256 + table_bytes(n_slabs);
+    std::vector<char *> rows(n_slabs);  // of each slab
+    rows[0] = ws + 256 + table_bytes(n_slabs);
+    for (int i = 1; i < n_slabs; ++i) rows[i] = rows[i - 1] + rows_bytes(slabs[i - 1], filtered_t);
+    auto filter_slab = [&](int i) {
+        const xct_slab &sl = slabs[i];
+        // (an offset scan's redundancy-weighted rows are filtered on the virtual detector)
+        return sl.offset_overlap != 0.0 ? xct_filter_offset(&sl.geom, sl.n_slices, sl.sino, sino_t, rows[i], filtered_t, window, sl.offset_overlap, stream)
+                                        : xct_filter(&sl.geom, sl.n_slices, sl.sino, sino_t, rows[i], filtered_t, window, stream);
+    };
+    // The host weighs the back-projections' forms (some 3 us a slab) while
+    // filters run: the first slab's, so that a matrix-core launch of the others
+    // finds its rows in cache (three slabs of up to 4 x 2048^2: 3.57 ms, 3.60
+    // with all filters first), or of many slabs all of them.
+    const int ahead = n_slabs > 8 ? n_slabs : 1;
+    for (int i = 0; i < ahead; ++i)
+        if (int rc = filter_slab(i)) return rc;
+    BatchPlan b;
+    plan_batch(slabs, n_slabs, filtered_t, b);
+    // without the scratch every slab takes whole walks of the vector kernels
+    const bool with_scratch = workspace_bytes >= base + b.scratch;
+    float *partial = reinterpret_cast<float *>(ws + base);
     // Launch groups: the generic kernel; slices in pairs, the mirror and the
     // symmetric kernel, each with one slice (pair) per item or two.  A slab takes
     // the vector kernel that a call with that slab alone takes.
     enum { kGroupGeneric = 0, kGroupPairs1, kGroupPairs2, kGroupPairs3, kGroupMirror1, kGroupMirror2, kGroupSym1, kGroupSym2, kGroups };
     std::vector<BPJob> groups[kGroups];
     for (int i = 0; i < n_slabs; ++i) {
-        const xct_slab &sl = slabs[i];
-        const xct_geometry *g = &sl.geom;
-        void *filt = ws + off;
-        off += align256((size_t)sl.n_slices * g->n_angles * filtered_bins(sl) * dtype_size(filtered_t));
-        const bool offset = sl.offset_overlap != 0.0;
-        // (an offset scan's redundancy-weighted rows are filtered on the virtual detector)
-        if (int rc = offset ? xct_filter_offset(g, sl.n_slices, sl.sino, sino_t, filt, filtered_t, window, sl.offset_overlap, stream)
-                            : xct_filter(g, sl.n_slices, sl.sino, sino_t, filt, filtered_t, window, stream))
-            return rc;
+        if (i >= ahead)
+            if (int rc = filter_slab(i)) return rc;
         BPJob &j = b.jobs[i];
-        j.sino = filt;
+        j.sino = rows[i];
         if (int rc = geo_tables(j.g, s, &j.t)) return rc;
         if (with_scratch && b.mx[i].cols) {
-            if (int rc = launch_bp_matrix(j, b.mx[i], filtered_t, ws + b.base, s)) return rc;
+            if (int rc = launch_bp_matrix(j, b.mx[i], filtered_t, ws + base, s)) return rc;
             continue;
         }
         if (with_scratch && b.spread && part_bytes(j)) {
