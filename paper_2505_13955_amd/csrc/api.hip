@@ -719,11 +719,7 @@ int launch_bp_jobs(std::vector<BPJob> jobs, int dtype, unsigned int *counters, B
                      [](const BPJob &a, const BPJob &b) { return a.g->n_angles > b.g->n_angles; });
     // two slices (pairs) per work item when every slab has at least two
     int spi = item_slices(jobs[0]);
-    bool split = gate != nullptr;
-    for (const BPJob &j : jobs) {
-        spi = std::min(spi, item_slices(j));
-        split = split || j.partial;
-    }
+    for (const BPJob &j : jobs) spi = std::min(spi, item_slices(j));
     std::vector<BPSlab> desc(jobs.size());
     int W = 0;
     int64_t items = 0;
@@ -780,14 +776,9 @@ int launch_bp_jobs(std::vector<BPJob> jobs, int dtype, unsigned int *counters, B
         std::memcpy(b.slab, desc.data(), sizeof(BPSlab) * desc.size());
     }
     if (counters) {
-        const int per_cu = bp_max_blocks_per_cu(path, dtype, W, spi, split, lds);
-        const int grid = (int)std::min<int64_t>(items, (int64_t)per_cu * device_cus());
-        hipError_t e = launch_bp(path, b, dtype, spi, split, grid, lds, s);
-        return e == hipSuccess ? XCT_OK : hip_fail(e);
-    }
-    if (gate) {  // most often nothing to do: a grid that fills the device strides over the items
-        b.stride = (int)std::min<int64_t>(items, 2 * (int64_t)device_cus());
-        hipError_t e = launch_bp(path, b, dtype, spi, split, b.stride, lds, s);
+        const int per_cu = bp_max_blocks_per_cu(path, dtype, W, spi, lds);
+        const int grid = (int)std::min<int64_t>(items, (int64_t)per_cu * jobs[0].cus);
+        hipError_t e = launch_bp(path, b, dtype, spi, grid, lds, s);
         return e == hipSuccess ? XCT_OK : hip_fail(e);
     }
     const int64_t threads = bp_block_threads(path, spi);
@@ -796,7 +787,7 @@ int launch_bp_jobs(std::vector<BPJob> jobs, int dtype, unsigned int *counters, B
         const int64_t count = std::min(max_items, items - base);
         b.item_base = base;
         b.xcd_remap = (count % 8 == 0) ? 1 : 0;
-        hipError_t e = launch_bp(path, b, dtype, spi, split, (int)count, lds, s);
+        hipError_t e = launch_bp(path, b, dtype, spi, (int)count, lds, s);
         if (e != hipSuccess) return hip_fail(e);
     }
     return XCT_OK;
@@ -845,7 +836,7 @@ bool reflected_set(const xct_geometry *g)
     return true;
 }
 
-size_t mx_words_bytes(int n_slices) { return align256(sizeof(uint32_t) * (2 * (size_t)n_slices + 1)); }
+size_t mx_words_bytes(int n_slices) { return align256(sizeof(uint32_t) * (2 * (size_t)n_slices + 1 + kXcds)); }
 
 int mx_ops(int kind)
 {
@@ -965,7 +956,8 @@ size_t mx_scratch_bytes(const BPJob &j, const MXPlan &p)
 
 // The slices' magnitudes, then for each range of angles its split table and
 // its back-projection, and last the vector kernels, whose launch does nothing
-// unless some row element is not finite or some slice's range too wide.
+// unless some row element is not finite or some slice's range too wide (as many
+// workgroups as the device holds, so that doing nothing is short).
 int launch_bp_matrix(const BPJob &j, const MXPlan &p, int dtype, void *scratch, hipStream_t s)
 {
     const xct_geometry *g = j.g;
@@ -1018,7 +1010,7 @@ int launch_bp_matrix(const BPJob &j, const MXPlan &p, int dtype, void *scratch, 
             a.accumulate = 1;
         }
     }
-    return launch_bp_jobs({j}, dtype, nullptr, nullptr, s, amax);
+    return launch_bp_jobs({j}, dtype, amax + 1 + 2 * (size_t)j.n_slices, nullptr, s, amax);
 }
 
 }  // namespace

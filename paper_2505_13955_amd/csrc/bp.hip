@@ -85,7 +85,6 @@ __device__ __forceinline__ KSlab *slab_at(KBatch *b, int s)
     return &b->slab[s];
 }
 
-template <bool PARTS>
 __device__ __forceinline__ void select_slab(KBatch *b, int s, BPSlab &out)
 {
     KSlab *d = slab_at(b, s);
@@ -109,10 +108,8 @@ __device__ __forceinline__ void select_slab(KBatch *b, int s, BPSlab &out)
     out.code_a = d->code_a;
     out.code_b = d->code_b;
     out.sets = d->sets;
-    if constexpr (PARTS) {
-        out.part_len = d->part_len;
-        out.partial = d->partial;
-    }
+    out.part_len = d->part_len;
+    out.partial = d->partial;
 }
 
 // Store of voxel `idx` (slab-wide index) from its accumulated sum: v = scale
@@ -137,13 +134,12 @@ __device__ __forceinline__ void store_voxel(const BPSlab &sl, int64_t idx, float
 // The angles (symmetric path: pairs) [begin, end) of a work item, of `units` in
 // all, and the item's index within its part: an item of a split slab covers one
 // part and stores to that part's copy (see BPSlab).
-template <bool PARTS>
 __device__ __forceinline__ int64_t item_part(BPSlab &sl, int64_t local, int64_t per_part, int64_t voxels, int units, int &begin,
                                              int &end)
 {
     begin = 0;
     end = units;
-    if (!PARTS || !sl.partial) return local;
+    if (!sl.partial) return local;
     const int part = __builtin_amdgcn_readfirstlane((int)(local / per_part));
     begin = part * sl.part_len;
     end = min(units, begin + sl.part_len);
@@ -184,7 +180,6 @@ __device__ __forceinline__ int64_t uniform64(int64_t v)
 //    neighbouring tiles.  A workgroup whose XCD has run out takes items from
 //    the other XCDs' counters in turn.  Which XCD a workgroup runs on only
 //    affects locality: every item is taken exactly once either way.
-template <bool PARTS>
 __device__ __forceinline__ int64_t next_item(KBatch *b, int64_t *slot, int iter)
 {
     if (b->counter) {
@@ -208,7 +203,6 @@ __device__ __forceinline__ int64_t next_item(KBatch *b, int64_t *slot, int iter)
         __syncthreads();
         return it;
     }
-    if (PARTS && b->stride > 0) return (int64_t)blockIdx.x + (int64_t)iter * b->stride;
     if (iter > 0) return b->total_items;
     int64_t bid = blockIdx.x;
     if (b->xcd_remap) {
@@ -233,11 +227,11 @@ size_t bp_generic_lds_bytes(int win, int kb)
     return (size_t)kb * sizeof(float4) + (size_t)kb * win * sizeof(float2);
 }
 
-template <typename T, bool PARTS>
+template <typename T>
 __global__ __launch_bounds__(kBPThreads) void bp_generic_kernel(BPBatch arg)
 {
     KBatch *b = kernarg_batch();
-    if (PARTS && b->gate && *b->gate == 0) return;
+    if (b->gate && *b->gate == 0) return;
     extern __shared__ float4 lds4[];
     __shared__ int64_t item_slot;
     const int kb = b->kb, W = b->win;
@@ -249,13 +243,13 @@ __global__ __launch_bounds__(kBPThreads) void bp_generic_kernel(BPBatch arg)
     const float dxo = px - 31.5f, dyo = py - 31.5f;
 
     for (int iter = 0;; ++iter) {
-        const int64_t item = uniform64(next_item<PARTS>(b, &item_slot, iter));
+        const int64_t item = uniform64(next_item(b, &item_slot, iter));
         if (item >= b->total_items) break;
         BPSlab sl;
-        select_slab<PARTS>(b, find_slab(b, item), sl);
+        select_slab(b, find_slab(b, item), sl);
         const int tiles = sl.tiles_x * sl.tiles_y;
         int k_begin, k_end;
-        const int64_t local = item_part<PARTS>(sl, item - sl.item_begin, (int64_t)tiles * sl.n_slices,
+        const int64_t local = item_part(sl, item - sl.item_begin, (int64_t)tiles * sl.n_slices,
                                                (int64_t)sl.n_slices * sl.nx * sl.ny, sl.n_angles, k_begin, k_end);
         const int z = __builtin_amdgcn_readfirstlane((int)(local / tiles));
         const int t = __builtin_amdgcn_readfirstlane((int)(local - (int64_t)z * tiles));
@@ -411,11 +405,11 @@ constexpr int sym_threads() { return SL == 2 ? XCT_SYM2_THREADS : kBPThreads; }
 template <int SL>
 constexpr int sym_waves() { return SL == 2 ? XCT_SYM2_WAVES : 4; }
 
-template <typename T, int W, int SL, bool PARTS>
+template <typename T, int W, int SL>
 __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_sym_kernel(BPBatch arg)
 {
     KBatch *b = kernarg_batch();
-    if (PARTS && b->gate && *b->gate == 0) return;
+    if (b->gate && *b->gate == 0) return;
     extern __shared__ float4 lds4[];
     __shared__ int64_t item_slot;
     constexpr int kThreads = sym_threads<SL>();
@@ -435,13 +429,13 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_sym_ker
     const float dxo = px - 31.5f, dyo = py - 31.5f;
 
     for (int iter = 0;; ++iter) {
-        const int64_t item = uniform64(next_item<PARTS>(b, &item_slot, iter));
+        const int64_t item = uniform64(next_item(b, &item_slot, iter));
         if (item >= b->total_items) break;
         BPSlab sl;
-        select_slab<PARTS>(b, find_slab(b, item), sl);
+        select_slab(b, find_slab(b, item), sl);
         const int tiles = sl.tiles_x * sl.tiles_y;
         int k_begin, k_end;
-        const int64_t local = item_part<PARTS>(sl, item - sl.item_begin, (int64_t)tiles * ((sl.n_slices + SL - 1) / SL),
+        const int64_t local = item_part(sl, item - sl.item_begin, (int64_t)tiles * ((sl.n_slices + SL - 1) / SL),
                                                (int64_t)sl.n_slices * sl.nx * sl.ny, sl.n_angles / 2, k_begin, k_end);
         // slice group and tile (the 64-bit division runs on the vector unit;
         // pin the results back to scalars)
@@ -478,7 +472,7 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_sym_ker
         for (int kc = k_begin, nk = 0; kc < k_end; kc += nk) {
             const int set = kc / H;
             const int k0 = kc + set * H;
-            nk = min(PARTS ? min(kb, k_end - kc) : kb, (set + 1) * H - kc);
+            nk = min(min(kb, k_end - kc), (set + 1) * H - kc);
             __syncthreads();
             if (tid < nk) {
                 const double2 cd = sl.csd[k0 + tid];
@@ -657,11 +651,11 @@ size_t bp_mirror_lds_bytes(int win, int kb, int sl)
     return (size_t)kb * sizeof(float4) + (size_t)kb * win * (sl == 3 ? 24 : 16 * sl);
 }
 
-template <typename T, int W, int SL, bool PARTS, bool MIRROR, bool THREE>
+template <typename T, int W, int SL, bool MIRROR, bool THREE>
 __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_mirror_kernel(BPBatch arg)
 {
     KBatch *b = kernarg_batch();
-    if (PARTS && b->gate && *b->gate == 0) return;
+    if (b->gate && *b->gate == 0) return;
     extern __shared__ float4 lds4[];
     __shared__ int64_t item_slot;
     constexpr int kThreads = sym_threads<SL>();
@@ -680,13 +674,13 @@ __global__ __launch_bounds__(sym_threads<SL>(), sym_waves<SL>()) void bp_mirror_
     const float dxo = px - 31.5f, dyo = py - 31.5f;
 
     for (int iter = 0;; ++iter) {
-        const int64_t item = uniform64(next_item<PARTS>(b, &item_slot, iter));
+        const int64_t item = uniform64(next_item(b, &item_slot, iter));
         if (item >= b->total_items) break;
         BPSlab sl;
-        select_slab<PARTS>(b, find_slab(b, item), sl);
+        select_slab(b, find_slab(b, item), sl);
         const int tiles = sl.tiles_x * sl.tiles_y;
         int k_begin, k_end;
-        const int64_t local = item_part<PARTS>(sl, item - sl.item_begin, (int64_t)tiles * ((sl.n_slices + SPI - 1) / SPI),
+        const int64_t local = item_part(sl, item - sl.item_begin, (int64_t)tiles * ((sl.n_slices + SPI - 1) / SPI),
                                                (int64_t)sl.n_slices * sl.nx * sl.ny, sl.n_angles, k_begin, k_end);
         const int zg = __builtin_amdgcn_readfirstlane((int)(local / tiles));
         const int t = __builtin_amdgcn_readfirstlane((int)(local - (int64_t)zg * tiles));
@@ -945,57 +939,54 @@ int bp_sym_window(int need) { return need <= 96 ? 96 : (need <= 192 ? 192 : 0); 
 
 // The kernel instantiation for (path, filtered dtype, window, slices per
 // item) and an action on it (launch or occupancy query), given the kernel
-// and its block size.  PARTS: launches that are gated or hold split slabs (the
-// loop over parts costs the mirror kernel a quarter of its speed, so the
-// others are built without it).
-template <int SL, bool PARTS, typename F>
+// and its block size.
+template <int SL, typename F>
 static auto with_sym(int dtype, int win, F &&f)
 {
     constexpr int th = sym_threads<SL>();
     if (win == 96) {
-        if (dtype == XCT_F32) return f(bp_sym_kernel<float, 96, SL, PARTS>, th);
-        if (dtype == XCT_F16) return f(bp_sym_kernel<f16_t, 96, SL, PARTS>, th);
-        return f(bp_sym_kernel<bf16_t, 96, SL, PARTS>, th);
+        if (dtype == XCT_F32) return f(bp_sym_kernel<float, 96, SL>, th);
+        if (dtype == XCT_F16) return f(bp_sym_kernel<f16_t, 96, SL>, th);
+        return f(bp_sym_kernel<bf16_t, 96, SL>, th);
     }
-    if (dtype == XCT_F32) return f(bp_sym_kernel<float, 192, SL, PARTS>, th);
-    if (dtype == XCT_F16) return f(bp_sym_kernel<f16_t, 192, SL, PARTS>, th);
-    return f(bp_sym_kernel<bf16_t, 192, SL, PARTS>, th);
+    if (dtype == XCT_F32) return f(bp_sym_kernel<float, 192, SL>, th);
+    if (dtype == XCT_F16) return f(bp_sym_kernel<f16_t, 192, SL>, th);
+    return f(bp_sym_kernel<bf16_t, 192, SL>, th);
 }
 
-template <int SL, bool PARTS, bool MIRROR, bool THREE, typename F>
+template <int SL, bool MIRROR, bool THREE, typename F>
 static auto with_mirror(int dtype, int win, F &&f)
 {
     constexpr int th = sym_threads<SL>();
     if (win == 96) {
-        if (dtype == XCT_F32) return f(bp_mirror_kernel<float, 96, SL, PARTS, MIRROR, THREE>, th);
-        if (dtype == XCT_F16) return f(bp_mirror_kernel<f16_t, 96, SL, PARTS, MIRROR, THREE>, th);
-        return f(bp_mirror_kernel<bf16_t, 96, SL, PARTS, MIRROR, THREE>, th);
+        if (dtype == XCT_F32) return f(bp_mirror_kernel<float, 96, SL, MIRROR, THREE>, th);
+        if (dtype == XCT_F16) return f(bp_mirror_kernel<f16_t, 96, SL, MIRROR, THREE>, th);
+        return f(bp_mirror_kernel<bf16_t, 96, SL, MIRROR, THREE>, th);
     }
-    if (dtype == XCT_F32) return f(bp_mirror_kernel<float, 192, SL, PARTS, MIRROR, THREE>, th);
-    if (dtype == XCT_F16) return f(bp_mirror_kernel<f16_t, 192, SL, PARTS, MIRROR, THREE>, th);
-    return f(bp_mirror_kernel<bf16_t, 192, SL, PARTS, MIRROR, THREE>, th);
+    if (dtype == XCT_F32) return f(bp_mirror_kernel<float, 192, SL, MIRROR, THREE>, th);
+    if (dtype == XCT_F16) return f(bp_mirror_kernel<f16_t, 192, SL, MIRROR, THREE>, th);
+    return f(bp_mirror_kernel<bf16_t, 192, SL, MIRROR, THREE>, th);
 }
 
-template <bool PARTS, typename F>
+template <typename F>
 static auto with_kernel(int path, int dtype, int win, int sl, F &&f)
 {
     if (path == kPathGeneric) {
-        if (dtype == XCT_F32) return f(bp_generic_kernel<float, PARTS>, kBPThreads);
-        if (dtype == XCT_F16) return f(bp_generic_kernel<f16_t, PARTS>, kBPThreads);
-        return f(bp_generic_kernel<bf16_t, PARTS>, kBPThreads);
+        if (dtype == XCT_F32) return f(bp_generic_kernel<float>, kBPThreads);
+        if (dtype == XCT_F16) return f(bp_generic_kernel<f16_t>, kBPThreads);
+        return f(bp_generic_kernel<bf16_t>, kBPThreads);
     }
-    if (path == kPathMirror) return sl == 2 ? with_mirror<2, PARTS, true, false>(dtype, win, f) : with_mirror<1, PARTS, true, false>(dtype, win, f);
+    if (path == kPathMirror) return sl == 2 ? with_mirror<2, true, false>(dtype, win, f) : with_mirror<1, true, false>(dtype, win, f);
     if (path == kPathPairs) {
-        if (sl == 3) return with_mirror<2, PARTS, false, true>(dtype, win, f);
-        return sl == 2 ? with_mirror<2, PARTS, false, false>(dtype, win, f) : with_mirror<1, PARTS, false, false>(dtype, win, f);
+        if (sl == 3) return with_mirror<2, false, true>(dtype, win, f);
+        return sl == 2 ? with_mirror<2, false, false>(dtype, win, f) : with_mirror<1, false, false>(dtype, win, f);
     }
-    return sl == 2 ? with_sym<2, PARTS>(dtype, win, f) : with_sym<1, PARTS>(dtype, win, f);
+    return sl == 2 ? with_sym<2>(dtype, win, f) : with_sym<1>(dtype, win, f);
 }
 
-hipError_t launch_bp(int path, const BPBatch &b, int dtype, int sl, bool parts, int grid, size_t lds, hipStream_t s)
+hipError_t launch_bp(int path, const BPBatch &b, int dtype, int sl, int grid, size_t lds, hipStream_t s)
 {
-    auto go = [&](auto k, int threads) { return launch(k, threads, b, grid, lds, s); };
-    return parts ? with_kernel<true>(path, dtype, b.win, sl, go) : with_kernel<false>(path, dtype, b.win, sl, go);
+    return with_kernel(path, dtype, b.win, sl, [&](auto k, int threads) { return launch(k, threads, b, grid, lds, s); });
 }
 
 int bp_block_threads(int path, int sl)
@@ -1004,10 +995,9 @@ int bp_block_threads(int path, int sl)
     return sl >= 2 ? sym_threads<2>() : sym_threads<1>();
 }
 
-int bp_max_blocks_per_cu(int path, int dtype, int win, int sl, bool parts, size_t lds)
+int bp_max_blocks_per_cu(int path, int dtype, int win, int sl, size_t lds)
 {
-    auto query = [&](auto k, int threads) { return occupancy(k, threads, lds); };
-    return parts ? with_kernel<true>(path, dtype, win, sl, query) : with_kernel<false>(path, dtype, win, sl, query);
+    return with_kernel(path, dtype, win, sl, [&](auto k, int threads) { return occupancy(k, threads, lds); });
 }
 
 }  // namespace xct

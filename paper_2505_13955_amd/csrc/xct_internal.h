@@ -66,7 +66,6 @@ struct BPBatch {
     int32_t kb;             // angles (generic) / angle pairs (symmetric) per LDS stage
     int32_t xcd_remap;      // map consecutive items to one XCD (non-persistent launches)
     const uint32_t *gate;   // the launch does nothing if *gate is 0 (nullptr: it always runs)
-    int32_t stride;         // > 0: workgroup b takes items b, b + stride, ... (gated launches)
 };
 
 // Accelerator complex dies of an MI355X: workgroups are dispatched to them
@@ -89,13 +88,12 @@ enum { kPathGeneric = 0, kPathSymmetric = 1, kPathMirror = 2, kPathPairs = 3 };
 
 // Launch (returns hipError_t of the launch) and sizing helpers.
 // `sl`: slices per work item of the symmetric kernel (1 or 2).
-// `parts`: some slab of the launch is split, or the launch is gated.
-hipError_t launch_bp(int path, const BPBatch &b, int dtype, int sl, bool parts, int grid, size_t lds, hipStream_t s);
+hipError_t launch_bp(int path, const BPBatch &b, int dtype, int sl, int grid, size_t lds, hipStream_t s);
 size_t bp_generic_lds_bytes(int win, int kb);
 size_t bp_sym_lds_bytes(int win, int kb, int sl);
 size_t bp_mirror_lds_bytes(int win, int kb, int sl);
 int bp_sym_window(int need);  // window of the symmetric kernel covering `need` (0: none)
-int bp_max_blocks_per_cu(int path, int dtype, int win, int sl, bool parts, size_t lds);
+int bp_max_blocks_per_cu(int path, int dtype, int win, int sl, size_t lds);
 int bp_block_threads(int path, int sl);  // threads per workgroup of the kernel
 
 // Matrix-core back-projection (bp_mfma.hip): what a pixel's coordinate serves.
@@ -109,7 +107,7 @@ struct MXArgs {
     const double2 *csd;    // [Np] (cos, sin) * pixel / pitch
     // [0]: a row element is not finite, or a slice's range is too wide; [1 + z]: slice
     // z's largest magnitude (float bits); [1 + n_slices + z]: minus the least that a
-    // run of its samples reaches
+    // run of its samples reaches; then kXcds zeros (counters of the gated launch)
     const uint32_t *amax;
     double center;
     // angles of this launch: k_first .. , with k_jump more from the
