@@ -529,6 +529,19 @@ int item_slices(const BPJob &j)
     return std::min(j.path == kPathPairs ? (j.n_slices + 1) / 2 : j.n_slices, XCT_SYM_MAX_SLICES);
 }
 
+// Work items by which the entry points limit a call (kMaxItems to a launch):
+// those of the path that the geometry gives, one generic item per slice and
+// tile also where slices go in pairs or the matrix cores take the slab.
+constexpr int64_t kMaxItems = (int64_t)1 << 31;
+int64_t plan_tiles(const BPJob &j, int sl, int *tx, int *ty);
+
+int64_t limit_items(BPJob j)
+{
+    if (j.path == kPathPairs) j.path = kPathGeneric;
+    int tx, ty;
+    return plan_tiles(j, item_slices(j), &tx, &ty);
+}
+
 // Slices of any geometry go two at a time where the call may round otherwise
 // than xct_backproject_u16 does (which keeps the generic kernel's bits) and
 // the windows fit.
@@ -550,16 +563,17 @@ int64_t plan_tiles(const BPJob &j, int sl, int *tx, int *ty)
     if (j.path == kPathPairs) {
         *tx = (j.g->nx + kTile - 1) / kTile;
         *ty = (j.g->ny + kTile - 1) / kTile;
-        return (int64_t)*tx * *ty * (sl == 3 ? (j.n_slices + 2) / 3 : (j.n_slices + 2 * sl - 1) / (2 * sl));
+        const int64_t spi = sl == 3 ? 3 : 2 * sl;  // slices per item
+        return (int64_t)*tx * *ty * ((j.n_slices + spi - 1) / spi);
     }
     if (j.path == kPathMirror) {  // the upper ceil(N_y/2) rows
         *tx = (j.g->nx + kTile - 1) / kTile;
         *ty = ((j.g->ny + 1) / 2 + kTile - 1) / kTile;
-        return (int64_t)*tx * *ty * ((j.n_slices + sl - 1) / sl);
+        return (int64_t)*tx * *ty * (((int64_t)j.n_slices + sl - 1) / sl);
     }
     const int q = (j.g->nx / 2 + kTile - 1) / kTile;  // tiles along a quadrant edge
     *tx = *ty = q;
-    return (int64_t)q * q * ((j.n_slices + sl - 1) / sl);
+    return (int64_t)q * q * (((int64_t)j.n_slices + sl - 1) / sl);
 }
 
 // LDS bytes of one angle stage: the symmetric kernel takes 6 angle pairs of
@@ -754,7 +768,7 @@ int launch_bp_jobs(std::vector<BPJob> jobs, int dtype, unsigned int *counters, B
         items += j.partial ? n_items * j.parts : n_items;
         W = std::max(W, window_entries(j.g->pixel_size / j.g->det_pitch));
     }
-    if (items >= (int64_t)1 << 31) return XCT_ETOOBIG;
+    if (items >= kMaxItems) return XCT_ETOOBIG;
     BPBatch b;
     std::memset(&b, 0, sizeof(b));
     b.n_slabs = (int32_t)jobs.size();
@@ -1185,6 +1199,7 @@ static int backproject_one(const xct_geometry *g, int32_t n_slices, const void *
     j.out_u16 = out_u16;
     j.code_a = code_a;
     j.code_b = code_b;
+    if (limit_items(j) >= kMaxItems) return XCT_ETOOBIG;
     if (int rc = geo_tables(g, s, &j.t)) return rc;
     const double updates = (double)n_slices * g->n_angles * g->nx * g->ny;
     if (updates >= least) pair_slices(j);
@@ -1521,6 +1536,24 @@ struct BatchPlan {
     bool spread = false; // the vector launch splits the slabs that ask for it
 };
 
+static void batch_jobs(const xct_slab *slabs, int32_t n_slabs, BatchPlan &b)
+{
+    b.virt.resize(n_slabs);
+    b.jobs.reserve(n_slabs);
+    for (int i = 0; i < n_slabs; ++i) b.jobs.push_back(slab_job(slabs[i], &b.virt[i]));
+}
+
+// The limit on the items of a launch, for each kernel's slabs together (one
+// slice per item apart from two).
+static int check_batch_items(const BatchPlan &b)
+{
+    int64_t items[4][2] = {};
+    for (const BPJob &j : b.jobs)
+        if ((items[j.path == kPathPairs ? (int)kPathGeneric : j.path][j.path != kPathPairs && item_slices(j) == 2] += limit_items(j)) >= kMaxItems)
+            return XCT_ETOOBIG;
+    return XCT_OK;
+}
+
 // A slab alone is split, or goes to the matrix cores, partly because it leaves
 // the device idle otherwise.  In a batch that is no reason where the slabs fill
 // the device together: slabs that the matrix cores are not faster for per
@@ -1529,15 +1562,13 @@ struct BatchPlan {
 // angles: 2.0 ms, and 2.5 on the matrix cores; 32 of four slices 2.4 and 3.3),
 // and parts are work items of their own in a vector launch that would not fill
 // the device without them.
-static void plan_batch(const xct_slab *slabs, int32_t n_slabs, int32_t filtered_t, BatchPlan &b)
+static void plan_batch(int32_t n_slabs, int32_t filtered_t, BatchPlan &b)
 {
-    b.virt.resize(n_slabs);
-    b.jobs.resize(n_slabs);
     b.mx.resize(n_slabs);
     double turns = 0, shares = 0, walk = 0;
     auto joins = [&](int i) { return b.mx[i].cols && b.mx[i].ns >= vector_share_ns(b.jobs[i]); };
     for (int i = 0; i < n_slabs; ++i) {
-        BPJob &j = b.jobs[i] = slab_job(slabs[i], &b.virt[i]);
+        BPJob &j = b.jobs[i];
         plan_parts(j);
         b.mx[i] = mx_plan(j, filtered_t);
         if (!joins(i)) continue;
@@ -1567,7 +1598,8 @@ size_t xct_fbp_workspace_bytes(const xct_slab *slabs, int32_t n_slabs, int32_t f
 {
     if (check_slabs(slabs, n_slabs, false) || !dtype_ok(filtered_t)) return 0;
     BatchPlan b;
-    plan_batch(slabs, n_slabs, filtered_t, b);
+    batch_jobs(slabs, n_slabs, b);
+    plan_batch(n_slabs, filtered_t, b);
     return base_bytes(slabs, n_slabs, filtered_t) + b.scratch;
 }
 
@@ -1580,6 +1612,9 @@ int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_
     if (window < XCT_RAM_LAK || window > XCT_HANN) return XCT_EDTYPE;
     const size_t base = base_bytes(slabs, n_slabs, filtered_t);
     if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < base) return XCT_EWORKSPACE;
+    BatchPlan b;
+    batch_jobs(slabs, n_slabs, b);
+    if (int rc = check_batch_items(b)) return rc;
     hipStream_t s = (hipStream_t)stream;
 
     char *ws = static_cast<char *>(workspace);
@@ -1601,8 +1636,7 @@ int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_
     const int ahead = n_slabs > 8 ? n_slabs : 1;
     for (int i = 0; i < ahead; ++i)
         if (int rc = filter_slab(i)) return rc;
-    BatchPlan b;
-    plan_batch(slabs, n_slabs, filtered_t, b);
+    plan_batch(n_slabs, filtered_t, b);
     // without the scratch every slab takes whole walks of the vector kernels
     const bool with_scratch = workspace_bytes >= base + b.scratch;
     float *partial = reinterpret_cast<float *>(ws + base);
