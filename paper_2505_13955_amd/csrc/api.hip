@@ -993,8 +993,8 @@ int launch_bp_matrix(const BPJob &j, const MXPlan &p, int dtype, void *scratch, 
     a.scale = j.scale;
     a.accumulate = j.accumulate;
     a.part_len = p.part_len;
-    float *partial = reinterpret_cast<float *>(static_cast<char *>(scratch) + mx_scratch_bytes(j, p) - align256(p.parts * image_bytes(j)));
-    a.partial = p.spread ? partial : nullptr;
+    if (p.spread)  // the parts' images end the scratch
+        a.partial = reinterpret_cast<float *>(static_cast<char *>(scratch) + mx_scratch_bytes(j, p) - align256(p.parts * image_bytes(j)));
     const int64_t items = mx_items(j, p.kind, p.cols, &a.tiles_x, &a.tiles_y);
     const int sets = p.kind == kMXQuarter ? j.sets : 1;
     const int h = g->n_angles / sets / 2;                       // quarter turn
@@ -1019,7 +1019,7 @@ int launch_bp_matrix(const BPJob &j, const MXPlan &p, int dtype, void *scratch, 
             const int parts = (a.n_angles + a.part_len - 1) / a.part_len;
             if (e == hipSuccess) e = launch_bp_mfma(a, p.cols, p.kind, (int)(p.spread ? items * parts : items), s);
             if (e == hipSuccess && p.spread)
-                e = launch_sum_parts(a.image, partial, parts, (int64_t)j.n_slices * g->nx * g->ny, a.accumulate, amax, s);
+                e = launch_sum_parts(a.image, a.partial, parts, (int64_t)j.n_slices * g->nx * g->ny, a.accumulate, amax, s);
             if (e != hipSuccess) return hip_fail(e);
             a.accumulate = 1;
         }
