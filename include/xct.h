@@ -40,11 +40,15 @@
  * device synchronisation.  xct_cache_clear() frees them all.  The library
  * allocates nothing else but stream-ordered scratch (hipMallocAsync) in
  * xct_backproject, xct_project_adjoint, xct_forward_project and
- * xct_forward_residual, freed on the stream before the call returns; the first
- * such call on a device sets that device's default memory pool to keep up to
- * 1.25 GiB of freed memory between calls.  xct_backproject and
- * xct_project_adjoint on a stream under capture, or without memory for it,
- * take kernels that need none.
+ * xct_forward_residual (up to 1.25 GiB, and 8 bytes a slice), freed on the
+ * stream before the call returns; the first such call on a device raises the
+ * release threshold of that device's default memory pool, where it is lower,
+ * so that it keeps up to 1.25 GiB of freed memory between calls, which
+ * xct_cache_clear() gives back.  Back-projections on a stream under capture, or
+ * without memory for scratch, take kernels that need none: vector kernels in
+ * whole walks, whose sums are rounded otherwise.  Which kernels a call takes
+ * also depends on its number of slices and on the device's compute units, so
+ * one slice's image may differ by FP32 rounding with the slices beside it.
  *
  * Errors: every argument is validated before any HIP call and nothing is
  * written when a call returns an error.  Return value 0 = XCT_OK, otherwise a
@@ -181,7 +185,7 @@ int xct_preprocess_filter(const xct_geometry *g, int32_t n_rows, int32_t row_beg
  * (pixels up to 1.1 bins wide; finite rows in which every run of 32 samples, a
  * slice's rows following each other, is all zero or reaches 2^-20 of the
  * slice's largest magnitude, so that a far larger sample elsewhere takes no
- * bits from it; up to 1 GiB of scratch); of the
+ * bits from it; up to 1.25 GiB of scratch); of the
  * rest, square even slices with an angle set closed under
  * quarter turns and 2c integral take the quarter-turn symmetric kernel; any
  * other slice with 2c integral the mirror kernel (pixel pairs reflected
@@ -338,7 +342,8 @@ const char *xct_status_string(int status);
 int xct_version(void);
 /* hipError_t of the most recent XCT_EHIP on the calling thread (0 if none). */
 int xct_last_hip_error(void);
-/* Frees the cached per-geometry device tables (call with no work in flight). */
+/* Frees the cached per-geometry device tables, and the scratch that the default
+ * memory pools keep for this library (call with no work in flight). */
 void xct_cache_clear(void);
 
 #ifdef __cplusplus

@@ -33,19 +33,33 @@ int hip_fail(hipError_t e)
 constexpr int64_t kQuadBytes = (int64_t)1 << 30;
 constexpr int64_t kPartBytes = (int64_t)1 << 28;
 
+std::mutex g_pool_mu;
+std::vector<int> g_pool_seen, g_pool_raised;  // devices
+
+// Raises the current device's default pool to that, once; a larger threshold
+// of the caller's stays.
 void keep_stream_pool()
 {
-    static std::mutex m;
-    static std::vector<int> done;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return;
-    std::lock_guard<std::mutex> lock(m);
-    if (std::find(done.begin(), done.end(), dev) != done.end()) return;
-    done.push_back(dev);
+    std::lock_guard<std::mutex> lock(g_pool_mu);
+    if (std::find(g_pool_seen.begin(), g_pool_seen.end(), dev) != g_pool_seen.end()) return;
+    g_pool_seen.push_back(dev);
     hipMemPool_t pool;
+    uint64_t held = 0, keep = (uint64_t)(kQuadBytes + kPartBytes);
     if (hipDeviceGetDefaultMemPool(&pool, dev) != hipSuccess) return;
-    uint64_t keep = (uint64_t)(kQuadBytes + kPartBytes);
-    (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep);
+    if (hipMemPoolGetAttribute(pool, hipMemPoolAttrReleaseThreshold, &held) != hipSuccess || held >= keep) return;
+    if (hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep) == hipSuccess) g_pool_raised.push_back(dev);
+}
+
+// Gives back what those pools hold without use.
+void trim_stream_pools()
+{
+    std::lock_guard<std::mutex> lock(g_pool_mu);
+    for (int dev : g_pool_raised) {
+        hipMemPool_t pool;
+        if (hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess) (void)hipMemPoolTrimTo(pool, 0);
+    }
 }
 
 bool dtype_ok(int t) { return t == XCT_F32 || t == XCT_F16 || t == XCT_BF16; }
@@ -1056,6 +1070,7 @@ void xct_cache_clear(void)
     for (auto &kv : g_cache) entry_release(*kv.second);
     g_cache.clear();
     g_cache_bytes = 0;
+    trim_stream_pools();
 }
 
 int xct_filter(const xct_geometry *g, int32_t n_slices, const void *sino, int32_t sino_t,
