@@ -26,16 +26,42 @@ def xct():
     return pkg
 
 
-def on_matrix_cores(xct, g, S, filtered=torch.float32):
-    """Whether a call of this slab alone has a split table: the workspace behind
-    the counters, the descriptor and the rows holds the magnitudes, the table and
-    a whole number of partial images."""
+def on_matrix_cores(xct, g, S, filtered=torch.float32, rows=None):
+    """Partial images of a call of this slab alone on the matrix cores (0 or 2 to
+    64), None if it is not there: the workspace behind the counters, the
+    descriptor and the rows holds the magnitudes, the split table (of `rows`
+    angles where it does not hold all) and that many images."""
     a256 = lambda b: (b + 255) // 256 * 256
     size = 4 if filtered == torch.float32 else 2
     sino = torch.empty((S, g.n_angles, g.n_det), device="cuda")
     scratch = xct.xct_fbp_workspace_bytes([(g, sino, None)], filtered) - 512 - a256(sino.numel() * size)
-    rest = scratch - a256(4 * (2 * S + 9)) - a256((S + 3) // 4 * g.n_angles * g.n_det * 16)
-    return rest >= 0 and any(rest == a256(p * 4 * S * g.nx * g.ny) for p in [0] + list(range(2, 65)))
+    rest = scratch - a256(4 * (2 * S + 9)) - a256((S + 3) // 4 * (rows or g.n_angles) * g.n_det * 16)
+    fit = [p for p in [0] + list(range(2, 65)) if rest == a256(p * 4 * S * g.nx * g.ny)]
+    return fit[0] if fit else None
+
+
+def sampled(q, g, pixels, scale):
+    """FP64 back-projection of the rows q (S, N_p, N_c) at pixels (n, 2) of every slice."""
+    x = (pixels[:, 1].double() - 0.5 * (g.nx - 1)) * g.pixel_size
+    y = (pixels[:, 0].double() - 0.5 * (g.ny - 1)) * g.pixel_size
+    out = torch.zeros((q.shape[0], len(pixels)), dtype=torch.float64, device=q.device)
+    th = torch.as_tensor(np.asarray(g.angles), device=q.device)
+    for k in range(0, g.n_angles, 1024):
+        t = th[k:k + 1024, None]
+        u = (x * torch.cos(t) + y * torch.sin(t)) / g.det_pitch + g.center
+        n = torch.floor(u)
+        f, n = u - n, n.long()
+        for z in range(q.shape[0]):
+            for bin_, w in ((n, 1.0 - f), (n + 1, f)):
+                inside = (bin_ >= 0) & (bin_ < g.n_det)
+                v = torch.gather(q[z, k:k + 1024].double(), 1, bin_.clamp(0, g.n_det - 1))
+                out[z] += torch.where(inside, v * w, 0.0).sum(0)
+    return out * scale
+
+
+def random_pixels(g, n, seed):
+    gen = torch.Generator().manual_seed(seed)
+    return torch.stack([torch.randint(g.ny, (n,), generator=gen), torch.randint(g.nx, (n,), generator=gen)], 1).cuda()
 
 
 @pytest.mark.parametrize("case", [
@@ -50,7 +76,7 @@ def test_wide_range_of_magnitudes(xct, case):
     pixel that one huge bin's ray does not meet."""
     S, nx, ny, na, nd, c = case
     g = synth.Geometry(n_angles=na, n_det=nd, nx=nx, ny=ny, center=c)
-    assert on_matrix_cores(xct, g, S)
+    assert on_matrix_cores(xct, g, S) is not None
     rng = np.random.default_rng(61)
     q = rng.standard_normal((S, na, nd)).astype(np.float32)
     inner = np.abs(np.arange(nd) - c) <= 70
@@ -188,7 +214,7 @@ def test_non_finite_slab_of_many_items(xct, case):
     as xct_backproject walks it below its limit, to the bit."""
     S, nx, ny, na, nd, c = case
     g = synth.Geometry(n_angles=na, n_det=nd, nx=nx, ny=ny, center=c)
-    assert on_matrix_cores(xct, g, S)
+    assert on_matrix_cores(xct, g, S) is not None
     q = torch.randn((S, na, nd), generator=torch.Generator().manual_seed(nx)).cuda()
     q[0, na // 2, nd // 3] = float("inf")
     say("non-finite, many items", case)
@@ -198,3 +224,90 @@ def test_non_finite_slab_of_many_items(xct, case):
     torch.cuda.synchronize()
     assert not torch.isfinite(img[0]).all() and torch.isfinite(img[1:]).all()
     assert torch.equal(img.nan_to_num(0.5, 7.0, -7.0), want.nan_to_num(0.5, 7.0, -7.0))
+
+
+@pytest.mark.parametrize("filtered", [torch.float32, torch.float16, torch.bfloat16])
+def test_batch_of_matrix_and_split_slabs(xct, filtered):
+    """A slab on the matrix cores, one with partial images there, and slabs
+    whose angles are split, in one batch: their scratch takes turns, and every
+    image equals its own call's to the bit; also the rows in 16 bits."""
+    slabs = []
+    for i, (S, nx, ny, na, nd, c, images) in enumerate([
+            (1, 256, 256, 360, 367, 183.0, None),      # split
+            (4, 813, 811, 602, 1160, 579.5, 3),        # mirror with reflection
+            (3, 131, 77, 163, 150, 74.3, None),        # split, a pair and one
+            (64, 512, 500, 150, 729, 363.7, 0),        # plain
+            (8, 1030, 1030, 300, 1460, 729.5, 0)]):    # quarter turn
+        g = synth.Geometry(n_angles=na, n_det=nd, nx=nx, ny=ny, center=c)
+        assert on_matrix_cores(xct, g, S, filtered) == images, i
+        p = torch.randn((S, na, nd), generator=torch.Generator().manual_seed(i)).cuda()
+        slabs.append((g, p, torch.full((S, ny, nx), float("nan"), device="cuda")))
+    say("batch of matrix and split slabs", filtered)
+    xct.xct_fbp_batch(slabs, "hann", filtered)
+    for i, (g, p, img) in enumerate(slabs):
+        alone = xct.fbp(p, g, "hann", filtered)
+        rows = xct.filter(p, g, "hann", filtered)
+        torch.cuda.synchronize()
+        assert torch.equal(alone, img), i
+        at = random_pixels(g, 3000, i)
+        assert rel_l2(img[:, at[:, 0], at[:, 1]].cpu(), sampled(rows, g, at, math.pi / g.n_angles).cpu()) < TOL, i
+
+
+@pytest.mark.parametrize("storage", [torch.float32, torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("nx, ny, na, nd", [
+    (1024, 1024, 1024, 1449),  # quarter turn
+    (1025, 1001, 1023, 1449),  # mirror; rows of a slice not 16-byte aligned
+])
+def test_back_projection_of_stored_rows(xct, storage, nx, ny, na, nd):
+    """xct_backproject from 1.5e10 updates, rows in every storage type; with a
+    non-finite element pixels off its ray are as before within rounding."""
+    S = 16
+    g = synth.Geometry(n_angles=na, n_det=nd, nx=nx, ny=ny, center=(nd - 1) / 2.0)
+    size = torch.float32 if storage == torch.float32 else torch.float16
+    assert on_matrix_cores(xct, g, S, size) is not None and S * na * nx * ny >= 1.5e10
+    q = torch.randn((S, na, nd), generator=torch.Generator().manual_seed(nd)).cuda().to(storage)
+    say("stored rows", storage, na)
+    img = xct.backproject(q, g, 0.25)
+    at = random_pixels(g, 3000, 3)
+    ref = sampled(q, g, at, 0.25)
+    got = img[:, at[:, 0], at[:, 1]].double()
+    for z in range(S):
+        assert rel_l2(got[z].cpu(), ref[z].cpu()) < TOL, z
+    for bad in (float("nan"), float("inf")):
+        q[3, na // 3, nd // 2] = bad
+        hit = xct.backproject(q, g, 0.25)[:, at[:, 0], at[:, 1]].double()
+        torch.cuda.synchronize()
+        finite = torch.isfinite(hit)
+        x, y = at[:, 1] - 0.5 * (nx - 1), at[:, 0] - 0.5 * (ny - 1)
+        off = (x * math.cos(g.angles[na // 3]) + y * math.sin(g.angles[na // 3]) + g.center - nd // 2).abs()
+        assert not finite[3][off < 0.99].any() and finite[3][off > 1.01].all()
+        assert finite[[z for z in range(S) if z != 3]].all()
+        assert rel_l2(hit[finite].cpu(), ref[finite].cpu()) < TOL
+
+
+@pytest.mark.parametrize("case", [
+    # slices, nx, ny, angles, bins, centre, rows of a split table, partial images
+    (32, 1024, 1024, 2049, 4100, 2049.3, 1028, 0),   # plain
+    (32, 1024, 1024, 2049, 4100, 2049.5, 1028, 0),   # mirror
+    (3, 1500, 1499, 8201, 8190, 4094.5, 4104, 4),    # mirror, each range's parts items of their own
+    (3, 900, 900, 8200, 8190, 4094.5, 4104, 2),      # the same, quarter turn
+])
+def test_split_table_in_ranges(xct, case):
+    """Split tables beyond 1 GiB are made and used range by range of angles, the
+    image accumulating; the last range is shorter."""
+    S, nx, ny, na, nd, c, rows, images = case
+    g = synth.Geometry(n_angles=na, n_det=nd, nx=nx, ny=ny, center=c)
+    assert on_matrix_cores(xct, g, S, rows=rows) == images
+    q = torch.randn((S, na, nd), device="cuda", generator=torch.Generator(device="cuda").manual_seed(na))
+    base = torch.randn((S, ny, nx), device="cuda", generator=torch.Generator(device="cuda").manual_seed(nd))
+    say("ranges", case)
+    img = xct.project_adjoint(q, g)
+    acc = base.clone()
+    xct.xct_project_adjoint(g, q, acc, -0.5, accumulate=True)
+    at = random_pixels(g, 1500, nx)
+    ref = sampled(q, g, at, 1.0)
+    got = img[:, at[:, 0], at[:, 1]].double()
+    added = (acc - base)[:, at[:, 0], at[:, 1]].double()
+    for z in range(S):
+        assert rel_l2(got[z].cpu(), ref[z].cpu()) < TOL, z
+        assert rel_l2(added[z].cpu(), -0.5 * ref[z].cpu()) < TOL, z
