@@ -747,7 +747,11 @@ int launch_bp_jobs(std::vector<BPJob> jobs, int dtype, unsigned int *counters, B
                      [](const BPJob &a, const BPJob &b) { return a.g->n_angles > b.g->n_angles; });
     // two slices (pairs) per work item when every slab has at least two
     int spi = item_slices(jobs[0]);
-    for (const BPJob &j : jobs) spi = std::min(spi, item_slices(j));
+    bool split = gate != nullptr;
+    for (const BPJob &j : jobs) {
+        spi = std::min(spi, item_slices(j));
+        split = split || j.partial;
+    }
     std::vector<BPSlab> desc(jobs.size());
     int W = 0;
     int64_t items = 0;
@@ -804,9 +808,9 @@ int launch_bp_jobs(std::vector<BPJob> jobs, int dtype, unsigned int *counters, B
         std::memcpy(b.slab, desc.data(), sizeof(BPSlab) * desc.size());
     }
     if (counters) {
-        const int per_cu = bp_max_blocks_per_cu(path, dtype, W, spi, lds);
+        const int per_cu = bp_max_blocks_per_cu(path, dtype, W, spi, split, lds);
         const int grid = (int)std::min<int64_t>(items, (int64_t)per_cu * jobs[0].cus);
-        hipError_t e = launch_bp(path, b, dtype, spi, grid, lds, s);
+        hipError_t e = launch_bp(path, b, dtype, spi, split, grid, lds, s);
         return e == hipSuccess ? XCT_OK : hip_fail(e);
     }
     const int64_t threads = bp_block_threads(path, spi);
@@ -815,7 +819,7 @@ int launch_bp_jobs(std::vector<BPJob> jobs, int dtype, unsigned int *counters, B
         const int64_t count = std::min(max_items, items - base);
         b.item_base = base;
         b.xcd_remap = (count % 8 == 0) ? 1 : 0;
-        hipError_t e = launch_bp(path, b, dtype, spi, (int)count, lds, s);
+        hipError_t e = launch_bp(path, b, dtype, spi, split, (int)count, lds, s);
         if (e != hipSuccess) return hip_fail(e);
     }
     return XCT_OK;

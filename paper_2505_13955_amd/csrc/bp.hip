@@ -85,6 +85,7 @@ __device__ __forceinline__ KSlab *slab_at(KBatch *b, int s)
     return &b->slab[s];
 }
 
+template <bool PARTS = true>
 __device__ __forceinline__ void select_slab(KBatch *b, int s, BPSlab &out)
 {
     KSlab *d = slab_at(b, s);
@@ -108,8 +109,8 @@ __device__ __forceinline__ void select_slab(KBatch *b, int s, BPSlab &out)
     out.code_a = d->code_a;
     out.code_b = d->code_b;
     out.sets = d->sets;
-    out.part_len = d->part_len;
-    out.partial = d->partial;
+    out.part_len = PARTS ? d->part_len : 0;
+    out.partial = PARTS ? d->partial : nullptr;
 }
 
 // Store of voxel `idx` (slab-wide index) from its accumulated sum: v = scale
@@ -134,12 +135,13 @@ __device__ __forceinline__ void store_voxel(const BPSlab &sl, int64_t idx, float
 // The angles (symmetric path: pairs) [begin, end) of a work item, of `units` in
 // all, and the item's index within its part: an item of a split slab covers one
 // part and stores to that part's copy (see BPSlab).
+template <bool PARTS = true>
 __device__ __forceinline__ int64_t item_part(BPSlab &sl, int64_t local, int64_t per_part, int64_t voxels, int units, int &begin,
                                              int &end)
 {
     begin = 0;
     end = units;
-    if (!sl.partial) return local;
+    if (!PARTS || !sl.partial) return local;
     const int part = __builtin_amdgcn_readfirstlane((int)(local / per_part));
     begin = part * sl.part_len;
     end = min(units, begin + sl.part_len);
@@ -227,11 +229,15 @@ size_t bp_generic_lds_bytes(int win, int kb)
     return (size_t)kb * sizeof(float4) + (size_t)kb * win * sizeof(float2);
 }
 
-template <typename T>
+// PARTS: launches that are gated or hold split slabs.  Their scalar registers
+// leave seven wavefronts per SIMD, one fewer than the others' (1600 items, eight
+// to a CU: 1.15 times as long); bound to eight they spill (3000^2, pixel 1.3:
+// 1.3 times).
+template <typename T, bool PARTS>
 __global__ __launch_bounds__(kBPThreads) void bp_generic_kernel(BPBatch arg)
 {
     KBatch *b = kernarg_batch();
-    if (b->gate && *b->gate == 0) return;
+    if (PARTS && b->gate && *b->gate == 0) return;
     extern __shared__ float4 lds4[];
     __shared__ int64_t item_slot;
     const int kb = b->kb, W = b->win;
@@ -246,10 +252,10 @@ __global__ __launch_bounds__(kBPThreads) void bp_generic_kernel(BPBatch arg)
         const int64_t item = uniform64(next_item(b, &item_slot, iter));
         if (item >= b->total_items) break;
         BPSlab sl;
-        select_slab(b, find_slab(b, item), sl);
+        select_slab<PARTS>(b, find_slab(b, item), sl);
         const int tiles = sl.tiles_x * sl.tiles_y;
         int k_begin, k_end;
-        const int64_t local = item_part(sl, item - sl.item_begin, (int64_t)tiles * sl.n_slices,
+        const int64_t local = item_part<PARTS>(sl, item - sl.item_begin, (int64_t)tiles * sl.n_slices,
                                                (int64_t)sl.n_slices * sl.nx * sl.ny, sl.n_angles, k_begin, k_end);
         const int z = __builtin_amdgcn_readfirstlane((int)(local / tiles));
         const int t = __builtin_amdgcn_readfirstlane((int)(local - (int64_t)z * tiles));
@@ -969,12 +975,17 @@ static auto with_mirror(int dtype, int win, F &&f)
 }
 
 template <typename F>
-static auto with_kernel(int path, int dtype, int win, int sl, F &&f)
+static auto with_kernel(int path, int dtype, int win, int sl, bool parts, F &&f)
 {
+    if (path == kPathGeneric && parts) {
+        if (dtype == XCT_F32) return f(bp_generic_kernel<float, true>, kBPThreads);
+        if (dtype == XCT_F16) return f(bp_generic_kernel<f16_t, true>, kBPThreads);
+        return f(bp_generic_kernel<bf16_t, true>, kBPThreads);
+    }
     if (path == kPathGeneric) {
-        if (dtype == XCT_F32) return f(bp_generic_kernel<float>, kBPThreads);
-        if (dtype == XCT_F16) return f(bp_generic_kernel<f16_t>, kBPThreads);
-        return f(bp_generic_kernel<bf16_t>, kBPThreads);
+        if (dtype == XCT_F32) return f(bp_generic_kernel<float, false>, kBPThreads);
+        if (dtype == XCT_F16) return f(bp_generic_kernel<f16_t, false>, kBPThreads);
+        return f(bp_generic_kernel<bf16_t, false>, kBPThreads);
     }
     if (path == kPathMirror) return sl == 2 ? with_mirror<2, true, false>(dtype, win, f) : with_mirror<1, true, false>(dtype, win, f);
     if (path == kPathPairs) {
@@ -984,9 +995,9 @@ static auto with_kernel(int path, int dtype, int win, int sl, F &&f)
     return sl == 2 ? with_sym<2>(dtype, win, f) : with_sym<1>(dtype, win, f);
 }
 
-hipError_t launch_bp(int path, const BPBatch &b, int dtype, int sl, int grid, size_t lds, hipStream_t s)
+hipError_t launch_bp(int path, const BPBatch &b, int dtype, int sl, bool parts, int grid, size_t lds, hipStream_t s)
 {
-    return with_kernel(path, dtype, b.win, sl, [&](auto k, int threads) { return launch(k, threads, b, grid, lds, s); });
+    return with_kernel(path, dtype, b.win, sl, parts, [&](auto k, int threads) { return launch(k, threads, b, grid, lds, s); });
 }
 
 int bp_block_threads(int path, int sl)
@@ -995,9 +1006,9 @@ int bp_block_threads(int path, int sl)
     return sl >= 2 ? sym_threads<2>() : sym_threads<1>();
 }
 
-int bp_max_blocks_per_cu(int path, int dtype, int win, int sl, size_t lds)
+int bp_max_blocks_per_cu(int path, int dtype, int win, int sl, bool parts, size_t lds)
 {
-    return with_kernel(path, dtype, win, sl, [&](auto k, int threads) { return occupancy(k, threads, lds); });
+    return with_kernel(path, dtype, win, sl, parts, [&](auto k, int threads) { return occupancy(k, threads, lds); });
 }
 
 }  // namespace xct

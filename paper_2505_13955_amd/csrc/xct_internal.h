@@ -88,12 +88,13 @@ enum { kPathGeneric = 0, kPathSymmetric = 1, kPathMirror = 2, kPathPairs = 3 };
 
 // Launch (returns hipError_t of the launch) and sizing helpers.
 // `sl`: slices per work item of the symmetric kernel (1 or 2).
-hipError_t launch_bp(int path, const BPBatch &b, int dtype, int sl, int grid, size_t lds, hipStream_t s);
+// `parts`: some slab of the launch is split, or the launch is gated.
+hipError_t launch_bp(int path, const BPBatch &b, int dtype, int sl, bool parts, int grid, size_t lds, hipStream_t s);
 size_t bp_generic_lds_bytes(int win, int kb);
 size_t bp_sym_lds_bytes(int win, int kb, int sl);
 size_t bp_mirror_lds_bytes(int win, int kb, int sl);
 int bp_sym_window(int need);  // window of the symmetric kernel covering `need` (0: none)
-int bp_max_blocks_per_cu(int path, int dtype, int win, int sl, size_t lds);
+int bp_max_blocks_per_cu(int path, int dtype, int win, int sl, bool parts, size_t lds);
 int bp_block_threads(int path, int sl);  // threads per workgroup of the kernel
 
 // Matrix-core back-projection (bp_mfma.hip): what a pixel's coordinate serves.
