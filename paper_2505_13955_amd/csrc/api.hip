@@ -868,7 +868,7 @@ bool reflected_set(const xct_geometry *g)
     return true;
 }
 
-size_t mx_words_bytes(int n_slices) { return align256(sizeof(uint32_t) * (2 * (size_t)n_slices + 1 + kXcds)); }
+size_t mx_words_bytes(int n_slices) { return align256(sizeof(uint32_t) * (2 * (size_t)n_slices + 1)); }
 
 int mx_ops(int kind)
 {
@@ -988,8 +988,7 @@ size_t mx_scratch_bytes(const BPJob &j, const MXPlan &p)
 
 // The slices' magnitudes, then for each range of angles its split table and
 // its back-projection, and last the vector kernels, whose launch does nothing
-// unless some row element is not finite or some slice's range too wide (as many
-// workgroups as the device holds, so that doing nothing is short).
+// unless some row element is not finite or some slice's range too wide.
 int launch_bp_matrix(const BPJob &j, const MXPlan &p, int dtype, void *scratch, hipStream_t s)
 {
     const xct_geometry *g = j.g;
@@ -1042,7 +1041,7 @@ int launch_bp_matrix(const BPJob &j, const MXPlan &p, int dtype, void *scratch, 
             a.accumulate = 1;
         }
     }
-    return launch_bp_jobs({j}, dtype, amax + 1 + 2 * (size_t)j.n_slices, nullptr, s, amax);
+    return launch_bp_jobs({j}, dtype, nullptr, nullptr, s, amax);
 }
 
 }  // namespace

@@ -557,7 +557,7 @@ __global__ __launch_bounds__(kMagThreads) void absmax_kernel(const T *sino, int6
 
 hipError_t launch_absmax(const void *sino, int dtype, int n_slices, int64_t per_slice, uint32_t *amax, hipStream_t s)
 {
-    hipError_t e = launch_fill_u32(amax, 1 + 2 * n_slices + kXcds, 0u, s);
+    hipError_t e = launch_fill_u32(amax, 1 + 2 * n_slices, 0u, s);
     if (e != hipSuccess) return e;
     // 8 loads a thread; one workgroup per CU, or two (2 per slice at least) where
     // whole numbers per slice come close to that

@@ -108,7 +108,7 @@ struct MXArgs {
     const double2 *csd;    // [Np] (cos, sin) * pixel / pitch
     // [0]: a row element is not finite, or a slice's range is too wide; [1 + z]: slice
     // z's largest magnitude (float bits); [1 + n_slices + z]: minus the least that a
-    // run of its samples reaches; then kXcds zeros (counters of the gated launch)
+    // run of its samples reaches
     const uint32_t *amax;
     double center;
     // angles of this launch: k_first .. , with k_jump more from the

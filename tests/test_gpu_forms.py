@@ -35,7 +35,7 @@ def on_matrix_cores(xct, g, S, filtered=torch.float32, rows=None):
     size = 4 if filtered == torch.float32 else 2
     sino = torch.empty((S, g.n_angles, g.n_det), device="cuda")
     scratch = xct.xct_fbp_workspace_bytes([(g, sino, None)], filtered) - 512 - a256(sino.numel() * size)
-    rest = scratch - a256(4 * (2 * S + 9)) - a256((S + 3) // 4 * (rows or g.n_angles) * g.n_det * 16)
+    rest = scratch - a256(4 * (2 * S + 1)) - a256((S + 3) // 4 * (rows or g.n_angles) * g.n_det * 16)
     fit = [p for p in [0] + list(range(2, 65)) if rest == a256(p * 4 * S * g.nx * g.ny)]
     return fit[0] if fit else None
 
