@@ -614,8 +614,11 @@ struct VectorShape { int win, kb; size_t lds; };
 VectorShape vector_shape(int path, int W, int spi, int64_t items, int cus)
 {
     VectorShape v;
-    const bool three = spi == 3 || (spi == 2 && path != kPathSymmetric && items > 2 * (int64_t)cus);
-    const bool six = spi == 1 && path != kPathSymmetric && items > 4 * (int64_t)cus;
+    // (the wide windows only where the shorter stages save a round: 8 x 1300^2,
+    // pixel 1.2, 924 items 1.07 times as long in them, 693 items 0.91)
+    const bool narrow = bp_sym_window(W) <= 96;
+    auto shorter = [&](int more) { return path != kPathSymmetric && items > (more - (more == 6 ? 2 : 1)) * (int64_t)cus && (narrow || items <= more * (int64_t)cus); };
+    const bool three = spi == 3 || (spi == 2 && shorter(3)), six = spi == 1 && shorter(6);
     const size_t budget = three ? kMirrorStageBytes : six ? kMirrorStageBytes / 2 : spi == 2 ? kSym2StageBytes : kSymStageBytes;
     v.win = path == kPathGeneric ? W : bp_sym_window(W);  // choose_path only routes windows that fit here
     if (path == kPathSymmetric) {
