@@ -646,32 +646,38 @@ int64_t vector_items(const BPJob &j, int *spi)
 }
 
 // Times of the vector kernels as measured (ns per angle that a round of work
-// items takes, with every slot of the device taken and with one item per CU):
-//  * symmetric, two slices per item: two items per CU, 1180 (8192^2: 458 ms)
-//    and 770; one slice: four, 1300 and 710.
-//  * mirror (and slices in pairs), two slices (pairs): two items, 750 (8192^2,
-//    4 slices: 140 ms) and 580; one: four, 1270 and 630.
-//  * a pair and one slice: three items, 870 and 465.
-//  * generic: four items, 580 (2048^2, 16 slices: 19.0 ms) and 485.
-struct VectorTimes { int per_cu; double full, alone; };
+// items takes, with every slot of the device taken and with one item per CU,
+// and ns for the stores that end a full round's items; shapes of 24 to 600
+// angles, and 8192^2), by the workgroups that vector_shape lets share a CU:
+//  * symmetric, two slices per item: two, 1260 (2048^2 1180, 1024^2 and 512^2
+//    1350) and 770; one slice: four, 1400 and 710; stores 17 us.
+//  * mirror (and slices in pairs), two slices (pairs): two, 820 and 600, or
+//    three, 1140; one: four, 1270 and 630, or six, 1300; stores 11 us.
+//  * a pair and one slice: three, 870 and 465.
+//  * generic: four, 640 and 510, or eight, 980 over many rounds and 1200 over
+//    one or two; stores 5 us.
+struct KernelTimes { int per_cu; double full, alone, store; };
 
-VectorTimes vector_times(int path, int spi)
+KernelTimes vector_times(int path, int spi, int64_t items, int cus)
 {
-    if (path == kPathGeneric) return {4, 580, 485};
-    if (spi == 3) return {3, 870, 465};
-    if (path == kPathSymmetric) return spi == 2 ? VectorTimes{2, 1180, 770} : VectorTimes{4, 1300, 710};
-    return spi == 2 ? VectorTimes{2, 750, 580} : VectorTimes{4, 1270, 630};
+    if (path == kPathGeneric && items > 4 * (int64_t)cus) return {8, items > 16 * (int64_t)cus ? 980.0 : 1200.0, 510, 5000};
+    if (path == kPathGeneric) return {4, 640, 510, 5000};
+    if (path == kPathSymmetric) return spi == 2 ? KernelTimes{2, 1260, 770, 17000} : KernelTimes{4, 1400, 710, 17000};
+    if (spi == 3) return {3, 870, 465, 11000};
+    if (spi == 2) return items > 2 * (int64_t)cus ? KernelTimes{3, 1140, 600, 11000} : KernelTimes{2, 820, 600, 11000};
+    return items > 4 * (int64_t)cus ? KernelTimes{6, 1300, 630, 11000} : KernelTimes{4, 1270, 630, 11000};
 }
 
-// Rounds of n items, in ns per angle (a last round fills the CUs from one
-// item each up to per_cu).
-double vector_rounds(const VectorTimes &t, int64_t n, int64_t cus)
+// Time of n items of `angles` angles that store `stores` times each.  The last
+// round takes as long as the CUs that hold most of its items, which up to three
+// large workgroups a CU show in steps.
+double rounds_ns(const KernelTimes &t, int64_t n, int64_t cus, double angles, double stores)
 {
+    const double full = t.full * angles + t.store * stores;
+    const double alone = t.alone * angles + (t.per_cu > 1 ? 0.6 : 1.0) * t.store * stores;
     const int64_t slots = t.per_cu * cus, rest = n % slots;
-    const double last = rest == 0      ? 0
-                        : rest <= cus ? t.alone
-                                      : t.alone + (t.full - t.alone) * (double)(rest - cus) / (double)(slots - cus);
-    return (n / slots) * t.full + last;
+    const double held = t.per_cu <= 3 ? (double)((rest + cus - 1) / cus) : (double)rest / cus;
+    return (n / slots) * full + (rest == 0 ? 0.0 : held <= 1.0 ? alone : alone + (full - alone) * (held - 1.0) / (t.per_cu - 1.0));
 }
 
 // The share of a job's whole walks in rounds that fill the device.
@@ -679,8 +685,8 @@ double vector_share_ns(const BPJob &j)
 {
     int spi;
     const int64_t items = vector_items(j, &spi);
-    const VectorTimes t = vector_times(j.path, spi);
-    return (double)items / (t.per_cu * (double)j.cus) * t.full * j.g->n_angles;
+    const KernelTimes t = vector_times(j.path, spi, std::numeric_limits<int64_t>::max(), j.cus);  // (in a batch that fills the device)
+    return (double)items / (t.per_cu * (double)j.cus) * (t.full * j.g->n_angles + t.store);
 }
 
 size_t image_bytes(const BPJob &j) { return sizeof(float) * (size_t)j.n_slices * j.g->nx * j.g->ny; }
@@ -688,14 +694,16 @@ size_t image_bytes(const BPJob &j) { return sizeof(float) * (size_t)j.n_slices *
 // Adding up parts: a launch and its scratch, and the passes over the images at 4 TB/s.
 double sum_ns(const BPJob &j, int64_t parts) { return 14000.0 + (parts + 1) * (double)image_bytes(j) / 4000.0; }
 
-double bp_vector_ns(const BPJob &j)
+// (stores: 0 where whole walks and parts are weighed against each other)
+double bp_vector_ns(const BPJob &j, double stores)
 {
     int spi;
     const int64_t items = vector_items(j, &spi);
-    const VectorTimes t = vector_times(j.path, spi);
-    if (j.parts < 2) return vector_rounds(t, items, j.cus) * j.g->n_angles;
+    const int64_t n = j.parts < 2 ? items : items * j.parts;
+    const KernelTimes t = vector_times(j.path, spi, n, j.cus);
+    if (j.parts < 2) return rounds_ns(t, n, j.cus, j.g->n_angles, stores);
     const double per_part = (double)j.part_len * (j.path == kPathSymmetric ? 2 : 1);
-    return vector_rounds(t, items * j.parts, j.cus) * per_part + sum_ns(j, j.parts);
+    return rounds_ns(t, n, j.cus, per_part, stores) + sum_ns(j, j.parts);
 }
 
 // Parts of a small job's angles: a workgroup walks all angles of its tile, so
@@ -710,22 +718,35 @@ void plan_parts(BPJob &j)
 {
     int spi;
     const int64_t items = vector_items(j, &spi);
-    if (j.out_u16 || items >= vector_times(j.path, spi).per_cu * (int64_t)j.cus) return;
+    if (j.out_u16 || items >= vector_times(j.path, spi, 0, j.cus).per_cu * (int64_t)j.cus) return;
     const VectorShape v = vector_shape(j.path, window_entries(j.g->pixel_size / j.g->det_pitch), spi, items, j.cus);
     const int units = j.path == kPathSymmetric ? j.g->n_angles / 2 : j.g->n_angles;
     const int64_t most = std::min<int64_t>(units / (kPartStages * v.kb), kPartBytes / image_bytes(j));
     BPJob t = j;
-    double least = 0.95 * bp_vector_ns(j);
+    double least = 0.95 * bp_vector_ns(j, 0);
     for (int64_t want = 2; want <= most && want <= 64; want += 1 + want / 8) {
         t.part_len = (int)((units + want - 1) / want + v.kb - 1) / v.kb * v.kb;
         t.parts = (units + t.part_len - 1) / t.part_len;
-        const double ns = t.parts < 2 ? least : bp_vector_ns(t);
+        const double ns = t.parts < 2 ? least : bp_vector_ns(t, 0);
         if (ns < least) {
             least = ns;
             j.part_len = t.part_len;
             j.parts = t.parts;
         }
     }
+}
+
+// A job alone: the parts of its angles, and slices in pairs only where that is
+// faster.  A call that leaves the device idle anyway ends sooner in the generic
+// kernel's more and shorter items (16 x 142^2 x 28 angles 35 us, 42 in pairs).
+void plan_alone(BPJob &j)
+{
+    BPJob single = j;
+    plan_parts(j);
+    if (j.path != kPathPairs) return;
+    single.path = kPathGeneric;
+    plan_parts(single);
+    if (bp_vector_ns(single, 1) < bp_vector_ns(j, 1)) j = single;
 }
 
 // Partial images of a split job that takes one item per part (0: too large, or not split).
@@ -890,22 +911,29 @@ int64_t mx_items(const BPJob &j, int kind, int cols, int *tiles_x, int *tiles_y)
 }
 
 // Which kernels a job takes is decided by their times as measured: the vector
-// kernels' above; the matrix kernel's ns per angle are 665 for a round of one
-// 64-column item per CU, and for two items per CU (one) 740 (490) with 32
-// columns and 440 (290) with 16 (16 x 2048^2 x 1800 angles in 64 columns 4.94
+// kernels' above; the matrix kernel's ns per angle are 610 for a round of one
+// 64-column item per CU, and for two items per CU (one) 680 (430) with 32
+// columns and 415 (270) with 16 (16 x 2048^2 x 1800 angles in 64 columns 4.94
 // ms; 32 x 1024^2 x 1025 in 32 columns 1.57 ms; 4 x 4096^2 x 1023 in 16 columns
 // 3.63 ms; 4 x 4096^2 x 3072, 2080 items of 32 columns or 4096 of 16: 9.1 and
-// 9.7 ms).  The matrix path's own passes over the rows (magnitudes, split
-// table) are added at the 4.5 TB/s they reach, with 30 us for their launches (4
-// x 512^2 x 721 angles: 102 us in matrix form, 94 in vector form).
+// 9.7 ms).  Every part's stores add 59, 46 and 23 us to a round in which all
+// columns are slices (16 x 1024^2, 64 x 512^2 and 4 x 2048^2 in two parts: 118
+// to 121, 92 to 97 and 46 to 51 us apart from the angles), which decides calls
+// of few angles: 104 x 1950^2 x 20 take 3.7 ms in matrix form, 0.94 in vector
+// form.  The matrix path's own passes over the rows (magnitudes, split table)
+// are added at the 4.5 TB/s they reach, with 30 us for their launches (4 x 512^2
+// x 721 angles: 102 us in matrix form, 94 in vector form).
 double bp_matrix_ns(const BPJob &j, const MXPlan &p, int64_t items, int dtype)
 {
     const double rows = (double)j.n_slices * j.g->n_angles * j.g->n_det;
+    const double launches = (j.g->n_angles + p.per_launch - 1) / p.per_launch;
     const double angles = p.spread ? (double)p.part_len / p.per_launch * j.g->n_angles : j.g->n_angles;
-    const VectorTimes t = p.cols == 64   ? VectorTimes{1, 665, 665}
-                          : p.cols == 32 ? VectorTimes{2, 740, 490}
-                                         : VectorTimes{2, 440, 290};
-    double ns = vector_rounds(t, (p.spread ? p.parts : 1) * items, j.cus) * angles;
+    const int spi = p.cols / mx_ops(p.kind);
+    const double used = (double)j.n_slices / ((j.n_slices + spi - 1) / spi * spi);
+    const KernelTimes t = p.cols == 64   ? KernelTimes{1, 610, 610, 59000}
+                          : p.cols == 32 ? KernelTimes{2, 680, 430, 46000}
+                                         : KernelTimes{2, 415, 270, 23000};
+    double ns = rounds_ns(t, (p.spread ? p.parts : 1) * items, j.cus, angles, launches * (p.spread ? 1 : p.parts) * used);
     ns += rows * (2 * dtype_size(dtype) + 4) / 4500.0 + 30000.0;
     if (p.spread) ns += sum_ns(j, p.parts);
     return ns;
@@ -952,7 +980,7 @@ MXPlan mx_plan(const BPJob &j, int dtype)
     const int64_t fit = kMXTableBytes / angle_bytes;
     // the reflected kinds read rows k and N_p - k together: whole tables only
     const bool refl = (j.path == kPathSymmetric || j.path == kPathMirror) && fit >= g->n_angles && reflected_set(g);
-    double least = 0.95 * bp_vector_ns(j);
+    double least = 0.95 * bp_vector_ns(j, 1);
     auto consider = [&](int kind) {
         MXPlan p;
         p.kind = kind;
@@ -1224,7 +1252,7 @@ static int backproject_one(const xct_geometry *g, int32_t n_slices, const void *
     if (int rc = geo_tables(g, s, &j.t)) return rc;
     const double updates = (double)n_slices * g->n_angles * g->nx * g->ny;
     if (updates >= least) pair_slices(j);
-    if (least == 0.0) plan_parts(j);
+    if (least == 0.0) plan_alone(j);
     MXPlan p;
     if (updates >= least) p = mx_plan(j, sino_t);
     // Scratch in stream-ordered memory.  A stream under capture, or no memory,
@@ -1595,12 +1623,13 @@ static void plan_batch(int32_t n_slabs, int32_t filtered_t, BatchPlan &b)
     auto joins = [&](int i) { return b.mx[i].cols && b.mx[i].ns >= vector_share_ns(b.jobs[i]); };
     for (int i = 0; i < n_slabs; ++i) {
         BPJob &j = b.jobs[i];
-        plan_parts(j);
+        plan_alone(j);
         b.mx[i] = mx_plan(j, filtered_t);
         if (!joins(i)) continue;
         turns += b.mx[i].ns;
         shares += vector_share_ns(j);
-        walk = std::max(walk, vector_times(j.path, item_slices(j)).full * j.g->n_angles);
+        const KernelTimes t = vector_times(j.path, item_slices(j), 0, j.cus);
+        walk = std::max(walk, t.full * j.g->n_angles + t.store);
     }
     // (the vector launch ends with a tail of half a walk on average)
     const bool join = n_slabs > 1 && shares + 0.5 * walk < turns;
@@ -1611,13 +1640,17 @@ static void plan_batch(int32_t n_slabs, int32_t filtered_t, BatchPlan &b)
         if (b.mx[i].cols) {
             b.scratch = std::max(b.scratch, mx_scratch_bytes(b.jobs[i], b.mx[i]));
         } else {
+            BPJob j = b.jobs[i];
+            pair_slices(j);
             int spi;
-            items += vector_items(b.jobs[i], &spi);
+            items += vector_items(j, &spi);
             parts += part_bytes(b.jobs[i]);
         }
     }
     b.spread = items < 2 * (int64_t)device_cus() && parts <= (size_t)kPartBytes;
     if (b.spread) b.scratch = std::max(b.scratch, parts);
+    else if (n_slabs > 1)
+        for (BPJob &j : b.jobs) pair_slices(j);
 }
 
 size_t xct_fbp_workspace_bytes(const xct_slab *slabs, int32_t n_slabs, int32_t filtered_t)
@@ -1704,7 +1737,7 @@ int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_
             const int64_t n = vector_items(j, &spi);
             items += j.partial ? n * j.parts : n;
         }
-        persistent[grp] = groups[grp].size() > 1 && items > vector_times(groups[grp][0].path, spi).per_cu * (int64_t)device_cus();
+        persistent[grp] = groups[grp].size() > 1 && items > vector_times(groups[grp][0].path, spi, items, device_cus()).per_cu * (int64_t)device_cus();
         any = any || persistent[grp];
     }
     hipError_t e = any ? launch_fill_u32(counters, kGroups * kXcds, 0u, s) : hipSuccess;

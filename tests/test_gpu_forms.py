@@ -13,8 +13,10 @@ from tests.gpu_util import rel_l2, say, to_dev
 
 pytestmark = pytest.mark.gpu
 
-# The gate of the vector kernels: coordinates below 96 or 192 bins.
+# The gate of the vector kernels: coordinates below 96 or 192 bins; and of the
+# matrix cores, below 64 (FP32 sums into an image of the same size besides).
 TOL = 2e-5
+TOL_MATRIX = 1e-5
 
 
 @pytest.fixture(scope="module")
@@ -68,7 +70,7 @@ def random_pixels(g, n, seed):
     # slices, nx, ny, angles, bins, centre
     (61, 413, 390, 301, 600, 299.7),    # plain
     (4, 813, 811, 602, 1160, 579.5),    # mirror with reflection
-    (4, 1030, 1030, 300, 1460, 729.5),  # quarter turn
+    (8, 1030, 1030, 300, 1460, 729.5),  # quarter turn
 ])
 def test_wide_range_of_magnitudes(xct, case):
     """Samples far smaller than the slice's largest keep their bits: a disc of
@@ -152,7 +154,7 @@ def test_forward_projection_captured_after_an_eager_call(xct, case):
 @pytest.mark.parametrize("case", [
     # slabs, slices, nx, ny, angles, bins: what a slab alone takes
     (140, 1, 256, 256, 90, 367),    # parts
-    (14, 8, 400, 300, 500, 520),    # the matrix cores
+    (14, 14, 400, 300, 500, 520),   # the matrix cores
 ])
 def test_batch_that_fills_the_device_walks_whole(xct, case):
     """Slabs that alone are split, or on the matrix cores, because they would
@@ -160,6 +162,7 @@ def test_batch_that_fills_the_device_walks_whole(xct, case):
     vector kernels, as xct_backproject walks them, to the bit."""
     n, S, nx, ny, na, nd = case
     g = synth.Geometry(n_angles=na, n_det=nd, nx=nx, ny=ny, center=(nd - 1) / 2.0)
+    assert (on_matrix_cores(xct, g, S) is None) == (S == 1)
     p = torch.randn((n, S, na, nd), generator=torch.Generator().manual_seed(na)).cuda()
     img = torch.empty((n, S, ny, nx), device="cuda")
     say("full batch", case)
@@ -205,8 +208,8 @@ def test_adjoint_captured_after_an_eager_call(xct, case):
 
 @pytest.mark.parametrize("case", [
     # slices, nx, ny, angles, bins, centre: more items than workgroups, no multiple of the XCDs
-    (72, 576, 576, 120, 815, 407.0),    # symmetric
-    (37, 500, 460, 151, 681, 340.0),    # mirror
+    (72, 576, 576, 240, 815, 407.0),    # symmetric
+    (37, 500, 460, 401, 681, 340.0),    # mirror
     (3, 1301, 1203, 301, 1800, 899.0),  # mirror, few slices
 ])
 def test_non_finite_slab_of_many_items(xct, case):
@@ -226,6 +229,57 @@ def test_non_finite_slab_of_many_items(xct, case):
     assert torch.equal(img.nan_to_num(0.5, 7.0, -7.0), want.nan_to_num(0.5, 7.0, -7.0))
 
 
+PLAIN, MIRROR, MIRROR2, QUARTER, QUARTER2 = range(5)
+
+
+@pytest.mark.parametrize("case", [
+    # columns, kind, partial images; slices, nx, ny, angles, bins, centre, angle set
+    (16, PLAIN, 0, 8, 713, 690, 180, 1034, 516.3, "half"),
+    (16, PLAIN, 2, 15, 433, 410, 301, 636, 317.3, "half"),
+    (32, PLAIN, 0, 31, 713, 690, 101, 1034, 516.3, "half"),
+    (32, PLAIN, 5, 31, 313, 290, 600, 466, 232.3, "half"),
+    (64, PLAIN, 2, 61, 313, 290, 404, 466, 232.3, "half"),
+    (16, MIRROR, 0, 7, 602, 591, 180, 857, 428.0, "half"),
+    (16, MIRROR, 5, 8, 300, 289, 600, 429, 214.0, "half"),
+    (32, MIRROR, 0, 31, 700, 689, 101, 997, 498.0, "half"),
+    (32, MIRROR, 3, 16, 513, 502, 1001, 731, 365.0, "rand"),
+    (64, MIRROR, 2, 61, 300, 289, 404, 429, 214.0, "half"),
+    (16, MIRROR2, 0, 3, 1020, 1009, 180, 1451, 725.0, "half"),
+    (32, MIRROR2, 3, 7, 813, 802, 301, 1157, 578.0, "half"),
+    (64, MIRROR2, 3, 15, 513, 502, 600, 731, 365.0, "half"),
+    (16, QUARTER, 0, 31, 300, 300, 180, 429, 214.0, "full"),
+    (32, QUARTER, 5, 15, 420, 420, 600, 599, 299.0, "half"),
+    (64, QUARTER, 2, 15, 602, 602, 404, 857, 428.0, "half"),
+    (64, QUARTER, 0, 61, 420, 420, 404, 599, 299.0, "full"),
+    (32, QUARTER2, 0, 3, 1950, 1950, 180, 2772, 1385.5, "half"),
+    (64, QUARTER2, 0, 7, 1400, 1400, 404, 1991, 995.0, "half"),
+])
+def test_matrix_kernels(xct, case):
+    """Every kind and column count of the matrix-core kernel, with the kernel
+    that ran read from a trace."""
+    cols, kind, images, S, nx, ny, na, nd, c, angles = case
+    rng = np.random.default_rng(cols + kind)
+    th = rng.uniform(-math.pi, 2.0 * math.pi, na) if angles == "rand" else np.arange(na) * ((2.0 if angles == "full" else 1.0) * math.pi / na)
+    g = synth.Geometry(n_angles=na, n_det=nd, nx=nx, ny=ny, center=c, angles=th)
+    q = torch.randn((S, na, nd), generator=torch.Generator().manual_seed(na)).cuda()
+    base = torch.randn((S, ny, nx), generator=torch.Generator().manual_seed(nd)).cuda()
+    say("matrix kernel", case)
+    img = xct.project_adjoint(q, g)
+    acc = base.clone()
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as trace:
+        xct.xct_project_adjoint(g, q, acc, -0.5, accumulate=True)
+        torch.cuda.synchronize()
+    ran = [e.name for e in trace.events() if "bp_mfma" in e.name]
+    assert ran and all(f"<{cols}, {kind}>" in name for name in ran), ran
+    at = random_pixels(g, 3000, nx)
+    ref = sampled(q, g, at, 1.0)
+    for z in range(S):
+        assert rel_l2(img[z, at[:, 0], at[:, 1]].cpu(), ref[z].cpu()) < TOL_MATRIX, z
+        assert rel_l2((acc - base)[z, at[:, 0], at[:, 1]].cpu(), -0.5 * ref[z].cpu()) < TOL_MATRIX, z
+    if angles != "full":  # (a launch of a full turn's set makes the table of that set)
+        assert on_matrix_cores(xct, g, S) == images
+
+
 @pytest.mark.parametrize("filtered", [torch.float32, torch.float16, torch.bfloat16])
 def test_batch_of_matrix_and_split_slabs(xct, filtered):
     """A slab on the matrix cores, one with partial images there, and slabs
@@ -237,7 +291,7 @@ def test_batch_of_matrix_and_split_slabs(xct, filtered):
             (4, 813, 811, 602, 1160, 579.5, 3),        # mirror with reflection
             (3, 131, 77, 163, 150, 74.3, None),        # split, a pair and one
             (64, 512, 500, 150, 729, 363.7, 0),        # plain
-            (8, 1030, 1030, 300, 1460, 729.5, 0)]):    # quarter turn
+            (8, 1030, 1030, 300, 1460, 729.5, 2)]):    # quarter turn
         g = synth.Geometry(n_angles=na, n_det=nd, nx=nx, ny=ny, center=c)
         assert on_matrix_cores(xct, g, S, filtered) == images, i
         p = torch.randn((S, na, nd), generator=torch.Generator().manual_seed(i)).cuda()
