@@ -1725,10 +1725,12 @@ int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_
                                                 : (two ? kGroupSym2 : kGroupSym1);
         groups[grp].push_back(j);
     }
-    // A group whose items all fit on the device at once, or are all alike (one
-    // slab), is launched with one workgroup per item: no counters, and no
-    // workgroup that asks every XCD's counter in turn before it ends (some 10 us
-    // of a call with one item each; 26 x 780^2 x 33 angles 118 us, 166 with them).
+    // A group whose items all fit on the device at once is launched with one
+    // workgroup per item: no counters, and no workgroup that asks every XCD's
+    // counter in turn before it ends (some 10 us of a call with one item each).
+    // So is one slab of less than a millisecond, whose items are all alike (26 x
+    // 780^2 x 33 angles 118 us, 166 with counters; longer, their order keeps rows
+    // in cache: 46 x 1554^2 x 660, pixel 1.3, 7.5 ms with them, 8.0 without).
     bool persistent[kGroups], any = false;
     for (int grp = 0; grp < kGroups; ++grp) {
         int64_t items = 0;
@@ -1737,7 +1739,8 @@ int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_
             const int64_t n = vector_items(j, &spi);
             items += j.partial ? n * j.parts : n;
         }
-        persistent[grp] = groups[grp].size() > 1 && items > vector_times(groups[grp][0].path, spi, items, device_cus()).per_cu * (int64_t)device_cus();
+        const bool shared = groups[grp].size() > 1 || (groups[grp].size() == 1 && bp_vector_ns(groups[grp][0], 1) >= 1e6);
+        persistent[grp] = shared && items > vector_times(groups[grp][0].path, spi, items, device_cus()).per_cu * (int64_t)device_cus();
         any = any || persistent[grp];
     }
     hipError_t e = any ? launch_fill_u32(counters, kGroups * kXcds, 0u, s) : hipSuccess;
