@@ -1389,6 +1389,10 @@ static int forward_form(const xct_geometry *g, int32_t n_slices, const float *im
     // a later call under capture takes it, and may not be its geometry's first)
     EntryRef t;
     if (int rc = fp_tables(g, s, &t)) return rc;
+    // one workgroup per (slice group, bin block, angle block), indexed in 32 bits
+    const int64_t bin_blocks = (g->n_det + kFPBins - 1) / kFPBins;
+    const int whole = n_slices >= 3 && t->fp_four ? 4 : 1;
+    if (t->n_blocks * bin_blocks * ((n_slices + whole - 1) / whole) >= ((int64_t)1 << 31)) return XCT_ETOOBIG;
     bool turned = scratch && fp_turns(g, n_slices);
     if (turned) {
         xct_geometry quarter = *g;
@@ -1406,15 +1410,13 @@ static int forward_form(const xct_geometry *g, int32_t n_slices, const float *im
     a.ang = t->table<FPAngle>(0);
     a.blocks = t->table<FPBlock>(1);
     a.n_blocks = t->n_blocks;
-    a.bin_blocks = (g->n_det + kFPBins - 1) / kFPBins;
+    a.bin_blocks = (int32_t)bin_blocks;
     // four slices per workgroup share coordinates and weights; a call with
     // one or two slices, without turned copies, keeps one per workgroup
     const int sl = turned || (n_slices >= 3 && t->fp_four) ? 4 : 1;
     const int64_t groups = turned ? n_slices : (n_slices + sl - 1) / sl;
-    // one workgroup per (slice group, bin block, angle block), indexed in 32 bits
-    const int64_t triples = (int64_t)a.n_blocks * a.bin_blocks * groups;
-    if (triples >= ((int64_t)1 << 31))
-        return turned ? forward_form(g, n_slices, image, base, sino, alpha, accumulate, false, s) : XCT_ETOOBIG;
+    const int64_t triples = a.n_blocks * bin_blocks * groups;
+    if (triples >= ((int64_t)1 << 31)) return forward_form(g, n_slices, image, base, sino, alpha, accumulate, false, s);
     a.scale = (float)((double)alpha * projector_scale(g));
     a.accumulate = accumulate ? 1 : 0;
     a.n_angles = g->n_angles;
