@@ -185,11 +185,12 @@ int xct_preprocess_filter(const xct_geometry *g, int32_t n_rows, int32_t row_beg
  * (pixels up to 1.1 bins wide; finite rows in which every run of 32 samples, a
  * slice's rows following each other, is all zero or reaches 2^-20 of the
  * slice's largest magnitude, so that a far larger sample elsewhere takes no
- * bits from it; up to 1.25 GiB of scratch); of the
- * rest, square even slices with an angle set closed under
- * quarter turns and 2c integral take the quarter-turn symmetric kernel; any
- * other slice with 2c integral the mirror kernel (pixel pairs reflected
- * through the slice centre, u -> 2c - u); the rest the generic kernel.  FBP over a half turn uses
+ * bits from it; up to 1.25 GiB of scratch); of the rest, square even slices with
+ * an angle set closed under quarter turns and 2c integral take the quarter-turn
+ * symmetric kernel; any other slice with 2c integral the mirror kernel (pixel
+ * pairs reflected through the slice centre, u -> 2c - u); the rest the generic
+ * kernel, or from 1.5e10 updates the mirror kernel's form for two slices of any
+ * geometry.  FBP over a half turn uses
  * scale = pi / N_p (xct_fbp_batch applies it itself). */
 int xct_backproject(const xct_geometry *g, int32_t n_slices, const void *sino, int32_t sino_t,
                     float *image, float scale, int32_t accumulate, xct_stream stream);
@@ -197,7 +198,10 @@ int xct_backproject(const xct_geometry *g, int32_t n_slices, const void *sino, i
 /* Back-projection with the volume-storage epilogue of the reconstruction
  * pipeline (Section V-A c, stage 4: slices normalised by a CT-number range and
  * quantised to 16-bit unsigned integers).  Each voxel's attenuation
- *   mu = scale * (A^T sino)      (FP32, by the vector kernels at any size)
+ *   mu = scale * (A^T sino)      (FP32, by the vector kernels at any size: to
+ *                                the bit xct_backproject's image below 1.5e10
+ *                                voxel updates, which may take other kernels
+ *                                from there on)
  * becomes the CT number HU = 1000 (mu - mu_water) / mu_water, and the range
  * [hu_min, hu_max] maps linearly onto the codes [0, 65535]:
  *   code = clamp(rint(fl(fl(mu * a) + b)), 0, 65535)

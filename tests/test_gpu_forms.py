@@ -365,3 +365,36 @@ def test_split_table_in_ranges(xct, case):
     for z in range(S):
         assert rel_l2(got[z].cpu(), ref[z].cpu()) < TOL, z
         assert rel_l2(added[z].cpu(), -0.5 * ref[z].cpu()) < TOL, z
+
+
+@pytest.mark.parametrize("S, nx, ny, na, nd, c", [
+    (9, 700, 700, 800, 991, 495.0),      # symmetric
+    (9, 801, 702, 701, 1135, 567.0),     # mirror, more items than two rounds
+    (5, 1100, 1000, 601, 1557, 777.7),   # generic
+    (8, 1408, 1408, 1024, 1992, 995.5),  # from 1.5e10 updates: the image on the matrix cores
+])
+def test_codes_against_the_image(xct, S, nx, ny, na, nd, c):
+    """Codes are the documented rounding of xct_backproject's image below 1.5e10
+    updates, and within one code of it where that image takes other kernels."""
+    g = synth.Geometry(n_angles=na, n_det=nd, nx=nx, ny=ny, center=c)
+    water, lo, hi = 0.3, -1000.0, 4000.0
+    q = torch.randn((S, na, nd), generator=torch.Generator().manual_seed(nx)).cuda()
+    scale = 0.3 / math.sqrt(na)
+    codes = torch.empty((S, ny, nx), dtype=torch.uint16, device="cuda")
+    image = torch.empty((S, ny, nx), device="cuda")
+    say("codes", nx, na)
+    xct.xct_backproject_u16(g, q, codes, scale, water, lo, hi)
+    xct.xct_backproject(g, q, image, scale)
+    torch.cuda.synchronize()
+    span = 65535.0 / (hi - lo)
+    a, b = np.float32(1000.0 / water * span), np.float32((-1000.0 - lo) * span)
+    mu = image.cpu().numpy()
+    want = np.clip(np.rint(mu * a + b), 0, 65535).astype(np.int64)
+    off = np.abs(codes.cpu().numpy().astype(np.int64) - want)
+    assert (want > 0).mean() > 0.3 and (want < 65535).mean() > 0.3
+    if S * na * nx * ny < 1.5e10:
+        assert off.max() == 0
+    else:
+        assert on_matrix_cores(xct, g, S) is not None
+        # (images 5e-6 apart, 11,000 codes of spread: some 0.04 codes on average)
+        assert off.max() <= 1 and (off > 0).mean() < 0.1
