@@ -41,7 +41,8 @@ FP32_VECTOR_PEAK_TFLOPS = 157.3
 CUS, CLOCK_HZ = 256, 2.4e9
 # The matrix-core back-projection: three 2:4 sparse FP16 products of 16 x 16 x
 # 32 (dense-equivalent flops) per 16 pixels x 16 columns x 4 angles, each 16
-# cycles of one of a CU's four matrix units
+# cycles of one of a CU's four matrix units: half of the rate of the unit's
+# longest sparse product (16 x 16 x 64 in the same cycles)
 MATRIX_FLOPS_PER_UPDATE = 3 * 2 * 16 * 16 * 32 / (16 * 16 * 4)
 MATRIX_PEAK_TFLOPS = CUS * 4 * (2 * 16 * 16 * 32 / 16) * CLOCK_HZ / 1e12
 HBM_PEAK_GBPS = 8000.0
@@ -105,8 +106,12 @@ def _alu_roofline(kernel, updates, ms):
 
 def _matrix_roofline(kernel, updates, ms):
     achieved = MATRIX_FLOPS_PER_UPDATE * updates / (ms * 1e-3) / 1e12
+    alu = _alu_roofline(kernel, updates, ms)  # the algorithm's own operations
     return {"kernel": kernel, "bound": "mfma", "achieved": achieved, "peak": MATRIX_PEAK_TFLOPS,
-            "unit": "TFLOP/s", "frac": achieved / MATRIX_PEAK_TFLOPS}
+            "unit": "TFLOP/s", "frac": achieved / MATRIX_PEAK_TFLOPS,
+            "frac_of_longest_sparse_product": achieved / (2 * MATRIX_PEAK_TFLOPS),
+            "algorithmic_flops_per_update": FLOPS_PER_UPDATE, "algorithmic_tflops": alu["achieved"],
+            "frac_of_fp32_vector_peak": alu["frac"]}
 
 
 def tile_pixels(ny, nx, seed, full_rows=0):

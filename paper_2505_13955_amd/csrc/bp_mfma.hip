@@ -8,7 +8,7 @@
 // non-zeros per angle) and B [angle, bin][column] the samples.  The vector
 // kernels (bp.hip) read 8 bytes of LDS and issue some three instructions per
 // update and are bound by the LDS; here a weight is formed once for all
-// columns and a sample is read once per 64 pixels.
+// columns and a sample is read once per 16 pixels.
 //
 // Precision.  FP32 operands are split into two FP16 halves: samples scaled by
 // a power of two (per slice, so that its largest magnitude lies in
@@ -44,8 +44,9 @@
 // What bounds it: with 64 columns the matrix cores, the vector instructions and
 // the LDS together (0.52 of the matrix units' cycles, 0.39 vector instructions a
 // cycle and CU, LDS 0.73 at 2.07 GHz; 16 x 2048^2 x 1800 angles: 4.94 ms, 24,450
-// GUPS; the vector kernels 8.4 ms); with 32 and 16 columns the vector
-// instructions that form the weights (0.84 and 0.87; 4 x 4096^2 x 1023 angles
+// GUPS; the vector kernels 8.4 ms; the instruction does half the products of
+// the unit's longest, 16 x 16 x 64 in the same cycles); with 32 and 16 columns
+// the vector instructions that form the weights (0.84 and 0.87; 4 x 4096^2 x 1023 angles
 // with 16 columns: 3.63 ms, 18,900 GUPS, the vector kernels 5.90 ms).
 // Blocks of 8 x 8 pixels with four groups of four bins and 32 x 32 tiles took
 // half the LDS reads but twice the cycles of the matrix unit and two more
