@@ -398,3 +398,26 @@ def test_codes_against_the_image(xct, S, nx, ny, na, nd, c):
         assert on_matrix_cores(xct, g, S) is not None
         # (images 5e-6 apart, 11,000 codes of spread: some 0.04 codes on average)
         assert off.max() <= 1 and (off > 0).mean() < 0.1
+
+
+def test_batch_captured_after_an_eager_call(xct):
+    """A batch takes the same forms under capture: its scratch is the caller's."""
+    slabs = []
+    for i, (S, nx, ny, na, nd, c) in enumerate([(1, 256, 256, 360, 367, 183.0), (4, 813, 811, 602, 1160, 579.5),
+                                                (2, 131, 77, 163, 150, 74.3)]):
+        g = synth.Geometry(n_angles=na, n_det=nd, nx=nx, ny=ny, center=c)
+        p = torch.randn((S, na, nd), generator=torch.Generator().manual_seed(i)).cuda()
+        slabs.append((g, p, torch.empty((S, ny, nx), device="cuda")))
+    ws = torch.empty(xct.xct_fbp_workspace_bytes(slabs), dtype=torch.uint8, device="cuda")
+    say("captured batch")
+    xct.xct_fbp_batch(slabs, "hann", workspace=ws)
+    graph = captured(lambda: xct.xct_fbp_batch(slabs, "hann", workspace=ws))
+    for k in range(3):
+        for i, (_, p, _) in enumerate(slabs):
+            p.copy_(torch.randn(p.shape, generator=torch.Generator().manual_seed(10 * k + i)))
+        want = [torch.empty_like(img) for _, _, img in slabs]
+        xct.xct_fbp_batch([(g, p, w) for (g, p, _), w in zip(slabs, want)], "hann")
+        graph.replay()
+        torch.cuda.synchronize()
+        for (_, _, img), w in zip(slabs, want):
+            assert torch.equal(img, w)
