@@ -682,6 +682,9 @@ double rounds_ns(const KernelTimes &t, int64_t n, int64_t cus, double angles, do
     return (n / slots) * full + (rest == 0 ? 0.0 : held <= 1.0 ? alone : alone + (full - alone) * (held - 1.0) / (t.per_cu - 1.0));
 }
 
+// Angles that a work item of a job walks.
+int item_angles(const BPJob &j) { return j.parts < 2 ? j.g->n_angles : j.part_len * (j.path == kPathSymmetric ? 2 : 1); }
+
 // The share of a job's whole walks in rounds that fill the device.
 double vector_share_ns(const BPJob &j)
 {
@@ -705,8 +708,18 @@ double bp_vector_ns(const BPJob &j, double stores)
     KernelTimes t = vector_times(j.path, spi, n, j.cus);
     if (j.path != kPathGeneric && bp_sym_window(window_entries(j.g->pixel_size / j.g->det_pitch)) > 96) t.full *= 1.13, t.alone *= 1.13;
     if (j.parts < 2) return rounds_ns(t, n, j.cus, j.g->n_angles, stores);
-    const double per_part = (double)j.part_len * (j.path == kPathSymmetric ? 2 : 1);
-    return rounds_ns(t, n, j.cus, per_part, stores) + sum_ns(j, j.parts);
+    return rounds_ns(t, n, j.cus, item_angles(j), stores) + sum_ns(j, j.parts);
+}
+
+// At most `want` parts of whole LDS stages, as equal as these allow.
+void set_parts(BPJob &j, int64_t want)
+{
+    int spi;
+    const int64_t items = vector_items(j, &spi);
+    const int kb = vector_shape(j.path, window_entries(j.g->pixel_size / j.g->det_pitch), spi, items, j.cus).kb;
+    const int64_t units = j.path == kPathSymmetric ? j.g->n_angles / 2 : j.g->n_angles;
+    j.part_len = (int)(((units + want - 1) / want + kb - 1) / kb * kb);
+    j.parts = (int)((units + j.part_len - 1) / j.part_len);
 }
 
 // Parts of a small job's angles: a workgroup walks all angles of its tile, so
@@ -728,8 +741,7 @@ void plan_parts(BPJob &j)
     BPJob t = j;
     double least = 0.95 * bp_vector_ns(j, 0);
     for (int64_t want = 2; want <= most && want <= 64; want += 1 + want / 8) {
-        t.part_len = (int)((units + want - 1) / want + v.kb - 1) / v.kb * v.kb;
-        t.parts = (units + t.part_len - 1) / t.part_len;
+        set_parts(t, want);
         const double ns = t.parts < 2 ? least : bp_vector_ns(t, 0);
         if (ns < least) {
             least = ns;
@@ -1592,8 +1604,20 @@ struct BatchPlan {
     std::vector<BPJob> jobs;
     std::vector<MXPlan> mx;
     size_t scratch = 0;  // bytes behind the base: the matrix-core launches use them in turn, then the split slabs' copies
-    bool spread = false; // the vector launch splits the slabs that ask for it
 };
+
+// Launch groups of a batch: the generic kernel; slices in pairs, the mirror and
+// the symmetric kernel, each with one slice (pair) per item or two.
+enum { kGroupGeneric = 0, kGroupPairs1, kGroupPairs2, kGroupPairs3, kGroupMirror1, kGroupMirror2, kGroupSym1, kGroupSym2, kGroups };
+
+static int launch_group(const BPJob &j)
+{
+    const int spi = item_slices(j), two = spi == 2;
+    return j.path == kPathGeneric  ? kGroupGeneric
+           : j.path == kPathPairs  ? (spi == 3 ? kGroupPairs3 : two ? kGroupPairs2 : kGroupPairs1)
+           : j.path == kPathMirror ? (two ? kGroupMirror2 : kGroupMirror1)
+                                   : (two ? kGroupSym2 : kGroupSym1);
+}
 
 static void batch_jobs(const xct_slab *slabs, int32_t n_slabs, BatchPlan &b)
 {
@@ -1613,49 +1637,144 @@ static int check_batch_items(const BatchPlan &b)
     return XCT_OK;
 }
 
+// Estimated time of the jobs' launches in turn, a group at a time, and of the
+// sum of the split jobs' copies.  A group of items that the device holds at once,
+// or of items that are all alike, takes its rounds; else the items' shares of the
+// device and for the tail part of a mean walk, or what the longest walk, begun
+// at the rate of a full device, has left.
+static double launches_ns(const std::vector<BPJob> &jobs)
+{
+    struct Group { int64_t items = 0; double least = 0, most = 0, share = 0, walks = 0; KernelTimes t; } groups[kGroups];
+    double sums = 0, ns = 0;
+    auto angles = [](const BPJob &j) { return (double)item_angles(j); };
+    int spi;
+    for (const BPJob &j : jobs) {
+        Group &grp = groups[launch_group(j)];
+        grp.least = grp.items ? std::min(grp.least, angles(j)) : angles(j);
+        grp.most = std::max(grp.most, angles(j));
+        grp.items += vector_items(j, &spi) * j.parts;
+    }
+    for (const BPJob &j : jobs) {
+        Group &grp = groups[launch_group(j)];
+        const double n = (double)vector_items(j, &spi) * j.parts;
+        grp.t = vector_times(j.path, spi, grp.items, j.cus);
+        const double walk = grp.t.full * angles(j) + grp.t.store;
+        grp.share += n / (grp.t.per_cu * (double)j.cus) * walk;
+        grp.walks += n * walk;
+        if (j.parts > 1) sums += 1000.0 + (j.parts + 1) * (double)image_bytes(j) / 6700.0;
+    }
+    for (const Group &grp : groups) {
+        if (!grp.items) continue;
+        const int cus = jobs[0].cus;
+        const double left = std::max(0.0, grp.most - grp.share / grp.t.full) * grp.t.alone;
+        ns += 6000.0 + (grp.items <= grp.t.per_cu * (int64_t)cus || grp.least == grp.most
+                            ? rounds_ns(grp.t, grp.items, cus, grp.most, 1)
+                            : grp.share + std::max(left, 0.4 * grp.walks / grp.items));
+    }
+    return ns + (sums > 0 ? 5000.0 + sums : 0.0);
+}
+
+// How the vector kernels take a batch's slabs, given as they are taken alone,
+// with an estimate of the time.  Either that way, with no more parts for a slab
+// than cut the longest walks into four, three or two, where that saves 5 %, and
+// the room for copies to the longest walks first (8 slabs of 1 to 2 x 68^2 to
+// 1540 x 1138, 76 to 1484 angles: 1.22 ms, 2.26 where copies larger than the room
+// left every slab whole).  Or in whole walks, where slices of any geometry go in
+// pairs only if that is worth launches of their own behind the generic kernel's
+// (25 slabs of 1 to 30 slices of 63^2 to 1588^2: pairs, triples and singles in
+// three launches 1.38 ms, in one 0.90).  Whole walks are preferred up to 3 %.
+static double plan_vector(std::vector<BPJob> &jobs)
+{
+    std::vector<int> order;
+    int longest = 0;
+    bool generic = false;
+    for (size_t i = 0; i < jobs.size(); ++i) {
+        generic = generic || jobs[i].path == kPathPairs || jobs[i].path == kPathGeneric;
+        if (jobs[i].parts < 2) continue;
+        order.push_back((int)i);
+        longest = std::max(longest, jobs[i].g->n_angles);
+    }
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return jobs[x].g->n_angles > jobs[y].g->n_angles; });
+
+    std::vector<BPJob> apart, whole;
+    double apart_ns = 0, whole_ns = 0;
+    for (int most : {0, 4, 3, 2}) {
+        std::vector<BPJob> v = jobs;
+        size_t room = (size_t)kPartBytes;
+        for (int i : order) {
+            BPJob &j = v[i];
+            if (most) set_parts(j, std::min<int64_t>(j.parts, ((int64_t)j.g->n_angles * most + longest - 1) / longest));
+            const size_t bytes = part_bytes(j);
+            if (bytes <= room) room -= bytes;
+            else j.parts = 1;
+        }
+        const double ns = launches_ns(v);
+        if (!most || ns < 0.95 * apart_ns) {
+            apart_ns = ns;
+            apart.swap(v);
+        }
+        if (order.empty()) break;
+    }
+    for (int pairs = 0; pairs < (generic ? 8 : 1); ++pairs) {  // a bit for each of the groups in pairs
+        std::vector<BPJob> v = jobs;
+        for (BPJob &j : v) {
+            j.parts = 1;
+            if (j.path == kPathPairs) j.path = kPathGeneric;
+            BPJob two = j;
+            pair_slices(two);
+            if (two.path == kPathPairs && (pairs >> (launch_group(two) - kGroupPairs1) & 1)) j.path = kPathPairs;
+        }
+        const double ns = launches_ns(v);
+        if (!pairs || ns < whole_ns) {
+            whole_ns = ns;
+            whole.swap(v);
+        }
+    }
+    jobs.swap(whole_ns < 1.03 * apart_ns ? whole : apart);
+    return std::min(whole_ns, apart_ns);
+}
+
 // A slab alone is split, or goes to the matrix cores, partly because it leaves
 // the device idle otherwise.  In a batch that is no reason where the slabs fill
 // the device together: slabs that the matrix cores are not faster for per
-// share of the device join the one vector launch when that is estimated to
-// take less than their launches in turn (64 slabs of one 512^2 slice, 720
-// angles: 2.0 ms, and 2.5 on the matrix cores; 32 of four slices 2.4 and 3.3),
-// and parts are work items of their own in a vector launch that would not fill
-// the device without them.
+// share of the device join the vector launches when those are estimated to take
+// less than the slabs' launches in turn (64 slabs of one 512^2 slice, 720
+// angles: 1.9 ms, and 2.5 on the matrix cores; 32 of four slices 2.4 and 3.3).
 static void plan_batch(int32_t n_slabs, int32_t filtered_t, BatchPlan &b)
 {
     b.mx.resize(n_slabs);
-    double turns = 0, shares = 0, walk = 0;
-    auto joins = [&](int i) { return b.mx[i].cols && b.mx[i].ns >= vector_share_ns(b.jobs[i]); };
+    std::vector<int> joins;
+    double turns = 0;
+    std::vector<BPJob> apart, joined;  // the vector kernels' jobs without and with those slabs
     for (int i = 0; i < n_slabs; ++i) {
         BPJob &j = b.jobs[i];
         plan_alone(j);
         b.mx[i] = mx_plan(j, filtered_t);
-        if (!joins(i)) continue;
-        turns += b.mx[i].ns;
-        shares += vector_share_ns(j);
-        const KernelTimes t = vector_times(j.path, item_slices(j), 0, j.cus);
-        walk = std::max(walk, t.full * j.g->n_angles + t.store);
+        const bool may_join = n_slabs > 1 && b.mx[i].cols && b.mx[i].ns >= vector_share_ns(j);
+        if (may_join) {
+            joins.push_back(i);
+            turns += b.mx[i].ns;
+        }
+        if (!b.mx[i].cols) apart.push_back(j);
+        if (may_join || !b.mx[i].cols) joined.push_back(j);
     }
-    // (the vector launch ends with a tail of half a walk on average)
-    const bool join = n_slabs > 1 && shares + 0.5 * walk < turns;
-    size_t parts = 0;
-    int64_t items = 0;
+    if (n_slabs > 1) {
+        turns += plan_vector(apart);
+        if (!joins.empty() && plan_vector(joined) < turns) {
+            for (int i : joins) b.mx[i] = MXPlan();
+            apart.swap(joined);
+        }
+    }
+    size_t parts = 0, next = 0;
     for (int i = 0; i < n_slabs; ++i) {
-        if (join && joins(i)) b.mx[i] = MXPlan();
         if (b.mx[i].cols) {
             b.scratch = std::max(b.scratch, mx_scratch_bytes(b.jobs[i], b.mx[i]));
         } else {
-            BPJob j = b.jobs[i];
-            pair_slices(j);
-            int spi;
-            items += vector_items(j, &spi);
+            b.jobs[i] = apart[next++];
             parts += part_bytes(b.jobs[i]);
         }
     }
-    b.spread = items < 2 * (int64_t)device_cus() && parts <= (size_t)kPartBytes;
-    if (b.spread) b.scratch = std::max(b.scratch, parts);
-    else if (n_slabs > 1)
-        for (BPJob &j : b.jobs) pair_slices(j);
+    b.scratch = std::max(b.scratch, parts);
 }
 
 size_t xct_fbp_workspace_bytes(const xct_slab *slabs, int32_t n_slabs, int32_t filtered_t)
@@ -1704,10 +1823,6 @@ int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_
     // without the scratch every slab takes whole walks of the vector kernels
     const bool with_scratch = workspace_bytes >= base + b.scratch;
     float *partial = reinterpret_cast<float *>(ws + base);
-    // Launch groups: the generic kernel; slices in pairs, the mirror and the
-    // symmetric kernel, each with one slice (pair) per item or two.  A slab takes
-    // the vector kernel that a call with that slab alone takes.
-    enum { kGroupGeneric = 0, kGroupPairs1, kGroupPairs2, kGroupPairs3, kGroupMirror1, kGroupMirror2, kGroupSym1, kGroupSym2, kGroups };
     std::vector<BPJob> groups[kGroups];
     for (int i = 0; i < n_slabs; ++i) {
         if (i >= ahead)
@@ -1719,33 +1834,35 @@ int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_
             if (int rc = launch_bp_matrix(j, b.mx[i], filtered_t, ws + base, s)) return rc;
             continue;
         }
-        if (with_scratch && b.spread && part_bytes(j)) {
+        if (with_scratch && part_bytes(j)) {
             j.partial = partial;
             partial += part_bytes(j) / sizeof(float);
+        } else {
+            j.parts = 1;
         }
-        const int spi = item_slices(j), two = spi == 2;
-        const int grp = j.path == kPathGeneric  ? kGroupGeneric
-                        : j.path == kPathPairs  ? (spi == 3 ? kGroupPairs3 : two ? kGroupPairs2 : kGroupPairs1)
-                        : j.path == kPathMirror ? (two ? kGroupMirror2 : kGroupMirror1)
-                                                : (two ? kGroupSym2 : kGroupSym1);
-        groups[grp].push_back(j);
+        groups[launch_group(j)].push_back(j);
     }
     // A group whose items all fit on the device at once is launched with one
     // workgroup per item: no counters, and no workgroup that asks every XCD's
     // counter in turn before it ends (some 10 us of a call with one item each).
-    // So is one slab of less than a millisecond, whose items are all alike (26 x
+    // So is one of less than a millisecond whose items all walk as many angles (26 x
     // 780^2 x 33 angles 118 us, 166 with counters; longer, their order keeps rows
     // in cache: 46 x 1554^2 x 660, pixel 1.3, 7.5 ms with them, 8.0 without).
     bool persistent[kGroups], any = false;
     for (int grp = 0; grp < kGroups; ++grp) {
         int64_t items = 0;
         int spi = 1;
+        bool alike = true;
         for (const BPJob &j : groups[grp]) {
-            const int64_t n = vector_items(j, &spi);
-            items += j.partial ? n * j.parts : n;
+            items += vector_items(j, &spi) * j.parts;
+            alike = alike && item_angles(j) == item_angles(groups[grp][0]);
         }
-        const bool shared = groups[grp].size() > 1 || (groups[grp].size() == 1 && bp_vector_ns(groups[grp][0], 1) >= 1e6);
-        persistent[grp] = shared && items > vector_times(groups[grp][0].path, spi, items, device_cus()).per_cu * (int64_t)device_cus();
+        persistent[grp] = false;
+        if (!items) continue;
+        const BPJob &j = groups[grp][0];
+        const KernelTimes t = vector_times(j.path, spi, items, j.cus);
+        persistent[grp] = items > t.per_cu * (int64_t)j.cus &&
+                          (!alike || rounds_ns(t, items, j.cus, item_angles(j), 1) >= 1e6);
         any = any || persistent[grp];
     }
     hipError_t e = any ? launch_fill_u32(counters, kGroups * kXcds, 0u, s) : hipSuccess;
@@ -1760,13 +1877,17 @@ int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_
     for (int grp = kGroups - 1; grp >= 0; --grp)
         if (int rc = launch_bp_jobs(groups[grp], filtered_t, persistent[grp] ? counters + grp * kXcds : nullptr, group_table[grp], s))
             return rc;
+    std::vector<SumJob> sums;
     for (const auto &grp : groups)
-        for (const BPJob &j : grp) {
-            if (!j.partial) continue;
-            e = launch_sum_parts(static_cast<float *>(j.image), j.partial, j.parts, (int64_t)j.n_slices * j.g->nx * j.g->ny, 0, nullptr, s);
-            if (e != hipSuccess) return hip_fail(e);
-        }
-    return XCT_OK;
+        for (const BPJob &j : grp)
+            if (j.partial)
+                sums.push_back({static_cast<float *>(j.image), j.partial, (int64_t)j.n_slices * j.g->nx * j.g->ny, j.parts});
+    // (one image: four elements a thread where it is large)
+    if (sums.size() == 1)
+        e = launch_sum_parts(sums[0].image, sums[0].partial, (int)sums[0].parts, sums[0].n, 0, nullptr, s);
+    else
+        e = launch_sum_jobs(sums.data(), (int)sums.size(), s);
+    return e == hipSuccess ? XCT_OK : hip_fail(e);
 }
 
 size_t xct_reduce_workspace_bytes(int64_t n)

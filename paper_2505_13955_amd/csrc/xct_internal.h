@@ -127,6 +127,16 @@ struct MXArgs {
 // nothing if *skip is not 0 (nullptr: always runs).
 hipError_t launch_sum_parts(float *image, const float *partial, int parts, int64_t n, int accumulate,
                             const uint32_t *skip, hipStream_t s);
+
+// image = the sum of its `parts` copies of n floats, in order, for n_jobs images.
+struct SumJob {
+    float *image;
+    const float *partial;
+    int64_t n;
+    int64_t parts;
+};
+constexpr int kSumJobs = 64;  // images a launch carries in its arguments
+hipError_t launch_sum_jobs(const SumJob *jobs, int n_jobs, hipStream_t s);
 struct SplitArgs {
     const void *sino;      // [S][n_angles][Nc]
     uint4 *table;          // [S/4][rows][Nc]

@@ -307,6 +307,35 @@ def test_batch_of_matrix_and_split_slabs(xct, filtered):
         assert rel_l2(img[:, at[:, 0], at[:, 1]].cpu(), sampled(rows, g, at, math.pi / g.n_angles).cpu()) < TOL, i
 
 
+@pytest.mark.parametrize("case", [
+    # slabs, and the launches that sum their copies: 64 images a launch
+    ([(1, 40, 41, 400)] * 70, 2),
+    # the copies that these ask for alone are more than there is room for
+    ([(1, 1200, 1200, 900 + 40 * i) for i in range(5)] + [(1, 64, 64, 3000), (3, 300, 250, 200)], 1)])
+def test_batch_of_split_slabs(xct, case):
+    """Slabs of fractional axis that a batch splits: their copies are summed
+    together, the room for copies goes to the longest walks and the other
+    slabs walk whole; against separate calls (sums in another order: some
+    sqrt(angles) roundings of 2^-24)."""
+    sizes, launches = case
+    slabs, alone = [], 0
+    for i, (S, nx, ny, na) in enumerate(sizes):
+        nd = int(1.42 * max(nx, ny)) + 6
+        g = synth.Geometry(n_angles=na, n_det=nd, nx=nx, ny=ny, center=(nd - 1) / 2 + 0.3)
+        p = torch.randn((S, na, nd), generator=torch.Generator().manual_seed(i)).cuda()
+        slabs.append((g, p, torch.full((S, ny, nx), float("nan"), device="cuda")))
+        alone += xct.xct_fbp_workspace_bytes(slabs[-1:])
+    if len(sizes) < 64:
+        assert xct.xct_fbp_workspace_bytes(slabs) < alone - (64 << 20)
+    say("batch of split slabs", len(sizes))
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as trace:
+        xct.xct_fbp_batch(slabs, "hann")
+        torch.cuda.synchronize()
+    assert len([e for e in trace.events() if "sum_" in e.name and "kernel" in e.name]) == launches
+    for i, (g, p, img) in enumerate(slabs):
+        assert rel_l2(img.cpu(), xct.fbp(p, g, "hann").cpu()) < 5e-6, i
+
+
 @pytest.mark.parametrize("storage", [torch.float32, torch.float16, torch.bfloat16])
 @pytest.mark.parametrize("nx, ny, na, nd", [
     (1024, 1024, 1024, 1449),  # quarter turn
