@@ -1821,7 +1821,11 @@ int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_
         if (int rc = filter_slab(i)) return rc;
     plan_batch(n_slabs, filtered_t, b);
     // without the scratch every slab takes whole walks of the vector kernels
-    const bool with_scratch = workspace_bytes >= base + b.scratch;
+    if (workspace_bytes < base + b.scratch) {
+        std::fill(b.mx.begin(), b.mx.end(), MXPlan());
+        for (BPJob &j : b.jobs) j.parts = 1;
+        plan_vector(b.jobs);
+    }
     float *partial = reinterpret_cast<float *>(ws + base);
     std::vector<BPJob> groups[kGroups];
     for (int i = 0; i < n_slabs; ++i) {
@@ -1830,11 +1834,11 @@ int xct_fbp_batch(const xct_slab *slabs, int32_t n_slabs, int32_t sino_t, int32_
         BPJob &j = b.jobs[i];
         j.sino = rows[i];
         if (int rc = geo_tables(j.g, s, &j.t)) return rc;
-        if (with_scratch && b.mx[i].cols) {
+        if (b.mx[i].cols) {
             if (int rc = launch_bp_matrix(j, b.mx[i], filtered_t, ws + base, s)) return rc;
             continue;
         }
-        if (with_scratch && part_bytes(j)) {
+        if (part_bytes(j)) {
             j.partial = partial;
             partial += part_bytes(j) / sizeof(float);
         } else {

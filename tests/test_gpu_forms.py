@@ -318,22 +318,31 @@ def test_batch_of_split_slabs(xct, case):
     slabs walk whole; against separate calls (sums in another order: some
     sqrt(angles) roundings of 2^-24)."""
     sizes, launches = case
-    slabs, alone = [], 0
+    slabs, asked = [], 0
     for i, (S, nx, ny, na) in enumerate(sizes):
         nd = int(1.42 * max(nx, ny)) + 6
         g = synth.Geometry(n_angles=na, n_det=nd, nx=nx, ny=ny, center=(nd - 1) / 2 + 0.3)
         p = torch.randn((S, na, nd), generator=torch.Generator().manual_seed(i)).cuda()
         slabs.append((g, p, torch.full((S, ny, nx), float("nan"), device="cuda")))
-        alone += xct.xct_fbp_workspace_bytes(slabs[-1:])
+        asked += xct.xct_fbp_workspace_bytes(slabs[-1:])
     if len(sizes) < 64:
-        assert xct.xct_fbp_workspace_bytes(slabs) < alone - (64 << 20)
+        assert xct.xct_fbp_workspace_bytes(slabs) < asked - (64 << 20)
     say("batch of split slabs", len(sizes))
     with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as trace:
         xct.xct_fbp_batch(slabs, "hann")
         torch.cuda.synchronize()
     assert len([e for e in trace.events() if "sum_" in e.name and "kernel" in e.name]) == launches
+    alone = [xct.fbp(p, g, "hann") for g, p, img in slabs]
     for i, (g, p, img) in enumerate(slabs):
-        assert rel_l2(img.cpu(), xct.fbp(p, g, "hann").cpu()) < 5e-6, i
+        assert rel_l2(img.cpu(), alone[i].cpu()) < 5e-6, i
+    # without room for the copies every slab walks whole
+    ws = torch.empty(xct.xct_fbp_workspace_bytes(slabs) - 256, dtype=torch.uint8, device="cuda")
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as trace:
+        xct.xct_fbp_batch(slabs, "hann", workspace=ws)
+        torch.cuda.synchronize()
+    assert not [e for e in trace.events() if "sum_" in e.name and "kernel" in e.name]
+    for i, (g, p, img) in enumerate(slabs):
+        assert rel_l2(img.cpu(), alone[i].cpu()) < 5e-6, i
 
 
 @pytest.mark.parametrize("storage", [torch.float32, torch.float16, torch.bfloat16])
