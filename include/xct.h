@@ -293,20 +293,19 @@ size_t xct_fbp_workspace_bytes(const xct_slab *slabs, int32_t n_slabs, int32_t f
  * V-A b):
  *   image = (pi / N_p) A^T ((1/det_pitch) h_W * sino)      per slice
  * The filter runs over every row of every slab into `workspace` (stored as
- * filtered_t), then ONE persistent back-projection launch per kernel variant
- * (the quarter-turn symmetric kernel, the mirror kernel and the generic
- * kernel, the first two with two slices per work item or, for single-slice
- * slabs, one)
- * walks all (slab, slice, tile) work items, most expensive slab first; the
- * work counters and the table of slab descriptors also live in the
- * workspace.  Slabs that the matrix cores are faster for are launched on their
- * own before it (their operands split as in xct_backproject).  A slab too small
- * to fill the device has its angles split into parts, work items of their own
- * whose images are added up in a fixed order, or takes the matrix cores, where
- * the batch does not fill the device either; in a batch that does, it is walked
- * whole in the one launch.  So the images of a slab equal those of a separate
- * call bit for bit where both take the same form, and within FP32 rounding
- * otherwise.
+ * filtered_t), then one back-projection launch per kernel variant (the
+ * quarter-turn symmetric kernel, the mirror kernel, slices in pairs and the
+ * generic kernel, by the slices per work item) walks all (slab, slice, tile)
+ * work items, most expensive slab first; the work counters of launches that are
+ * persistent and the table of slab descriptors also live in the workspace.
+ * Slabs that the matrix cores are faster for are launched on their own before
+ * it (their operands split as in xct_backproject).  A slab too small to fill the
+ * device has its angles split into parts, work items of their own whose images
+ * are added up in a fixed order, or takes the matrix cores, as far as the batch
+ * does not fill the device either: the form of each slab is the one that makes
+ * the batch's launches together shortest by an estimate.  So the images of a
+ * slab equal those of a separate call bit for bit where both take the same form,
+ * and within FP32 rounding otherwise.
  * (A workspace that covers only the counters, table and filtered rows is
  * accepted: every slab is then walked whole by the vector kernels.)  workspace: device, 256-byte aligned,
  * at least xct_fbp_workspace_bytes(); its contents are scratch, and calls
