@@ -1681,8 +1681,8 @@ static double launches_ns(const std::vector<BPJob> &jobs)
 // 1540 x 1138, 76 to 1484 angles: 1.22 ms, 2.26 where copies larger than the room
 // left every slab whole).  Or in whole walks, where slices of any geometry go in
 // pairs only if that is worth launches of their own behind the generic kernel's
-// (25 slabs of 1 to 30 slices of 63^2 to 1588^2: pairs, triples and singles in
-// three launches 1.38 ms, in one 0.90).  Whole walks are preferred up to 3 %.
+// (25 slabs of 1 to 30 slices of 63^2 to 1588^2: triples, pairs, single pairs and
+// the rest in four launches 2.15 ms, in one 0.90).  Whole walks are preferred up to 3 %.
 static double plan_vector(std::vector<BPJob> &jobs)
 {
     std::vector<int> order;

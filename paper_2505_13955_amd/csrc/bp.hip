@@ -880,8 +880,9 @@ hipError_t launch_sum_parts(float *image, const float *partial, int parts, int64
 }
 
 // The same for several images at once, one a row of the grid: a batch's split
-// slabs are small, and a launch for each costs more than its sum (14 images of
-// 5 x 75^2: 5 us each, 6 together).
+// slabs are small, and a launch for each costs more than its sum (60 images of
+// 40 x 41, 2.8 us each, 4.2 together, and the host's time: the batch of 60 slabs,
+// 400 angles, 1147 us with a launch for each, 962).
 struct SumChunk {
     SumJob job[kSumJobs];
 };
