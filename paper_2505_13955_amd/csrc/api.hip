@@ -781,9 +781,9 @@ int launch_bp_jobs(std::vector<BPJob> jobs, int dtype, unsigned int *counters, B
 {
     if (jobs.empty()) return XCT_OK;
     const int path = jobs[0].path;
-    // largest cost per item first (items of one slab cost the same)
+    // longest items first (those of one slab cost the same; a split slab's are short)
     std::stable_sort(jobs.begin(), jobs.end(),
-                     [](const BPJob &a, const BPJob &b) { return a.g->n_angles > b.g->n_angles; });
+                     [](const BPJob &a, const BPJob &b) { return item_angles(a) > item_angles(b); });
     // two slices (pairs) per work item when every slab has at least two
     int spi = item_slices(jobs[0]);
     bool split = gate != nullptr;
